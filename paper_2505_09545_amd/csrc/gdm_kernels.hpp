@@ -254,12 +254,11 @@ struct LUWork {
   int32_t* npairs;           // [nblocks]
   int32_t* spec;             // [nblocks] speculative panel failed its check (after npairs, same item stride)
   void* tmp;                 // [tmp_elems] complex scratch (operand copies, split-k partials, solve sweeps)
-  void* dinv;                // [nblocks][nb][nb] complex inverses of the diagonal triangles
-  void* l21c;                // speculative panels: copy of the rows below the diagonal block (n x nb complex)
+  void* tinv;                // [nblocks][tinv_block_elems(nb)] complex inverses of the 16 x 16 diagonal triangles
   std::vector<hipEvent_t>* events;  // host-side pool of reusable events (look-ahead)
   int64_t tmp_elems;         // capacity of tmp per item in complex elements
   int nbatch = 1;
-  int64_t s_cand = 0, s_rows = 0, s_pairs = 0, s_npairs = 0, s_tmp = 0, s_dinv = 0, s_l21c = 0;
+  int64_t s_cand = 0, s_rows = 0, s_pairs = 0, s_npairs = 0, s_tmp = 0, s_tinv = 0;
   size_t bytes = 0;          // total size (set by lu_workspace_carve)
 };
 
@@ -276,6 +275,32 @@ hipError_t lu_prepare(const LUPlan& plan);
 bool lu_plan_fits(const LUPlan& p);
 size_t lu_workspace_bytes(const LUPlan& p, int elem_bytes, int num_cu, int nbatch = 1);
 void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu, LUWork& w, int nbatch = 1);
+
+// Triangular block operations on 16 x 16 matrix-core tiles (tiles.hip).  Block at
+// (k0, k0), width w <= nb <= 128; tinv: the block's tile inverses
+// (tinv_block_elems(nb) complex), all with an item stride for batches.
+int64_t tinv_block_elems(int nb);
+template <typename T>
+hipError_t prepare_diag_lu();  // one-time host-side setting (before any graph capture)
+// speculative diagonal block: factors, checks (*flag |= 1), identity pivots, tile inverses
+template <typename T>
+hipError_t launch_diag_lu(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, int32_t* ipiv, int32_t* flag,
+                          cplx<T>* tinv, hipStream_t st, int nbatch, int64_t sA, int64_t sipiv, int64_t sflag,
+                          int64_t stinv);
+// tile inverses of a block that a pivoting panel factored
+template <typename T>
+hipError_t launch_tile_inv(const cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, cplx<T>* tinv, hipStream_t st,
+                           int nbatch, int64_t sA, int64_t stinv);
+// the nrows rows below the block become L21 = A21 U11^-1 (checked against the
+// pivots), and columns [cu, cu + ncols) of the block's rows U12 = L11^-1 A12
+template <typename T>
+hipError_t launch_tri_panel(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, int64_t nrows, int64_t cu, int64_t ncols,
+                            const cplx<T>* tinv, int32_t* flag, hipStream_t st, int nbatch, int64_t sA, int64_t stinv,
+                            int64_t sflag);
+// solve-ready form of every block; tinv: the first block's tile inverses
+template <typename T>
+hipError_t launch_finish(cplx<T>* A, int64_t ld, int64_t n, int nb, const cplx<T>* tinv, hipStream_t st, int nbatch,
+                         int64_t sA, int64_t stinv);
 
 // `side` (may be null): second stream for the look-ahead; all work is joined
 // back into `st` before return.  Batch (ws.nbatch items): matrix z at A + z sA,

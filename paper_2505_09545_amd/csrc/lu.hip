@@ -15,11 +15,11 @@
 //      form
 //          M = P1^T L1 P2^T L2 ... Pk^T Lk U
 //      and the solve applies P_b before using L_b, which is equivalent.
-//   3. U12 = L11^-1 A12 (by substitution for the next panel's columns, by a
-//      product with the inverse of L11 for the rest), 4. A22 -= L21 U12
-//      (complex GEMM on MFMA, gemm.hip).  With look-ahead, steps 3-4 for the
-//      next panel's columns run on the main stream and the rest of the trailing
-//      matrix on a side stream, overlapping the next panel.
+//   3. U12 = L11^-1 A12 (tiles.hip), 4. A22 -= L21 U12 (complex GEMM on MFMA,
+//      gemm.hip).  With look-ahead, steps 3-4 for the next panel's columns run
+//      on the main stream and the rest of the trailing matrix on a side stream,
+//      overlapping the next panel.
+//   5. after the last block, the solve-ready form of all blocks (tiles.hip).
 //
 // Layout: column-major interleaved complex, leading dimension ld.  ipiv holds
 // 0-based global row indices (LAPACK semantics otherwise).
@@ -33,37 +33,11 @@
 
 #include "gdm_common.hpp"
 #include "gdm_kernels.hpp"
+#include "lu_common.hpp"
 
 namespace gdm {
 
 constexpr uint32_t SPIN_LIMIT = 1u << 22;
-
-template <typename CT> __device__ inline CT cmul_t(CT a, CT b) {
-  CT r;
-  r.x = a.x * b.x - a.y * b.y;
-  r.y = a.x * b.y + a.y * b.x;
-  return r;
-}
-// t - l u: one entry of a rank-1 update
-template <typename CT> __device__ inline CT r1_upd(CT t, const CT& l, const CT& u) {
-  t.x -= l.x * u.x - l.y * u.y;
-  t.y -= l.x * u.y + l.y * u.x;
-  return t;
-}
-template <typename CT> __device__ inline CT cinv_t(CT a) {
-  // 1/a = conj(a) / |a|^2, with a scaled by the power of two 2^-e of its larger
-  // component (exact) so that |a|^2 can neither overflow nor underflow; one
-  // division (a = 0 gives NaN, as the quotient form did)
-  const auto s = fabs(a.x) > fabs(a.y) ? fabs(a.x) : fabs(a.y);
-  int e;
-  (void)frexp(s, &e);
-  const auto ar = ldexp(a.x, -e), ai = ldexp(a.y, -e);
-  const auto id = 1 / (ar * ar + ai * ai);
-  CT r;
-  r.x = ldexp(ar * id, -e);
-  r.y = ldexp(-ai * id, -e);
-  return r;
-}
 
 __device__ inline unsigned long long shfl_xor_u64(unsigned long long v, int m) {
   const unsigned lo = __shfl_xor((unsigned)(v & 0xffffffffu), m);
@@ -140,17 +114,6 @@ __device__ inline void ll_get_n(const u64* const (&p)[K], uint32_t epoch, uint32
   }
 #pragma unroll
   for (int i = 0; i < K; ++i) out[i] = (uint32_t)v[i];
-}
-
-// f(0), f(1), ..., f(N - 1) with compile-time indices (expanded whatever the
-// unroller decides, so register arrays indexed by them stay in registers)
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 // CPT records of KW consecutive words each (record u at base[u]), returned once
@@ -1208,578 +1171,6 @@ __global__ void __launch_bounds__(256) row_permute_inv_kernel(cplx<T>* __restric
 }
 
 // ---------------------------------------------------------------------------
-// 3. small triangular solves op(Tri) X = B for a w x ncols block B (in place)
-// ---------------------------------------------------------------------------
-// KIND 0: L unit lower (forward)        KIND 1: U upper non-unit (backward)
-// KIND 2: U^T lower non-unit (forward)  KIND 3: L^T upper unit (backward)
-// Wave-synchronous substitution (w <= 128): each wave owns CPW columns of B in
-// registers, lane l holding rows l and l + 64; x_j is broadcast from its owner
-// lane with readlane, so the w sequential steps need no workgroup barrier.  The
-// columns of op(Tri) are staged in LDS, PW at a time, shared by the 4 waves.
-constexpr int TRSM_LS_BYTES = 64 * 1024;
-
-__device__ inline float2 readlane_c(float2 v, int l) {
-  return make_float2(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v.x), l)),
-                     __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v.y), l)));
-}
-__device__ inline double readlane_d(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ inline double2 readlane_c(double2 v, int l) { return make_double2(readlane_d(v.x, l), readlane_d(v.y, l)); }
-
-// Substitution sweep on register-resident columns b (lane l holds rows l, l+64).
-template <typename T, int KIND, int CPW>
-__device__ inline void trsm_sweep(const cplx<T>* __restrict__ Tri, int64_t ldt, int w, cplx<T> (&b)[2][CPW],
-                                  cplx<T>* Ls, int PW) {
-  using CT = cplx<T>;
-  const int tid = threadIdx.x, lane = tid & 63;
-  constexpr bool forward = (KIND == 0 || KIND == 2);
-  constexpr bool unit = (KIND == 0 || KIND == 3);
-  constexpr bool transposed = (KIND >= 2);
-  // this lane's two rows, clamped into the staged column (masked below)
-  const int i0 = lane < w ? lane : w - 1, i1 = lane + 64 < w ? lane + 64 : w - 1;
-  for (int ph = 0; ph < w; ph += PW) {
-    const int pw = w - ph < PW ? w - ph : PW;
-    // columns of op(Tri) handled in this phase: [jb, jb + pw); rows needed: [lo, hi)
-    const int jb = forward ? ph : w - ph - pw;
-    const int lo = forward ? jb : 0;
-    const int hi = forward ? w : jb + pw;
-    const int len = hi - lo;
-    __syncthreads();
-    // staged in batches of SB loads in flight per thread (then a remainder)
-    constexpr int SB = 128 / (int)sizeof(CT);
-    const int tot = pw * len, full = tot - tot % (256 * SB);
-    auto at = [&](int idx, int& i, int& cc) {
-      if (!transposed) { i = lo + idx % len; cc = idx / len; }
-      else { cc = idx % pw; i = lo + idx / pw; }
-    };
-    for (int base = tid; base < full; base += 256 * SB) {
-      CT v[SB];
-#pragma unroll
-      for (int u = 0; u < SB; ++u) {
-        int i, cc;
-        at(base + 256 * u, i, cc);
-        const int j = jb + cc;
-        v[u] = transposed ? Tri[j + (int64_t)i * ldt] : Tri[i + (int64_t)j * ldt];
-      }
-#pragma unroll
-      for (int u = 0; u < SB; ++u) {
-        int i, cc;
-        at(base + 256 * u, i, cc);
-        Ls[cc * w + i] = v[u];
-      }
-    }
-    for (int idx = full + tid; idx < tot; idx += 256) {
-      int i, cc;
-      at(idx, i, cc);
-      const int j = jb + cc;
-      Ls[cc * w + i] = transposed ? Tri[j + (int64_t)i * ldt] : Tri[i + (int64_t)j * ldt];
-    }
-    __syncthreads();
-    // Columns [jb, jb + pw) in order; x_j sits in lane j & 63 of half j >> 6, so
-    // the sweep is split at column 64 to make that half a compile-time choice.
-    // The L entries of the next steps do not depend on x: with no branches in
-    // the loop their LDS reads can run ahead of the substitution chain.
-    auto sweep = [&](auto half, int ja, int jz) __attribute__((always_inline)) {
-      constexpr int H = decltype(half)::value;
-      const int cnt = jz - ja;
-      if (cnt <= 0) return;
-      // this lane's entries of the next column, read one step ahead
-      const CT* lnext = Ls + ((forward ? ja : jz - 1) - jb) * w;
-      CT n0 = lnext[i0], n1 = lnext[i1];
-      for (int s = 0; s < cnt; ++s) {
-        const int j = forward ? ja + s : jz - 1 - s;
-        const CT* lcol = Ls + (j - jb) * w;
-        const CT l0 = n0, l1 = n1;
-        if (s + 1 < cnt) {
-          lnext = lcol + (forward ? w : -w);
-          n0 = lnext[i0];
-          n1 = lnext[i1];
-        }
-        const bool a0 = forward ? (lane > j && lane < w) : (lane < j);
-        const bool a1 = forward ? (lane + 64 > j && lane + 64 < w) : (lane + 64 < j);
-        CT x[CPW];
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) x[c] = readlane_c(b[H][c], j & 63);
-        if (!unit) {
-          const CT inv = cinv_t(lcol[j]);
-#pragma unroll
-          for (int c = 0; c < CPW; ++c) {
-            x[c] = cmul_t(x[c], inv);
-            if (lane == (j & 63)) b[H][c] = x[c];
-          }
-        }
-#pragma unroll
-        for (int c = 0; c < CPW; ++c) {
-          CT u0 = b[0][c], u1 = b[1][c];
-          u0.x -= l0.x * x[c].x - l0.y * x[c].y;
-          u0.y -= l0.x * x[c].y + l0.y * x[c].x;
-          u1.x -= l1.x * x[c].x - l1.y * x[c].y;
-          u1.y -= l1.x * x[c].y + l1.y * x[c].x;
-          b[0][c].x = a0 ? u0.x : b[0][c].x;
-          b[0][c].y = a0 ? u0.y : b[0][c].y;
-          b[1][c].x = a1 ? u1.x : b[1][c].x;
-          b[1][c].y = a1 ? u1.y : b[1][c].y;
-        }
-      }
-    };
-    const int je = jb + pw;
-    if (forward) {
-      if (jb < 64) sweep(std::integral_constant<int, 0>{}, jb, je < 64 ? je : 64);
-      if (je > 64) sweep(std::integral_constant<int, 1>{}, jb > 64 ? jb : 64, je);
-    } else {
-      if (je > 64) sweep(std::integral_constant<int, 1>{}, jb > 64 ? jb : 64, je);
-      if (jb < 64) sweep(std::integral_constant<int, 0>{}, jb, je < 64 ? je : 64);
-    }
-  }
-}
-
-// Inverse of the diagonal triangle of blocks b0 + blockIdx.y (UPPER 0: unit lower
-// L11, 1: non-unit upper U11) by substitution on identity columns; written to
-// Dinv[b] (nb x nb column-major, zeros in the other triangle).
-template <typename T, int UPPER, int CPW>
-__global__ void __launch_bounds__(256) block_inv_kernel(const cplx<T>* __restrict__ A, int64_t ld, int64_t n, int nb,
-                                                        int b0, cplx<T>* __restrict__ Dinv, int PW, int64_t sA,
-                                                        int64_t sD) {
-  using CT = cplx<T>;
-  A += (int64_t)blockIdx.z * sA;  // batch item blockIdx.z
-  Dinv += (int64_t)blockIdx.z * sD;
-  extern __shared__ unsigned char smem_raw[];
-  CT* Ls = reinterpret_cast<CT*>(smem_raw);
-  const int bb = b0 + blockIdx.y;
-  const int64_t k0 = (int64_t)bb * nb;
-  const int w = (int)(n - k0 < nb ? n - k0 : nb);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col0 = blockIdx.x * (4 * CPW) + wave * CPW;
-  CT b[2][CPW];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      b[h][c].x = (lane + 64 * h == col0 + c) ? 1 : 0;
-      b[h][c].y = 0;
-    }
-  trsm_sweep<T, UPPER ? 1 : 0, CPW>(A + k0 + k0 * ld, ld, w, b, Ls, PW);
-  CT* D = Dinv + (size_t)bb * nb * nb;
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      const int i = lane + 64 * h;
-      if (i < w && col0 + c < w) D[i + (int64_t)(col0 + c) * nb] = b[h][c];
-    }
-}
-
-// X <- L11^-1 X in place for ncols columns of X (the rows of block b0, leading
-// dimension ldx): the forward substitution of block_inv_kernel applied to the
-// columns of X instead of identity columns (the look-ahead U12 block, without
-// waiting for the triangle's inverse).
-// PERM: first the block's row interchanges on each owned column (rows [k0, n),
-// X pointing at row k0; moved rows as listed by the panel), as
-// row_permute_kernel does, so that one launch replaces two.
-template <typename T, int CPW, bool PERM>
-__global__ void __launch_bounds__(256) block_trsm_kernel(const cplx<T>* __restrict__ A, int64_t ld, int64_t n, int nb,
-                                                         int b0, cplx<T>* __restrict__ X, int64_t ldx, int ncols,
-                                                         int PW, int64_t sA, int64_t sX, const int32_t* __restrict__ dst,
-                                                         const int32_t* __restrict__ src,
-                                                         const int32_t* __restrict__ npairs, int64_t spairs,
-                                                         int64_t snpairs) {
-  using CT = cplx<T>;
-  A += (int64_t)blockIdx.z * sA;  // batch item blockIdx.z
-  X += (int64_t)blockIdx.z * sX;
-  extern __shared__ unsigned char smem_raw[];
-  CT* Ls = reinterpret_cast<CT*>(smem_raw);
-  const int64_t k0 = (int64_t)b0 * nb;
-  const int w = (int)(n - k0 < nb ? n - k0 : nb);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col0 = blockIdx.x * (4 * CPW) + wave * CPW;
-  if constexpr (PERM) {
-    dst += (int64_t)blockIdx.z * spairs;
-    src += (int64_t)blockIdx.z * spairs;
-    const int np = npairs[(int64_t)blockIdx.z * snpairs];  // <= 2 nb <= 256
-    CT v[CPW][4];
-#pragma unroll
-    for (int c = 0; c < CPW; ++c)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int t = lane + 64 * q;
-        if (t < np && col0 + c < ncols) v[c][q] = X[(src[t] - k0) + (int64_t)(col0 + c) * ldx];
-      }
-    __syncthreads();  // every source read before any destination is written
-#pragma unroll
-    for (int c = 0; c < CPW; ++c)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int t = lane + 64 * q;
-        if (t < np && col0 + c < ncols) X[(dst[t] - k0) + (int64_t)(col0 + c) * ldx] = v[c][q];
-      }
-    __syncthreads();  // the interchanged rows visible to the whole workgroup
-  }
-  CT b[2][CPW];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      const int i = lane + 64 * h;
-      b[h][c].x = 0;
-      b[h][c].y = 0;
-      if (i < w && col0 + c < ncols) b[h][c] = X[i + (int64_t)(col0 + c) * ldx];
-    }
-  trsm_sweep<T, 0, CPW>(A + k0 + k0 * ld, ld, w, b, Ls, PW);  // every wave takes part (barriers)
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      const int i = lane + 64 * h;
-      if (i < w && col0 + c < ncols) X[i + (int64_t)(col0 + c) * ldx] = b[h][c];
-    }
-}
-
-// Diagonal block of block b0 + blockIdx.y: strict lower <- -Linv (UPPER 0), or
-// upper incl. diagonal <- I - Uinv (UPPER 1).  MODE 2: the strict lower part
-// of Dinv itself <- -Linv (A untouched); MODE 3: strict lower <- that part of
-// Dinv as it stands (after MODE 2).
-template <typename T, int UPPER>
-__global__ void __launch_bounds__(256) diag_store_kernel(cplx<T>* __restrict__ A, int64_t ld, int64_t n, int nb, int b0,
-                                                         cplx<T>* __restrict__ Dinv, int64_t sA, int64_t sD) {
-  using CT = cplx<T>;
-  A += (int64_t)blockIdx.z * sA;  // batch item blockIdx.z
-  Dinv += (int64_t)blockIdx.z * sD;
-  const int bb = b0 + blockIdx.y;
-  const int64_t k0 = (int64_t)bb * nb;
-  const int w = (int)(n - k0 < nb ? n - k0 : nb);
-  CT* D = Dinv + (size_t)bb * nb * nb;
-  for (int idx = blockIdx.x * 256 + threadIdx.x; idx < w * w; idx += gridDim.x * 256) {
-    const int i = idx % w, j = idx / w;
-    const CT d = D[i + (int64_t)j * nb];
-    CT v;
-    if (UPPER != 1) {
-      if (i <= j) continue;
-      v = d;
-      if (UPPER != 3) {
-        v.x = -d.x;
-        v.y = -d.y;
-      }
-    } else {
-      if (i > j) continue;
-      v.x = (i == j ? 1 : 0) - d.x;
-      v.y = -d.y;
-    }
-    if (UPPER == 2) D[i + (int64_t)j * nb] = v;
-    else A[(k0 + i) + (k0 + j) * ld] = v;
-  }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) copy_block_kernel(const cplx<T>* __restrict__ S, int64_t lds,
-                                                         cplx<T>* __restrict__ D, int64_t ldd, int64_t m, int64_t n,
-                                                         int64_t sS, int64_t sD) {
-  S += (int64_t)blockIdx.z * sS;  // batch item blockIdx.z
-  D += (int64_t)blockIdx.z * sD;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  for (int64_t j = blockIdx.y; j < n; j += gridDim.y) D[i + j * ldd] = S[i + j * lds];
-}
-
-template <typename T>
-static hipError_t launch_copy_block(const cplx<T>* S, int64_t lds, cplx<T>* D, int64_t ldd, int64_t m, int64_t n,
-                                    hipStream_t st, int nbatch = 1, int64_t sS = 0, int64_t sD = 0) {
-  if (m <= 0 || n <= 0 || nbatch <= 0) return hipSuccess;
-  const unsigned gy = (unsigned)(n < 65535 ? n : 65535);
-  hipLaunchKernelGGL(copy_block_kernel<T>, dim3((unsigned)((m + 255) / 256), gy, (unsigned)nbatch), dim3(256), 0, st, S,
-                     lds, D, ldd, m, n, sS, sD);
-  return hipGetLastError();
-}
-
-static int trsm_pw(int w, int elem) {
-  int PW = TRSM_LS_BYTES / (w * 2 * elem);
-  if (PW < 1) PW = 1;
-  if (PW > w) PW = w;
-  return PW;
-}
-
-// One column of the inverse per wave keeps the per-step work of the substitution
-// chain minimal (the chain, not the arithmetic, sets the time of one triangle);
-// with many triangles at once (more workgroups than CUs) four columns per wave
-// stage each triangle into LDS four times less often.
-// STORE: diag_store_kernel mode applied after the inverse (UPPER by default).
-template <typename T, int UPPER, int STORE = UPPER>
-static hipError_t launch_block_inv(const cplx<T>* A, int64_t ld, int64_t n, int nb, int b0, int nblocks, cplx<T>* Dinv,
-                                   hipStream_t st, int nbatch, int64_t sA, int64_t sD, int ncu) {
-  if (nblocks <= 0 || nbatch <= 0) return hipSuccess;
-  const int PW = trsm_pw(nb, (int)sizeof(T));
-  const size_t lds = (size_t)PW * nb * sizeof(cplx<T>);
-  const dim3 g1((unsigned)((nb + 3) / 4), (unsigned)nblocks, (unsigned)nbatch);
-  if ((int64_t)g1.x * nblocks * nbatch <= ncu) {
-    hipLaunchKernelGGL((block_inv_kernel<T, UPPER, 1>), g1, dim3(256), lds, st, A, ld, n, nb, b0, Dinv, PW, sA, sD);
-  } else {
-    const dim3 g4((unsigned)((nb + 15) / 16), (unsigned)nblocks, (unsigned)nbatch);
-    hipLaunchKernelGGL((block_inv_kernel<T, UPPER, 4>), g4, dim3(256), lds, st, A, ld, n, nb, b0, Dinv, PW, sA, sD);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((diag_store_kernel<T, STORE>), dim3(16, (unsigned)nblocks, (unsigned)nbatch), dim3(256), 0, st,
-                     const_cast<cplx<T>*>(A), ld, n, nb, b0, Dinv, sA, sD);
-  return hipGetLastError();
-}
-
-template <typename T>
-static hipError_t launch_block_trsm(const cplx<T>* A, int64_t ld, int64_t n, int nb, int b0, cplx<T>* X, int64_t ldx,
-                                   int64_t ncols, hipStream_t st, int nbatch, int64_t sA, int64_t sX,
-                                   const int32_t* dst = nullptr, const int32_t* src = nullptr,
-                                   const int32_t* npairs = nullptr, int64_t spairs = 0, int64_t snpairs = 0) {
-  if (ncols <= 0 || nbatch <= 0) return hipSuccess;
-  const int PW = trsm_pw(nb, (int)sizeof(T));
-  const size_t lds = (size_t)PW * nb * sizeof(cplx<T>);
-  const dim3 g((unsigned)((ncols + 3) / 4), 1, (unsigned)nbatch);
-  if (npairs)
-    hipLaunchKernelGGL((block_trsm_kernel<T, 1, true>), g, dim3(256), lds, st, A, ld, n, nb, b0, X, ldx, (int)ncols,
-                       PW, sA, sX, dst, src, npairs, spairs, snpairs);
-  else
-    hipLaunchKernelGGL((block_trsm_kernel<T, 1, false>), g, dim3(256), lds, st, A, ld, n, nb, b0, X, ldx, (int)ncols,
-                       PW, sA, sX, dst, src, npairs, spairs, snpairs);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// 1c. speculative panel: diagonal pivots, checked against partial pivoting
-// ---------------------------------------------------------------------------
-// Partial pivoting keeps the diagonal entry of column j as its pivot exactly
-// when no entry below it is larger in |re| + |im| (compared in FP32, lowest row
-// on ties: the rule of panel_kernel).  The coupling matrices of dielectric
-// structures are diagonally dominant enough for that to hold in every column,
-// and then the panel needs no pivot search at all: one workgroup factors the
-// diagonal block, and the rows below follow from L21 = A21 U11^-1, a
-// triangular solve per row.  The entries partial pivoting would have compared
-// in column j are a_ij = l_ij u_jj (the column after the eliminations of the
-// earlier columns), so each kernel checks |a_ij| <= |u_jj| for its rows; a
-// failure, a zero pivot or a NaN sets the block's flag, and the caller repeats
-// the factorisation with the pivot search (panel_kernel).  When no flag is set
-// the factors are those of partial pivoting, up to the rounding order of the
-// entries compared (near-ties within FP32 rounding may resolve either way).
-template <typename CT>
-__device__ inline float cabs1_f(const CT& v) {
-  return (float)(fabs(v.x) + fabs(v.y));
-}
-
-// Diagonal block (w x w at (k0, k0)) of batch item blockIdx.y, NT threads:
-// thread (tx, ty) = (tid % 32, tid / 32) holds rows tx + 32 p (p < 4) and
-// columns ty + TY q (q < 128 / TY, TY = NT / 32) in registers.  Per column j
-// the pivot row and the pivot column go through LDS (double-buffered by the
-// parity of j, one barrier per column); each thread reads all the entries it
-// needs at once and forms the multipliers of its rows itself.  Row and column
-// groups wholly at or before j are skipped (uniform branches), groups wholly
-// after it take a plain update and only the groups holding row or column j a
-// masked one, so the work per column follows the shrinking triangle (the VALU
-// of one CU sets the time: 64 lanes per cycle).  NT = 512: 32 entries per
-// thread, two waves per SIMD.
-template <typename T, int NT>
-__global__ void __launch_bounds__(NT) spec_diag_kernel(cplx<T>* __restrict__ A, int64_t ld, int64_t k0, int w,
-                                                        int32_t* __restrict__ ipiv, int32_t* __restrict__ flag,
-                                                        int64_t sA, int64_t sipiv, int64_t sflag) {
-  using CT = cplx<T>;
-  constexpr int TY = NT / 32, Q = 128 / TY;
-  A += (int64_t)blockIdx.y * sA;  // batch item blockIdx.y
-  ipiv += (int64_t)blockIdx.y * sipiv;
-  flag += (int64_t)blockIdx.y * sflag;
-  __shared__ CT rowb[2][128], colb[2][128];
-  const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
-  CT* D = A + k0 + k0 * ld;
-  CT a[4][Q];
-  static_for<4>([&](auto p) {
-    static_for<Q>([&](auto q) {
-      const int r = tx + 32 * p, c = ty + TY * q;
-      a[p][q].x = 0;
-      a[p][q].y = 0;
-      if (r < w && c < w) a[p][q] = D[r + (int64_t)c * ld];
-    });
-  });
-  bool bad = false;
-  for (int j = 0; j < w; ++j) {
-    const int par = j & 1;
-    const int jp = j >> 5, jr = j & 31;  // row group and lane index of row j
-    const int jq = j / TY, jc = j % TY;  // column group and index of column j
-    if (tx == jr) {
-      static_for<4>([&](auto p) {
-        if (p == jp) static_for<Q>([&](auto q) { rowb[par][ty + TY * q] = a[p][q]; });
-      });
-    }
-    if (ty == jc) {
-      static_for<Q>([&](auto q) {
-        if (q == jq) static_for<4>([&](auto p) { colb[par][tx + 32 * p] = a[p][q]; });
-      });
-    }
-    __syncthreads();
-    CT u[Q], v[4];
-    static_for<Q>([&](auto q) { u[q] = rowb[par][ty + TY * q]; });
-    static_for<4>([&](auto p) { v[p] = colb[par][tx + 32 * p]; });
-    const CT piv = rowb[par][j];
-    const float pk = cabs1_f(piv);
-    if (!(pk > 0.f)) bad = true;  // zero or NaN pivot
-    const CT inv = cinv_t(piv);
-    // groups wholly below / right of j take the plain update; the group holding
-    // row j (p == jp) or column j (q == jq) the masked one
-    static_for<4>([&](auto p) {
-      if (p < jp) return;
-      const bool pfull = p > jp;
-      const bool below = pfull || tx > jr;
-      const CT l = cmul_t(v[p], inv);
-      if (below && ty == jc && !(cabs1_f(v[p]) <= pk)) bad = true;
-      static_for<Q>([&](auto q) {
-        if (q < jq) return;
-        if (pfull && q > jq) {
-          a[p][q] = r1_upd(a[p][q], l, u[q]);
-          return;
-        }
-        const int c = ty + TY * q;
-        const CT t = r1_upd(a[p][q], l, u[q]);
-        const bool upd = below && c > j;
-        const bool mul = below && c == j;
-        a[p][q].x = upd ? t.x : (mul ? l.x : a[p][q].x);
-        a[p][q].y = upd ? t.y : (mul ? l.y : a[p][q].y);
-      });
-    });
-  }
-  static_for<4>([&](auto p) {
-    static_for<Q>([&](auto q) {
-      const int r = tx + 32 * p, c = ty + TY * q;
-      if (r < w && c < w) D[r + (int64_t)c * ld] = a[p][q];
-    });
-  });
-  if (tid < w) ipiv[k0 + tid] = (int32_t)(k0 + tid);
-  if (__syncthreads_or(bad) && tid == 0) atomicOr(flag, 1);
-}
-
-// The check of the rows below the diagonal block once L21 is formed:
-// |l_ij u_jj| <= |u_jj| in |re| + |im| (FP32): the entry partial pivoting
-// would compare with the pivot u_jj at step j is a_ij = l_ij u_jj, and the
-// diagonal keeps the pivot only if no such entry is larger (ties to the lower
-// row index).  Threads along the rows (coalesced), blockIdx.y over groups of
-// 16 columns.
-template <typename T>
-__global__ void __launch_bounds__(256) spec_check_kernel(const cplx<T>* __restrict__ A, int64_t ld, int64_t n,
-                                                          int64_t k0, int w, int32_t* __restrict__ flag, int64_t sA,
-                                                          int64_t sflag) {
-  using CT = cplx<T>;
-  A += (int64_t)blockIdx.z * sA;
-  flag += (int64_t)blockIdx.z * sflag;
-  constexpr int CG = 16;
-  const int j0 = blockIdx.y * CG;
-  __shared__ CT dg[CG];
-  __shared__ float pk[CG];
-  if (threadIdx.x < CG) {
-    const int j = j0 + threadIdx.x;
-    CT d;
-    d.x = 0;
-    d.y = 0;
-    if (j < w) d = A[(k0 + j) + (k0 + j) * ld];
-    dg[threadIdx.x] = d;
-    pk[threadIdx.x] = cabs1_f(d);
-  }
-  __syncthreads();
-  const int64_t r = k0 + w + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  bool bad = false;
-  if (r < n) {
-    const int jn = w - j0 < CG ? w - j0 : CG;
-    CT x[CG];
-#pragma unroll
-    for (int c = 0; c < CG; ++c)
-      if (c < jn) x[c] = A[r + (k0 + j0 + c) * ld];
-#pragma unroll
-    for (int c = 0; c < CG; ++c)
-      if (c < jn && !(cabs1_f(cmul_t(x[c], dg[c])) <= pk[c])) bad = true;
-  }
-  if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
-}
-
-// Speculative panel of block bi (columns [k0, k0 + w)): the diagonal block
-// (launch_spec_diag), then (launch_spec_l21) L21 = A21 U11^-1 for the rows below
-// as U11^-1 (into the block's inverse slot, which later steps overwrite only
-// after this panel) and one GEMM from a copy of A21, then the check.  (A row-parallel substitution x U11 = a on the
-// VALUs, with U11 staged in LDS, took 115 us per early FP32 block beside the
-// bulk update and 590 us in FP64, where the staged triangle fills 132 KB of a
-// CU's LDS; the inverse + GEMM form: FP32 factorisation 59.5 -> 59.2 ms, FP64
-// 110.3 -> 108.7 ms at n = 12 000.)
-template <typename T>
-static hipError_t launch_spec_diag(cplx<T>* A, int64_t ld, int nb, int bi, int64_t k0, int w, int32_t* ipiv,
-                                   const LUWork& ws, hipStream_t st, int nbatch, int64_t sA, int64_t sipiv) {
-  if (w > 128 || !ws.l21c || k0 != (int64_t)bi * nb) return hipErrorInvalidValue;
-  int32_t* flag = ws.spec + bi;
-  const int64_t sflag = ws.s_npairs;
-  constexpr int NT = 512;
-  // One system: the diagonal kernel reserves (without using it) nearly all of
-  // its CU's LDS, so that no workgroup of the concurrent bulk update shares
-  // that CU's VALUs with its 128-step chain.  It is launched before the
-  // step's bulk update, so a free CU is there to take it.  Measured at
-  // n = 12 000: FP32+IR step 69.7 -> 69.1 ms, FP64 103.4 -> 103.0 ms, adjoint
-  // (n = 6000, FP32+IR) 23.9 -> 23.2 ms.
-  size_t reserve = 0;
-  if (nbatch == 1) {
-    static std::once_flag once;
-    static size_t bytes = 0;
-    static hipError_t attr = hipSuccess;
-    std::call_once(once, [] {
-      int dev = 0, cu_lds = 0;
-      attr = hipGetDevice(&dev);
-      if (attr == hipSuccess)
-        attr = hipDeviceGetAttribute(&cu_lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
-      // the static 4 KB of the kernel and a margin stay free
-      if (attr == hipSuccess && cu_lds > 96 * 1024) {
-        bytes = (size_t)cu_lds - 12 * 1024;
-        attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&spec_diag_kernel<float, NT>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (attr == hipSuccess)
-          attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&spec_diag_kernel<double, NT>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-      }
-    });
-    if (attr != hipSuccess) return attr;
-    reserve = bytes;
-  }
-  hipLaunchKernelGGL((spec_diag_kernel<T, NT>), dim3(1, (unsigned)nbatch), dim3(NT), reserve, st, A, ld, k0, w, ipiv,
-                     flag, sA, sipiv, sflag);
-  return hipGetLastError();
-}
-
-// The rest of the speculative panel of block bi: L21 (w columns below the
-// diagonal block) and the check of its entries against the pivots.
-template <typename T>
-static hipError_t launch_spec_l21(cplx<T>* A, int64_t ld, int64_t n, int nb, int bi, int64_t k0, int w,
-                                  const LUWork& ws, hipStream_t st, int nbatch, int64_t sA) {
-  using CT = cplx<T>;
-  int32_t* flag = ws.spec + bi;
-  const int64_t sflag = ws.s_npairs;
-  hipError_t e;
-  const int64_t nr = n - k0 - w;
-  if (nr <= 0) return hipSuccess;
-  CT* dinv = static_cast<CT*>(ws.dinv);
-  const int PW = trsm_pw(nb, (int)sizeof(T));
-  const size_t lds = (size_t)PW * nb * sizeof(CT);
-  const dim3 g1((unsigned)((nb + 3) / 4), 1, (unsigned)nbatch);
-  if ((int64_t)g1.x * nbatch <= ws.gmax) {
-    hipLaunchKernelGGL((block_inv_kernel<T, 1, 1>), g1, dim3(256), lds, st, A, ld, n, nb, bi, dinv, PW, sA, ws.s_dinv);
-  } else {
-    const dim3 g4((unsigned)((nb + 15) / 16), 1, (unsigned)nbatch);
-    hipLaunchKernelGGL((block_inv_kernel<T, 1, 4>), g4, dim3(256), lds, st, A, ld, n, nb, bi, dinv, PW, sA, ws.s_dinv);
-  }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  CT* l21 = A + (k0 + w) + k0 * ld;
-  CT* cp = static_cast<CT*>(ws.l21c);
-  if ((e = launch_copy_block<T>(l21, ld, cp, nr, nr, w, st, nbatch, sA, ws.s_l21c)) != hipSuccess) return e;
-  GemmMask mk;
-  mk.bkind = GEMM_MASK_UPPER;
-  if ((e = launch_gemm<T>(1, 0, nr, w, w, cp, nr, dinv + (size_t)bi * nb * nb, nb, l21, ld, st, mk, nbatch, ws.s_l21c,
-                          ws.s_dinv, sA)) != hipSuccess)
-    return e;
-  const dim3 gc((unsigned)((nr + 255) / 256), (unsigned)((w + 15) / 16), (unsigned)nbatch);
-  hipLaunchKernelGGL((spec_check_kernel<T>), gc, dim3(256), 0, st, A, ld, n, k0, w, flag, sA, sflag);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
 // planning and workspace
 // ---------------------------------------------------------------------------
 static const int LDS_RESERVE = 2048;
@@ -1910,10 +1301,8 @@ void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu,
   w.tmp_elems = tmp_rows(p) * (int64_t)nb;
   w.s_tmp = (int64_t)(al256((size_t)w.tmp_elems * cb) / cb);
   w.tmp = take((size_t)nbatch * w.s_tmp * cb);
-  w.s_dinv = (int64_t)(al256(nblk * nb * nb * cb) / cb);
-  w.dinv = take((size_t)nbatch * w.s_dinv * cb);
-  w.s_l21c = p.spec ? w.s_tmp : 0;
-  w.l21c = p.spec ? take((size_t)nbatch * w.s_l21c * cb) : nullptr;
+  w.s_tinv = (int64_t)(al256(nblk * (size_t)tinv_block_elems(p.nb) * cb) / cb);
+  w.tinv = take((size_t)nbatch * w.s_tinv * cb);
   w.events = nullptr;
   w.bytes = off + 256;
 }
@@ -1959,6 +1348,14 @@ hipError_t lu_prepare(const LUPlan& plan) {
   static std::map<const void*, size_t> lds_set;
   static std::mutex mu;
   std::lock_guard<std::mutex> lk(mu);
+  if (plan.spec) {
+    static bool diag_set = false;
+    if (!diag_set) {
+      hipError_t e = prepare_diag_lu<T>();
+      if (e != hipSuccess) return e;
+      diag_set = true;
+    }
+  }
   for (const LUBlock& b : plan.blocks) {
     const size_t need = panel_lds_bytes(b.w, b.R, sizeof(cplx<T>), plan.pb);
     const void* fn = panel_fn<T>(plan.pb);
@@ -1974,6 +1371,13 @@ hipError_t lu_prepare(const LUPlan& plan) {
 }
 template hipError_t lu_prepare<double>(const LUPlan&);
 template hipError_t lu_prepare<float>(const LUPlan&);
+
+// Whether a step's trailing update is split between the two streams: below
+// about 30 us of update (its CU time at the rate of the large updates) the two
+// events of a split cost as much as the overlap with the next panel gives.
+static bool lu_lookahead_pays(int elem_bytes, int64_t nr, int nbatch) {
+  return (double)nr * (double)nr * nbatch * (elem_bytes / 4) > 2.5e6;
+}
 
 template <typename T>
 hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws, int32_t* ipiv, hipStream_t st,
@@ -2027,226 +1431,98 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
       return e;                    \
     }                              \
   } while (0)
-  CT* tmpB = static_cast<CT*>(ws.tmp);   // side-stream operand copies (n x nb per item)
-  CT* dinv = static_cast<CT*>(ws.dinv);
+  CT* tinv0 = static_cast<CT*>(ws.tinv);
+  const int64_t btinv = tinv_block_elems(nb);
   hipEvent_t bulk_done = nullptr;  // side stream finished the previous block's bulk update
-  // Upper parts of block b (final once panel b is done): the diagonal block
-  // gets I - U11^-1, the block column above it U01 U11^-1.  With look-ahead (one
-  // system) they are formed on the side stream after a block's bulk update,
-  // in the second half of the factorisation (the panels then set the pace and
-  // the side stream has time to spare); the rest at the end.  Measured at
-  // n = 12 000: FP32+IR step 93.3 -> 90.9 ms, FP64 146.7 -> 144.3 ms with three
-  // per step from half the rows (two per step from 3/4 of the rows: 91.5 and
-  // 145.8; the batched factorisations, whose side stream has no time to spare,
-  // keep the end).  Later, with the faster update and panels, three per step
-  // put the side stream on the panels' path (a kernel trace showed the next
-  // panel's substitution waiting for a bulk update held back by them); the
-  // graded count below: FP32+IR step 71.7 -> 69.6 ms, FP64 105.5 -> 103.5 ms
-  // (two per step from half the rows: 70.5 and 104.2).
-  int u_next = 0;  // blocks [0, u_next) have their upper parts formed
-  auto upper_parts = [&](hipStream_t s, int bb) -> hipError_t {
-    hipError_t r;
-    const int64_t kb = plan.blocks[bb].k0;
-    const int wb = plan.blocks[bb].w;
-    if ((r = P.begin(s, PROF_TRSM, 0.0)) != hipSuccess) return r;
-    if ((r = launch_block_inv<T, 1>(A, ld, n, nb, bb, 1, dinv, s, NB, sA, ws.s_dinv, ws.gmax)) != hipSuccess) return r;
-    if (kb > 0) {
-      if ((r = launch_copy_block<T>(A + kb * ld, ld, tmpB, kb, kb, wb, s, NB, sA, ws.s_tmp)) != hipSuccess) return r;
-      GemmMask mu;
-      mu.bkind = GEMM_MASK_UPPER;
-      if ((r = launch_gemm<T>(0, 0, kb, wb, wb, tmpB, kb, A + kb + kb * ld, ld, A + kb * ld, ld, s, mu, NB, ws.s_tmp,
-                              sA, sA)) != hipSuccess)
-        return r;
-    }
-    return P.end(s);
-  };
   for (int bi = 0; bi < nblk; ++bi) {
     const LUBlock& b = plan.blocks[bi];
     const int64_t k0 = b.k0;
     const int w = b.w;
     const size_t lds = panel_lds_bytes(w, b.R, sizeof(CT), plan.pb);
+    CT* tinv = tinv0 + bi * btinv;
     LUCHK(P.begin(st, PROF_PANEL, (double)w * fb));
     int32_t* dst = ws.pairs + bi * 4 * (size_t)nb;  // moved rows: destinations, then sources 2 nb later
     int32_t* src = dst + 2 * nb;
     int32_t* npr = ws.npairs + bi;
+    int32_t* flag = ws.spec + bi;
     if (plan.spec) {
-      LUCHK(launch_spec_diag<T>(A, ld, nb, bi, k0, w, ipiv, ws, st, NB, sA, sipiv));
-      LUCHK(P.end(st));
-      LUCHK(P.begin(st, PROF_PANEL_L21, 8.0 * (double)(n - k0 - w) * w * w * fb));
-      LUCHK(launch_spec_l21<T>(A, ld, n, nb, bi, k0, w, ws, st, NB, sA));
+      LUCHK(launch_diag_lu<T>(A, ld, nb, k0, w, ipiv, flag, tinv, st, NB, sA, sipiv, ws.s_npairs, ws.s_tinv));
     } else {
       launch_panel<T>(plan.pb, b, NB, lds, st, A, ld, n, ipiv, ws, epoch, sA, sipiv, dst, src, npr, 2 * nb);
       epoch += (uint32_t)w;
       LUCHK(hipGetLastError());
+      LUCHK(launch_tile_inv<T>(A, ld, nb, k0, w, tinv, st, NB, sA, ws.s_tinv));
     }
     LUCHK(P.end(st));
     const int64_t c1 = k0 + w;
     const int64_t nr = n - c1;
-    CT* diag = A + k0 + k0 * ld;
-    // L11^-1 -> strict lower part of the diagonal block holds I - L11^-1.  With
-    // look-ahead it is formed on the side stream, once the main stream has
-    // solved the next panel's U12 block directly (that solve reads L11).
-    auto form_inverse = [&](hipStream_t s) -> hipError_t {
+    if (nr <= 0) break;
+    // columns [c1, c1 + wa) on the main stream, [c1 + wa, n) on the side stream;
+    // once the trailing matrix is small, all of it on the main stream
+    const bool split = la && nr > nb && lu_lookahead_pays((int)sizeof(T), nr, NB);
+    const int64_t wa = split ? nb : nr;
+    // one block's interchanges on ncols columns from cb on (a speculative panel moves no rows)
+    auto permute = [&](hipStream_t s, int64_t cb, int64_t ncols) -> hipError_t {
+      if (plan.spec) return hipSuccess;
       hipError_t r;
-      if ((r = P.begin(s, PROF_TRSM, 0.0)) != hipSuccess) return r;
-      if ((r = launch_block_inv<T, 0>(A, ld, n, nb, bi, 1, dinv, s, NB, sA, ws.s_dinv, ws.gmax)) != hipSuccess)
-        return r;
+      if ((r = P.begin(s, PROF_PERM, 0.0)) != hipSuccess) return r;
+      hipLaunchKernelGGL(row_permute_kernel<T>, dim3((unsigned)ncols, NB), dim3(256), 0, s, A, ld, cb, dst, src, npr, sA,
+                         ws.s_pairs, ws.s_npairs);
+      if ((r = hipGetLastError()) != hipSuccess) return r;
       return P.end(s);
     };
-    if (!la || nr <= 0) LUCHK(form_inverse(st));
-    // columns [c1, c1 + wa) on the main stream, [c1 + wa, n) on the side stream
-    const int64_t wa = la ? std::min<int64_t>(nr, nb) : nr;
-    // While the trailing matrix is large (one system), the bulk update sets the
-    // pace: the side stream then starts its part as soon as the panel is done,
-    // beside the main stream's part.  L11^-1 goes to the block's inverse slot in
-    // its masked-operand form (-L11^-1 below the diagonal, = I - L11^-1 there),
-    // and reaches the diagonal block of A only after the main stream's
-    // substitution has read L11.
-    // (while more than half the rows remain: measured against three quarters,
-    // FP32 factorisation 58.4 -> 58.1 ms, FP64 100.5 -> 99.8 ms at n = 12 000)
-    const bool early = la && NB == 1 && nr - wa > 0 && 2 * nr > n;
-    hipEvent_t panel_done = nullptr;
-    if (early) {
-      LUCHK(new_event(panel_done));
-      LUCHK(hipEventRecord(panel_done, st));
-    }
-    if (bulk_done) LUCHK(hipStreamWaitEvent(st, bulk_done, 0));  // columns of this step were in the bulk
-    if (nr <= 0) break;
-    GemmMask ml;
-    ml.akind = GEMM_MASK_STRICT_LOWER;
-    ml.ar0 = 0;
-    ml.adw = w;
-    // lop: I - L11^-1 below its diagonal (leading dimension lld, item stride slop)
-    auto update_cols = [&](hipStream_t s, int64_t cb, int64_t ncols, CT* tmp, int64_t stmp, const CT* lop,
-                           int64_t lld, int64_t slop) -> hipError_t {
+    // L21 = A21 U11^-1 (speculative panels) and U12 = L11^-1 A12 of ncols columns
+    auto tri = [&](hipStream_t s, int tag, int64_t nrows, int64_t cb, int64_t ncols) -> hipError_t {
       hipError_t r;
-      if (ncols <= 0) return hipSuccess;
-      if (!plan.spec) {  // a speculative panel moves no rows
-        if ((r = P.begin(s, PROF_PERM, 0.0)) != hipSuccess) return r;
-        hipLaunchKernelGGL(row_permute_kernel<T>, dim3((unsigned)ncols, NB), dim3(256), 0, s, A, ld, cb, dst, src, npr,
-                           sA, ws.s_pairs, ws.s_npairs);
-        if ((r = P.end(s)) != hipSuccess) return r;
-      }
-      // U12 = L11^-1 A12 = A12 - (I - L11^-1) A12
-      if ((r = P.begin(s, PROF_TRSM, 8.0 * w * w * (double)ncols * fb)) != hipSuccess) return r;
-      if ((r = launch_copy_block<T>(A + k0 + cb * ld, ld, tmp, w, w, ncols, s, NB, sA, stmp)) != hipSuccess) return r;
-      if ((r = launch_gemm<T>(0, 0, w, ncols, w, lop, lld, tmp, w, A + k0 + cb * ld, ld, s, ml, NB, slop, stmp, sA)) !=
+      if ((r = P.begin(s, tag, 8.0 * (double)(nrows + ncols) * w * w * fb)) != hipSuccess) return r;
+      if ((r = launch_tri_panel<T>(A, ld, nb, k0, w, nrows, cb, ncols, tinv, flag, s, NB, sA, ws.s_tinv, ws.s_npairs)) !=
           hipSuccess)
         return r;
-      if ((r = P.end(s)) != hipSuccess) return r;
-      // A22[:, cols] -= L21 U12[:, cols]
-      if ((r = P.begin(s, PROF_UPDATE, 8.0 * (double)nr * (double)ncols * w * fb)) != hipSuccess) return r;
-      if ((r = launch_gemm_update<T>(nr, ncols, w, A + c1 + k0 * ld, ld, A + k0 + cb * ld, ld, A + c1 + cb * ld, ld,
-                                     s, NB, sA, sA, sA)) != hipSuccess)
+      return P.end(s);
+    };
+    // A22[:, cols] -= L21 U12[:, cols]
+    auto update = [&](hipStream_t s, int tag, int64_t cb, int64_t ncols) -> hipError_t {
+      hipError_t r;
+      if ((r = P.begin(s, tag, 8.0 * (double)nr * (double)ncols * w * fb)) != hipSuccess) return r;
+      if ((r = launch_gemm_update<T>(nr, ncols, w, A + c1 + k0 * ld, ld, A + k0 + cb * ld, ld, A + c1 + cb * ld, ld, s, NB,
+                                     sA, sA, sA)) != hipSuccess)
         return r;
       return P.end(s);
     };
-    // This event orders the side stream's writes of L11 (its inverse form; the
-    // substitution below reads L11) and of L21 (its transform; the look-ahead
-    // product reads it) after the main stream's part.  Each event record or
-    // wait costs 6-11 us on the GPU timeline, so outside the early blocks above
-    // it is the only one per block (measured: batched spectra 83 -> 98
-    // systems/s with one event instead of two, FP32+IR step 95.6 -> 95.2 ms).
+    // L21 needs the panel alone: while the previous block's bulk update still
+    // runs it goes ahead of the wait, else it shares the U12 block's launch
+    const int64_t lrows = plan.spec ? nr : 0;
+    if (bulk_done) {
+      if (lrows > 0) LUCHK(tri(st, PROF_PANEL_L21, lrows, c1, 0));
+      LUCHK(hipStreamWaitEvent(st, bulk_done, 0));  // columns of this step were in the bulk
+      bulk_done = nullptr;
+      LUCHK(permute(st, c1, wa));
+      LUCHK(tri(st, PROF_TRSM, 0, c1, wa));
+    } else {
+      LUCHK(permute(st, c1, wa));
+      LUCHK(tri(st, PROF_PANEL_L21, lrows, c1, wa));
+    }
+    // (a launch that reaches past the next panel's columns counts as bulk)
+    LUCHK(update(st, wa <= nb ? PROF_LOOKAHEAD : PROF_UPDATE, c1, wa));
+    if (!split) continue;
+    // The side stream starts after the look-ahead product, so that the next
+    // diagonal block's workgroup finds a free CU before the bulk update takes
+    // them all.
     hipEvent_t main_updated = nullptr;
-    if (la) {
-      // next panel's columns: interchanges and U12 by substitution in one
-      // launch (one launch and its gap fewer per block on the panels' path),
-      // then the update
-      LUCHK(P.begin(st, PROF_TRSM, 8.0 * w * w * (double)wa * fb));
-      LUCHK(launch_block_trsm<T>(A, ld, n, nb, bi, A + k0 + c1 * ld, ld, wa, st, NB, sA, sA, dst, src,
-                                 plan.spec ? nullptr : npr, ws.s_pairs, ws.s_npairs));
-      LUCHK(P.end(st));
-      LUCHK(P.begin(st, PROF_LOOKAHEAD, 8.0 * (double)nr * (double)wa * w * fb));
-      LUCHK(launch_gemm_update<T>(nr, wa, w, A + c1 + k0 * ld, ld, A + k0 + c1 * ld, ld, A + c1 + c1 * ld, ld, st, NB,
-                                  sA, sA, sA));
-      LUCHK(P.end(st));
-      LUCHK(new_event(main_updated));
-      LUCHK(hipEventRecord(main_updated, st));
-    } else {
-      LUCHK(update_cols(st, c1, wa, tmpB, ws.s_tmp, diag, ld, sA));
-    }
-    hipStream_t sb = la ? side : st;
-    CT* dslot = dinv + (size_t)bi * nb * nb;  // this block's inverse slot
-    if (early) {
-      LUCHK(hipStreamWaitEvent(sb, panel_done, 0));
-      LUCHK(P.begin(sb, PROF_TRSM, 0.0));
-      LUCHK((launch_block_inv<T, 0, 2>(A, ld, n, nb, bi, 1, dinv, sb, NB, sA, ws.s_dinv, ws.gmax)));
-      LUCHK(P.end(sb));
-      LUCHK(update_cols(sb, c1 + wa, nr - wa, tmpB, ws.s_tmp, dslot, nb, ws.s_dinv));
-    } else {
-      if (la) {
-        LUCHK(hipStreamWaitEvent(sb, main_updated, 0));
-        LUCHK(form_inverse(sb));
-      }
-      LUCHK(update_cols(sb, c1 + wa, nr - wa, tmpB, ws.s_tmp, diag, ld, sA));
-    }
-    // The next step's main stream needs only the update above; the work below
-    // touches block column bi alone, which no later step of the factorisation
-    // reads, so for one system it runs while the main stream goes on (measured
-    // at n = 12 000: FP32+IR 92.4 -> 91.8 ms, FP64 144.9 -> 144.0 ms; batched
-    // groups, whose side stream sets the pace, were 1 % slower and keep the
-    // record after it).
-    auto record_bulk_done = [&]() -> hipError_t {
-      hipError_t r = new_event(bulk_done);
-      return r != hipSuccess ? r : hipEventRecord(bulk_done, sb);
-    };
-    if (la && NB == 1) LUCHK(record_bulk_done());
-    if (early) {
-      LUCHK(hipStreamWaitEvent(sb, main_updated, 0));
-      LUCHK(P.begin(sb, PROF_TRSM, 0.0));
-      hipLaunchKernelGGL((diag_store_kernel<T, 3>), dim3(16, 1, (unsigned)NB), dim3(256), 0, sb, A, ld, n, nb, bi, dinv,
-                         sA, ws.s_dinv);
-      LUCHK(hipGetLastError());
-      LUCHK(P.end(sb));
-    }
-    // L21 is read by both parts of this step's update: transform it after both
-    // (the side stream already waited for the main stream's part above)
-    // solve-ready form: L21 <- L21 L11^-1 = L21 - L21 (I - L11^-1)
-    LUCHK(P.begin(sb, PROF_TRSM, 8.0 * w * w * (double)nr * fb));
-    LUCHK(launch_copy_block<T>(A + c1 + k0 * ld, ld, tmpB, nr, nr, w, sb, NB, sA, ws.s_tmp));
-    GemmMask mb;
-    mb.bkind = GEMM_MASK_STRICT_LOWER;
-    LUCHK(launch_gemm<T>(0, 0, nr, w, w, tmpB, nr, diag, ld, A + c1 + k0 * ld, ld, sb, mb, NB, ws.s_tmp, sA, sA));
-    LUCHK(P.end(sb));
-    if (la && NB > 1) LUCHK(record_bulk_done());
-    if (la && NB == 1) {
-      // as many upper parts per step as the side stream has time for beside
-      // the shrinking bulk update: none while more than 55 % of the rows
-      // remain, then one, two from 30 % and three from 20 %, which catches up
-      // with the panels by about the last block (small systems: three per step
-      // throughout)
-      const int64_t r100 = 100 * nr;
-      int per = r100 <= 55 * n ? 1 : 0;
-      if (r100 <= 30 * n) per = 2;
-      if (r100 <= 20 * n) per = 3;
-      if (n <= 4096) per = 3;
-      for (int q = 0; q < per && u_next <= bi; ++q) LUCHK(upper_parts(sb, u_next++));
-    }
+    LUCHK(new_event(main_updated));
+    LUCHK(hipEventRecord(main_updated, st));
+    LUCHK(hipStreamWaitEvent(side, main_updated, 0));
+    LUCHK(permute(side, c1 + wa, nr - wa));
+    LUCHK(tri(side, PROF_TRSM, 0, c1 + wa, nr - wa));
+    LUCHK(update(side, PROF_UPDATE, c1 + wa, nr - wa));
+    LUCHK(new_event(bulk_done));
+    LUCHK(hipEventRecord(bulk_done, side));
   }
-  if (bulk_done) {
-    // everything the side stream ran, upper parts included
-    hipEvent_t side_done = nullptr;
-    LUCHK(new_event(side_done));
-    LUCHK(hipEventRecord(side_done, side));
-    LUCHK(hipStreamWaitEvent(st, side_done, 0));
-  }
-  if (u_next == 0) {
-    // every block at the end: the inverses in one launch, then the block columns
-    LUCHK(P.begin(st, PROF_TRSM, 0.0));
-    LUCHK((launch_block_inv<T, 1>(A, ld, n, nb, 0, nblk, dinv, st, NB, sA, ws.s_dinv, ws.gmax)));
-    for (int bi = 1; bi < nblk; ++bi) {
-      const LUBlock& b = plan.blocks[bi];
-      const int64_t k0 = b.k0;
-      LUCHK(launch_copy_block<T>(A + k0 * ld, ld, tmpB, k0, k0, b.w, st, NB, sA, ws.s_tmp));
-      GemmMask mu;
-      mu.bkind = GEMM_MASK_UPPER;
-      LUCHK(launch_gemm<T>(0, 0, k0, b.w, b.w, tmpB, k0, A + k0 + k0 * ld, ld, A + k0 * ld, ld, st, mu, NB, ws.s_tmp,
-                           sA, sA));
-    }
-    LUCHK(P.end(st));
-  } else {
-    while (u_next < nblk) LUCHK(upper_parts(st, u_next++));
-  }
+  if (bulk_done) LUCHK(hipStreamWaitEvent(st, bulk_done, 0));
+  // the solve-ready form of all blocks at once
+  LUCHK(P.begin(st, PROF_TRSM, 0.0));
+  LUCHK(launch_finish<T>(A, ld, n, nb, tinv0, st, NB, sA, ws.s_tinv));
+  LUCHK(P.end(st));
   return hipGetLastError();
 #undef LUCHK
 }

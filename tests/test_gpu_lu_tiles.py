@@ -1,0 +1,66 @@
+"""Tile kernels of the blocked LU at the sizes where they can go wrong: one
+tile, tile and block edges, remainders, and the first size whose trailing
+updates are split between the two streams.  A caller's matrix takes the pivoting
+panels (tile inverses formed from the factored block), an assembled one the
+speculative panels; both solve directions read the solve-ready form.
+
+Matrices 2 I + G / sqrt(n) with G complex Gaussian of unit variance have a
+2-norm condition number below 10, so the bound 8 n eps on the relative error of
+the solution leaves the growth of rounding errors in an n-step elimination
+(sqrt(n) in practice, n in the worst case) a factor of several.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2505_09545_amd import gdm
+    c = gdm.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 64, 100, 127, 128, 129, 143, 256, 273, 700, 1900])
+def test_getrf_getrs_tile_edges(ctx, n, dtype):
+    rng = np.random.default_rng(n)
+    A = 2 * np.eye(n) + (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(2 * n)
+    A = A[rng.permutation(n)]  # the diagonal is no pivot
+    B = rng.standard_normal((3, n)) + 1j * rng.standard_normal((3, n))
+    tol = 8 * max(n, 16) * (2.2e-16 if dtype == torch.complex128 else 1.2e-7)
+    F = torch.as_tensor(A.T.copy()).to(device="cuda", dtype=dtype).contiguous()  # column-major storage
+    ctx.getrf(F)
+    for trans in (0, 1):
+        X = torch.as_tensor(B).to(device="cuda", dtype=dtype).contiguous()
+        ctx.getrs(F, X, trans)
+        ref = np.linalg.solve(A.T if trans else A, B.T).T
+        err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert err.max() <= tol, (n, dtype, trans, err)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("dims", [(1, 1, 1), (5, 1, 1), (4, 4, 1), (43, 1, 1), (8, 8, 2), (43, 3, 1), (10, 10, 6), (9, 9, 8)])
+def test_speculative_tile_edges(ctx, dims, prec):
+    """n = 3 .. 1944 unknowns of dielectric boxes: the solution against LAPACK on
+    the matrix that the library itself assembles (condition numbers below 100:
+    1e-12 leaves 45 eps times that)."""
+    import gdm_inputs as gi
+    rng = np.random.default_rng(7)
+    r = gi.cuboid_cells(*dims, 7.0)
+    eps = rng.uniform(2.0, 9.0, len(r)) + 1j * rng.uniform(0.0, 0.5, len(r))
+    k, e0 = gi.random_planewaves(rng, 3)
+    before = ctx.pivot_fallbacks()
+    ctx.set_environment(1.1)
+    ctx.set_structure(r, 7.0, eps)
+    M = ctx.assemble(640.0).cpu().numpy()
+    ctx.factorize(640.0, prec)
+    f0 = ctx.incident_planewave(k, e0)
+    _, f = ctx.solve(f0)
+    ref = np.linalg.solve(M, f0.cpu().numpy().T).T
+    err = np.linalg.norm(f.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 1e-12, (dims, prec, err)
+    assert ctx.pivot_fallbacks() == before
