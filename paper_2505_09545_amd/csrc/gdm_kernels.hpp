@@ -255,10 +255,11 @@ struct LUWork {
   int32_t* spec;             // [nblocks] speculative panel failed its check (after npairs, same item stride)
   void* tmp;                 // [tmp_elems] complex scratch (operand copies, split-k partials, solve sweeps)
   void* tinv;                // [nblocks][tinv_block_elems(nb)] complex inverses of the 16 x 16 diagonal triangles
+  unsigned char* split;      // FP32: split L21 of even blocks, of odd blocks, then U12 (s_split bytes each)
   std::vector<hipEvent_t>* events;  // host-side pool of reusable events (look-ahead)
   int64_t tmp_elems;         // capacity of tmp per item in complex elements
   int nbatch = 1;
-  int64_t s_cand = 0, s_rows = 0, s_pairs = 0, s_npairs = 0, s_tmp = 0, s_tinv = 0;
+  int64_t s_cand = 0, s_rows = 0, s_pairs = 0, s_npairs = 0, s_tmp = 0, s_tinv = 0, s_split = 0;
   size_t bytes = 0;          // total size (set by lu_workspace_carve)
 };
 
@@ -291,12 +292,28 @@ hipError_t launch_diag_lu(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, int
 template <typename T>
 hipError_t launch_tile_inv(const cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, cplx<T>* tinv, hipStream_t st,
                            int nbatch, int64_t sA, int64_t stinv);
+// Where the solves below also write an FP32 operand split for the trailing update
+// (rows of L21 or columns of U12 from the pointers' first row or column on, a
+// multiple of 32 of them; planes null: nowhere; w 128 or 64; ssplit bytes per
+// batch item).
+struct SplitOut {
+  unsigned char* planes = nullptr;
+  float* scales = nullptr;
+};
+int64_t split_bytes(int64_t rows, int k);         // planes and scales of `rows` rows (or columns) x k
+int64_t split_planes_bytes(int64_t rows, int k);  // of that the planes, which come first
 // the nrows rows below the block become L21 = A21 U11^-1 (checked against the
 // pivots), and columns [cu, cu + ncols) of the block's rows U12 = L11^-1 A12
 template <typename T>
 hipError_t launch_tri_panel(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, int64_t nrows, int64_t cu, int64_t ncols,
                             const cplx<T>* tinv, int32_t* flag, hipStream_t st, int nbatch, int64_t sA, int64_t stinv,
-                            int64_t sflag);
+                            int64_t sflag, SplitOut lout, SplitOut uout, int64_t ssplit);
+hipError_t launch_split_rows(const float2* X, int64_t ld, int64_t nrows, int w, SplitOut out, hipStream_t st, int nbatch,
+                             int64_t sX, int64_t ssplit);
+// C (m x n) -= L U from split operands (update_split.hip), k a multiple of 16; sl,
+// su: the scales of L's rows and U's columns; sL bytes, sC entries per item
+hipError_t launch_update_split(int64_t m, int64_t n, int k, const void* L, const void* U, const float* sl, const float* su,
+                               float2* C, int64_t ldc, hipStream_t st, int num_cu, int nbatch, int64_t sL, int64_t sC);
 // solve-ready form of every block; tinv: the first block's tile inverses
 template <typename T>
 hipError_t launch_finish(cplx<T>* A, int64_t ld, int64_t n, int nb, const cplx<T>* tinv, hipStream_t st, int nbatch,

@@ -1303,6 +1303,10 @@ void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu,
   w.tmp = take((size_t)nbatch * w.s_tmp * cb);
   w.s_tinv = (int64_t)(al256(nblk * (size_t)tinv_block_elems(p.nb) * cb) / cb);
   w.tinv = take((size_t)nbatch * w.s_tinv * cb);
+  // split operands of the FP32 trailing updates (whole blocks of 128 or 64; the
+  // updates read whole 128-wide tiles from any multiple of 64 columns on)
+  w.s_split = elem_bytes == 4 && (p.nb == 128 || p.nb == 64) && (int64_t)nb < p.n ? split_bytes(p.n - (int64_t)nb + 128, p.nb) : 0;
+  w.split = reinterpret_cast<unsigned char*>(w.s_split ? take((size_t)nbatch * 3 * w.s_split) : nullptr);
   w.events = nullptr;
   w.bytes = off + 256;
 }
@@ -1471,12 +1475,32 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
       if ((r = hipGetLastError()) != hipSuccess) return r;
       return P.end(s);
     };
+    // FP32 updates read split operands: L21's planes alternate between two
+    // buffers (the next panel writes its own while this step's bulk update still
+    // reads), U12's columns go to disjoint parts of one
+    const bool split_ops = ws.s_split > 0 && w == nb;
+    const int64_t ssplit = 3 * ws.s_split, pl_bytes = split_planes_bytes(plan.n - nb + 128, nb);
+    SplitOut lout, uout;
+    if (split_ops) {
+      lout.planes = ws.split + (bi & 1) * ws.s_split;
+      lout.scales = reinterpret_cast<float*>(lout.planes + pl_bytes);
+      uout.planes = ws.split + 2 * ws.s_split;
+      uout.scales = reinterpret_cast<float*>(uout.planes + pl_bytes);
+    }
+    auto u_at = [&](int64_t cb) {  // the part of U12 from column cb on
+      SplitOut o = uout;
+      if (split_ops) {
+        o.planes += (cb - c1) / 32 * (int64_t)(nb / 16) * 4096;
+        o.scales += cb - c1;
+      }
+      return o;
+    };
     // L21 = A21 U11^-1 (speculative panels) and U12 = L11^-1 A12 of ncols columns
     auto tri = [&](hipStream_t s, int tag, int64_t nrows, int64_t cb, int64_t ncols) -> hipError_t {
       hipError_t r;
       if ((r = P.begin(s, tag, 8.0 * (double)(nrows + ncols) * w * w * fb)) != hipSuccess) return r;
-      if ((r = launch_tri_panel<T>(A, ld, nb, k0, w, nrows, cb, ncols, tinv, flag, s, NB, sA, ws.s_tinv, ws.s_npairs)) !=
-          hipSuccess)
+      if ((r = launch_tri_panel<T>(A, ld, nb, k0, w, nrows, cb, ncols, tinv, flag, s, NB, sA, ws.s_tinv, ws.s_npairs,
+                                   lout, u_at(cb), ssplit)) != hipSuccess)
         return r;
       return P.end(s);
     };
@@ -1484,6 +1508,15 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
     auto update = [&](hipStream_t s, int tag, int64_t cb, int64_t ncols) -> hipError_t {
       hipError_t r;
       if ((r = P.begin(s, tag, 8.0 * (double)nr * (double)ncols * w * fb)) != hipSuccess) return r;
+      if constexpr (sizeof(T) == 4) {
+        if (split_ops) {
+          const SplitOut uo = u_at(cb);
+          if ((r = launch_update_split(nr, ncols, w, lout.planes, uo.planes, lout.scales, uo.scales, A + c1 + cb * ld, ld, s,
+                                       ws.gmax, NB, ssplit, sA)) != hipSuccess)
+            return r;
+          return P.end(s);
+        }
+      }
       if ((r = launch_gemm_update<T>(nr, ncols, w, A + c1 + k0 * ld, ld, A + k0 + cb * ld, ld, A + c1 + cb * ld, ld, s, NB,
                                      sA, sA, sA)) != hipSuccess)
         return r;
@@ -1492,6 +1525,9 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
     // L21 needs the panel alone: while the previous block's bulk update still
     // runs it goes ahead of the wait, else it shares the U12 block's launch
     const int64_t lrows = plan.spec ? nr : 0;
+    if constexpr (sizeof(T) == 4) {
+      if (!plan.spec && split_ops) LUCHK(launch_split_rows(A + c1 + k0 * ld, ld, nr, w, lout, st, NB, sA, ssplit));
+    }
     if (bulk_done) {
       if (lrows > 0) LUCHK(tri(st, PROF_PANEL_L21, lrows, c1, 0));
       LUCHK(hipStreamWaitEvent(st, bulk_done, 0));  // columns of this step were in the bulk

@@ -125,15 +125,54 @@ __device__ inline Frag<T> load_inv(const cplx<T>* __restrict__ ti, int s, int lr
   return f;
 }
 
+// Rows (columns) r0 .. r0 + 15 into the split planes of the trailing update
+// (update_split.hip), k = 16 NT of each in tiles x: scaled so that the largest
+// |re|, |im| of a row lies in [2^13, 2^14), then h + l with both rounded to f16;
+// fragments [r / 32][k / 16][plane] of 64 lanes x 8 f16, lane = r % 32 + 32 (k %
+// 16 / 8); the row's inverse scale to scales[r].  Every lane of the wave calls it.
+template <int NT>
+__device__ inline void put_planes(unsigned char* planes, float* scales, const Tile<float> (&x)[NT], int64_t r0, bool rv,
+                                  int lr, int lk) {
+  float big = 0.f;
+  static_for<NT>([&](auto s) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) big = fmaxf(big, fmaxf(fabsf(x[s].re[q]), fabsf(x[s].im[q])));
+  });
+  big = fmaxf(big, __shfl_xor(big, 16));
+  big = fmaxf(big, __shfl_xor(big, 32));
+  int ex = 14 - __builtin_amdgcn_frexp_expf(big);
+  // the scale and its inverse are both normal numbers
+  ex = big > 0.f ? min(max(ex, -113), 126) : 0;
+  const float sc = ldexpf(1.f, ex);
+  if (!rv) return;
+  if (lk == 0) scales[r0 + lr] = ldexpf(1.f, -ex);
+  unsigned char* f = planes + (r0 >> 5) * NT * 4096 + ((int)(r0 & 16) + lr + 32 * (lk >> 1)) * 16 + 8 * (lk & 1);
+  typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+  static_for<NT>([&](auto s) {
+    f16x4 p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float a = x[s].re[q] * sc, b = x[s].im[q] * sc;
+      p[0][q] = (_Float16)a;
+      p[1][q] = (_Float16)(a - (float)p[0][q]);
+      p[2][q] = (_Float16)b;
+      p[3][q] = (_Float16)(b - (float)p[2][q]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<f16x4*>(f + 4096 * s + 1024 * i) = p[i];
+  });
+}
+
 // One wave's blocked substitution on 16 rows (RIGHT) or columns of X, in place.
 enum { TRI_RIGHT_UPPER = 0, TRI_LEFT_LOWER = 1, TRI_RIGHT_LOWER = 2 };
 
 // NT: number of tiles of the block.  CHECK (TRI_RIGHT_UPPER): returns whether an
-// entry fails |l u_jj| <= |u_jj|.
+// entry fails |l u_jj| <= |u_jj|.  planes (FP32, may be null): X also goes there
+// split, as the trailing update reads it.
 template <typename T, int KIND, int NT, bool FULL, bool CHECK>
 __device__ inline bool tri_wave(const cplx<T>* __restrict__ D, int64_t ld, int w, const cplx<T>* __restrict__ linv,
                                 const cplx<T>* __restrict__ uinv, cplx<T>* __restrict__ X, int64_t ldx, int64_t r0,
-                                int64_t cnt) {
+                                int64_t cnt, unsigned char* planes, float* scales) {
   using CT = cplx<T>;
   constexpr bool TR = KIND != TRI_LEFT_LOWER;
   const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
@@ -215,19 +254,22 @@ __device__ inline bool tri_wave(const cplx<T>* __restrict__ D, int64_t ld, int w
     }
     __builtin_amdgcn_sched_barrier(0);  // operands of a later step are not hoisted past here (registers)
   });
+  if constexpr (sizeof(T) == 4 && FULL && KIND != TRI_RIGHT_LOWER)
+    if (planes) put_planes<NT>(planes, scales, x, r0, rv, lr, lk);
   return CHECK && bad && rv;
 }
 
-// A block of any width: whole tiles of 128, 64 or 32 columns unrolled without
-// masks, else the smallest masked form that holds it.
+// A block of any width: blocks of 128 or 64 columns unrolled without
+// masks, else the smallest masked form that holds it (no planes: split updates
+// follow whole blocks of 128 or 64 only).
 template <typename T, int KIND, bool CHECK>
 __device__ inline bool tri_wave_any(const cplx<T>* __restrict__ D, int64_t ld, int w, const cplx<T>* __restrict__ linv,
                                     const cplx<T>* __restrict__ uinv, cplx<T>* __restrict__ X, int64_t ldx, int64_t r0,
-                                    int64_t cnt) {
-  if (w == 128) return tri_wave<T, KIND, 8, true, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt);
-  if (w == 64) return tri_wave<T, KIND, 4, true, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt);
-  if (w <= 64) return tri_wave<T, KIND, 4, false, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt);
-  return tri_wave<T, KIND, 8, false, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt);
+                                    int64_t cnt, unsigned char* planes = nullptr, float* scales = nullptr) {
+  if (w == 128) return tri_wave<T, KIND, 8, true, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt, planes, scales);
+  if (w == 64) return tri_wave<T, KIND, 4, true, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt, planes, scales);
+  if (w <= 64) return tri_wave<T, KIND, 4, false, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt, nullptr, nullptr);
+  return tri_wave<T, KIND, 8, false, CHECK>(D, ld, w, linv, uinv, X, ldx, r0, cnt, nullptr, nullptr);
 }
 
 __device__ inline float lane_of(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
@@ -567,24 +609,48 @@ __global__ void __launch_bounds__(64) tile_inv_kernel(const cplx<T>* __restrict_
 // wave per 16 rows or columns, the columns first.
 template <typename T>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
-tri_panel_kernel(cplx<T>* __restrict__ A, int64_t ld, int64_t k0, int w,
-                                                       int64_t nrows, int64_t cu, int64_t ncols, int cblocks,
-                                                       const cplx<T>* __restrict__ tinv, int uoff,
-                                                       int32_t* __restrict__ flag, int64_t sA, int64_t stinv,
-                                                       int64_t sflag) {
+tri_panel_kernel(cplx<T>* __restrict__ A, int64_t ld, int64_t k0, int w, int64_t nrows, int64_t cu, int64_t ncols,
+                 int cblocks, const cplx<T>* __restrict__ tinv, int uoff, int32_t* __restrict__ flag,
+                 SplitOut lout, SplitOut uout, int64_t sA, int64_t stinv, int64_t sflag, int64_t ssplit) {
   using CT = cplx<T>;
   A += (int64_t)blockIdx.y * sA;
   tinv += (int64_t)blockIdx.y * stinv;
   flag += (int64_t)blockIdx.y * sflag;
   const CT* D = A + k0 + k0 * ld;
   const int b = blockIdx.x;
+  const int64_t po = (int64_t)blockIdx.y * ssplit;  // bytes per item
   if (b < cblocks) {
-    tri_wave_any<T, TRI_LEFT_LOWER, false>(D, ld, w, tinv, tinv + uoff, A + k0 + cu * ld, ld, 16 * (int64_t)b, ncols);
+    tri_wave_any<T, TRI_LEFT_LOWER, false>(D, ld, w, tinv, tinv + uoff, A + k0 + cu * ld, ld, 16 * (int64_t)b, ncols,
+                                           uout.planes ? uout.planes + po : nullptr, uout.scales + po / 4);
   } else {
     const bool bad = tri_wave_any<T, TRI_RIGHT_UPPER, true>(D, ld, w, tinv, tinv + uoff, A + (k0 + w) + k0 * ld, ld,
-                                                            16 * (int64_t)(b - cblocks), nrows);
+                                                            16 * (int64_t)(b - cblocks), nrows,
+                                                            lout.planes ? lout.planes + po : nullptr,
+                                                            lout.scales + po / 4);
     if (__ballot(bad) != 0 && threadIdx.x == 0) atomicOr(flag, 1);
   }
+}
+
+// The split planes of an L21 that a pivoting panel has formed (16 NT columns).
+template <int NT>
+__global__ void __launch_bounds__(64) split_rows_kernel(const float2* __restrict__ X, int64_t ld, int64_t nrows,
+                                                        SplitOut out, int64_t sX, int64_t ssplit) {
+  X += (int64_t)blockIdx.y * sX;
+  const int64_t po = (int64_t)blockIdx.y * ssplit;
+  const int lane = threadIdx.x, lr = lane & 15, lk = lane >> 4;
+  const int64_t r0 = 16 * (int64_t)blockIdx.x;
+  const bool rv = r0 + lr < nrows;
+  X += rv ? r0 + lr : nrows - 1;
+  Tile<float> x[NT];
+  static_for<NT>([&](auto s) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float2 v = X[(int64_t)(16 * s + rof<float>(lk, q)) * ld];
+      x[s].re[q] = v.x;
+      x[s].im[q] = v.y;
+    }
+  });
+  put_planes<NT>(out.planes + po, out.scales + po / 4, x, r0, rv, lr, lk);
 }
 
 // Solve-ready block columns, all blocks in one launch: rows above block
@@ -703,12 +769,23 @@ hipError_t launch_tile_inv(const cplx<T>* A, int64_t ld, int nb, int64_t k0, int
 template <typename T>
 hipError_t launch_tri_panel(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, int64_t nrows, int64_t cu, int64_t ncols,
                             const cplx<T>* tinv, int32_t* flag, hipStream_t st, int nbatch, int64_t sA, int64_t stinv,
-                            int64_t sflag) {
+                            int64_t sflag, SplitOut lout, SplitOut uout, int64_t ssplit) {
   const int64_t cb = (ncols + 15) / 16, rb = (nrows + 15) / 16;
   if (cb + rb <= 0) return hipSuccess;
   if (w < 1 || w > 128 || w > nb || cb + rb > INT32_MAX) return hipErrorInvalidValue;
+  if ((lout.planes || uout.planes) && w != 128 && w != 64) return hipErrorInvalidValue;
   hipLaunchKernelGGL(tri_panel_kernel<T>, dim3((unsigned)(cb + rb), (unsigned)nbatch), dim3(64), 0, st, A, ld, k0, w,
-                     nrows, cu, ncols, (int)cb, tinv, tinv_uoff(nb), flag, sA, stinv, sflag);
+                     nrows, cu, ncols, (int)cb, tinv, tinv_uoff(nb), flag, lout, uout, sA, stinv, sflag, ssplit);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_rows(const float2* X, int64_t ld, int64_t nrows, int w, SplitOut out, hipStream_t st, int nbatch,
+                             int64_t sX, int64_t ssplit) {
+  if (nrows <= 0) return hipSuccess;
+  if ((w != 128 && w != 64) || (nrows + 15) / 16 > INT32_MAX) return hipErrorInvalidValue;
+  const dim3 g((unsigned)((nrows + 15) / 16), (unsigned)nbatch);
+  if (w == 128) hipLaunchKernelGGL(split_rows_kernel<8>, g, dim3(64), 0, st, X, ld, nrows, out, sX, ssplit);
+  else hipLaunchKernelGGL(split_rows_kernel<4>, g, dim3(64), 0, st, X, ld, nrows, out, sX, ssplit);
   return hipGetLastError();
 }
 
@@ -735,7 +812,8 @@ hipError_t launch_finish(cplx<T>* A, int64_t ld, int64_t n, int nb, const cplx<T
   template hipError_t launch_tile_inv<T>(const cplx<T>*, int64_t, int, int64_t, int, cplx<T>*, hipStream_t, int,       \
                                          int64_t, int64_t);                                                            \
   template hipError_t launch_tri_panel<T>(cplx<T>*, int64_t, int, int64_t, int, int64_t, int64_t, int64_t,             \
-                                          const cplx<T>*, int32_t*, hipStream_t, int, int64_t, int64_t, int64_t);      \
+                                          const cplx<T>*, int32_t*, hipStream_t, int, int64_t, int64_t, int64_t,       \
+                                          SplitOut, SplitOut, int64_t);                                                \
   template hipError_t launch_finish<T>(cplx<T>*, int64_t, int64_t, int, const cplx<T>*, hipStream_t, int, int64_t,     \
                                        int64_t);
 GDM_TILES(double)

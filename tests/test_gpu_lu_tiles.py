@@ -64,3 +64,22 @@ def test_speculative_tile_edges(ctx, dims, prec):
     err = np.linalg.norm(f.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= 1e-12, (dims, prec, err)
     assert ctx.pivot_fallbacks() == before
+
+
+def test_getrf_fp32_column_scales(ctx):
+    """Columns scaled by powers of two from 2^-40 to 2^40 (far outside the range of
+    the 16-bit operands of the FP32 updates): the pivots and every rounding stay
+    the same, so D X of the scaled system (A D) X = B meets the same bound."""
+    n = 700
+    rng = np.random.default_rng(3)
+    A = 2 * np.eye(n) + (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(2 * n)
+    A = A[rng.permutation(n)]
+    D = 2.0 ** rng.integers(-40, 41, n)
+    B = rng.standard_normal((2, n)) + 1j * rng.standard_normal((2, n))
+    F = torch.as_tensor((A * D[None, :]).T.copy()).to(device="cuda", dtype=torch.complex64).contiguous()
+    X = torch.as_tensor(B).to(device="cuda", dtype=torch.complex64).contiguous()
+    ctx.getrf(F)
+    ctx.getrs(F, X, 0)
+    ref = np.linalg.solve(A, B.T).T
+    err = np.linalg.norm(X.cpu().numpy() * D[None, :] - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 8 * n * 1.2e-7, err
