@@ -1,8 +1,10 @@
 // Step (c) of the hot path: scattered fields at probe points by re-propagation
 // of the dipole moments,  F_sca(r_p) = sum_j G(r_p, r_j) q_j  (arXiv:2505.09545,
 // Sec. "Observables", first item, with the dyad of Eq. superprop_G), evaluated
-// matrix-free in FP64: the 6x6 dyad of every (probe, dipole) pair is recomputed
-// in registers (one sincos per pair) and never stored.
+// matrix-free in FP64: the dyad of every (probe, dipole) pair is recomputed in
+// registers (gdm_dyad.hpp) and never stored.  Bound by the FP64 vector rate
+// (262 144 probes x 4784 dipoles, E and H: 5.9 ms; 9.8 with the 3 x 3 matrices of
+// the dyad and the library sincos).
 //
 // Work decomposition: one thread per probe and RHS chunk; the dipoles are
 // swept in tiles of 256 staged in LDS (position + moments), so each dipole is
@@ -14,6 +16,7 @@
 // Moment layout q[r][u] (u = unknown index): p of dipole d at u = 3d..3d+2 for
 // all N dipoles, m of effective dipole e at u = 3N + 3e.  Output E, H [nrhs][P][3].
 #include "gdm_common.hpp"
+#include "gdm_dyad.hpp"
 #include "gdm_kernels.hpp"
 #include "gdm_misc.hpp"
 
@@ -50,6 +53,7 @@ __global__ void __launch_bounds__(256) fields_kernel(DipoleView d, Wave w, const
       H[r][a] = make_double2(0, 0);
     }
   const int64_t N = d.N, nc = d.nc;
+  const double inv_n = w.k0 / w.k;
   for (int64_t t0 = j0; t0 < j1; t0 += FT) {
     const int nt = (int)(j1 - t0 < FT ? j1 - t0 : FT);
     __syncthreads();
@@ -78,7 +82,7 @@ __global__ void __launch_bounds__(256) fields_kernel(DipoleView d, Wave w, const
       for (int r = 0; r < NR; ++r)
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          sp[t][r][a] = qv[r][a];
+          sp[t][r][a] = cscale(qv[r][a], inv_n);  // P = p / n
           sm[t][r][a] = mv[r][a];
         }
     }
@@ -86,42 +90,23 @@ __global__ void __launch_bounds__(256) fields_kernel(DipoleView d, Wave w, const
     if (!live) continue;
     const int ncell_in_tile = (int)(nc - t0 > 0 ? (nc - t0 < nt ? nc - t0 : nt) : 0);
     for (int t = 0; t < nt; ++t) {
-      const double Rx = x - spos[t][0], Ry = y - spos[t][1], Rz = z - spos[t][2];
-      const double R2 = Rx * Rx + Ry * Ry + Rz * Rz;
+      const double R[3] = {x - spos[t][0], y - spos[t][1], z - spos[t][2]};
+      const double R2 = fma(R[2], R[2], fma(R[1], R[1], R[0] * R[0]));
       if (R2 < min_r2) {
         atomicOr(flag, 1);
         continue;
       }
-      Green g;
-      green_eh(Rx, Ry, Rz, w, true, g);
+      const Dyad g = dyad_at<true>(R2, w.k);
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
-        const double2 px = sp[t][r][0], py = sp[t][r][1], pz = sp[t][r][2];
-        // E += G^Ep p
-        cfma(E[r][0], g.e[0], px); cfma(E[r][0], g.e[3], py); cfma(E[r][0], g.e[4], pz);
-        cfma(E[r][1], g.e[3], px); cfma(E[r][1], g.e[1], py); cfma(E[r][1], g.e[5], pz);
-        cfma(E[r][2], g.e[4], px); cfma(E[r][2], g.e[5], py); cfma(E[r][2], g.e[2], pz);
-        // H += h x p
-        cfma(H[r][0], g.h[1], pz); cfma(H[r][0], cscale(g.h[2], -1.0), py);
-        cfma(H[r][1], g.h[2], px); cfma(H[r][1], cscale(g.h[0], -1.0), pz);
-        cfma(H[r][2], g.h[0], py); cfma(H[r][2], cscale(g.h[1], -1.0), px);
+        dyad_electric(E[r], g, R, sp[t][r][0], sp[t][r][1], sp[t][r][2]);
+        dyad_magnetic<1>(H[r], g, R, sp[t][r][0], sp[t][r][1], sp[t][r][2]);
       }
       if (t >= ncell_in_tile) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-          const double2 mx = sm[t][r][0], my = sm[t][r][1], mz = sm[t][r][2];
-          // E += G^Em m = -(h x m)
-          cfma(E[r][0], cscale(g.h[1], -1.0), mz); cfma(E[r][0], g.h[2], my);
-          cfma(E[r][1], cscale(g.h[2], -1.0), mx); cfma(E[r][1], g.h[0], mz);
-          cfma(E[r][2], cscale(g.h[0], -1.0), my); cfma(E[r][2], g.h[1], mx);
-          // H += eps G^Ep m
-          double2 t0v = make_double2(0, 0), t1v = make_double2(0, 0), t2v = make_double2(0, 0);
-          cfma(t0v, g.e[0], mx); cfma(t0v, g.e[3], my); cfma(t0v, g.e[4], mz);
-          cfma(t1v, g.e[3], mx); cfma(t1v, g.e[1], my); cfma(t1v, g.e[5], mz);
-          cfma(t2v, g.e[4], mx); cfma(t2v, g.e[5], my); cfma(t2v, g.e[2], mz);
-          H[r][0] = cadd(H[r][0], cscale(t0v, w.eps_env));
-          H[r][1] = cadd(H[r][1], cscale(t1v, w.eps_env));
-          H[r][2] = cadd(H[r][2], cscale(t2v, w.eps_env));
+          dyad_magnetic<-1>(E[r], g, R, sm[t][r][0], sm[t][r][1], sm[t][r][2]);
+          dyad_electric(H[r], g, R, sm[t][r][0], sm[t][r][1], sm[t][r][2]);
         }
       }
     }
@@ -132,7 +117,7 @@ __global__ void __launch_bounds__(256) fields_kernel(DipoleView d, Wave w, const
     if (r0 + r >= nrhs) break;
     double2* oe = outE + split * split_stride + ((int64_t)(r0 + r) * P + p) * 3;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) oe[a] = E[r][a];
+    for (int a = 0; a < 3; ++a) oe[a] = cscale(E[r][a], inv_n);
     if (outH) {
       double2* oh = outH + split * split_stride + ((int64_t)(r0 + r) * P + p) * 3;
 #pragma unroll

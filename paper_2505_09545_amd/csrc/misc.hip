@@ -11,7 +11,11 @@
 //  * extinction / absorption / scattering cross sections (Sec. "Observables"):
 //    the kernels return the raw FP64 sums, the prefactor C = 4 pi k0 /
 //    (n_env |E0|^2) is applied on the host.
+#include <algorithm>
+#include <type_traits>
+
 #include "gdm_common.hpp"
+#include "gdm_dyad.hpp"
 #include "gdm_kernels.hpp"
 #include "gdm_misc.hpp"
 
@@ -200,70 +204,131 @@ hipError_t launch_cs_sums(const DipoleView& d, const double2* f0, const double2*
   return hipGetLastError();
 }
 
-// Im sum_{i != j} q_i^H G6(r_i - r_j) q_j for one RHS per blockIdx.y
-constexpr int FFT = 128;
-__global__ void __launch_bounds__(256) sca_ff_kernel(DipoleView d, Wave w, const double2* q, int64_t ldq,
-                                                     double* partial, int64_t nblk) {
+// Im sum_{i != j} q_i^H G6(r_i - r_j) q_j, NR right-hand sides per workgroup (the
+// dyad of a pair once for all of them): a thread sums the field of the sources of
+// its split at dipole i, then takes it against q_i.  blockIdx.x: (256 targets,
+// split of the sources), blockIdx.y: right-hand sides.  Bound by the FP64 vector
+// rate.  N = 2431, 24 right-hand sides: 0.44 ms (2.3 ms with a dyad matrix and its
+// quadratic form per pair and right-hand side, one workgroup per 256 targets).
+constexpr int FFT = 64;  // sources per LDS tile
+
+template <int NR>
+__global__ void __launch_bounds__(256) sca_ff_kernel(DipoleView d, Wave w, const double2* q, int64_t ldq, int64_t nrhs,
+                                                     int nsplit, int64_t jps, double* partial, int64_t nblk) {
   __shared__ double spos[FFT][3];
-  __shared__ double2 sq[FFT][6];
+  __shared__ double2 sq[FFT][NR][6];  // P = p / n, then m
   __shared__ double red[256];
-  const int64_t r = blockIdx.y;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const double2* qc = q + r * ldq;
+  const int64_t r0 = (int64_t)blockIdx.y * NR;
+  const int64_t i = (int64_t)(blockIdx.x / nsplit) * 256 + threadIdx.x;
+  const int split = (int)(blockIdx.x % nsplit);
   const int64_t N = d.N, nc = d.nc;
-  const bool live = i < N;
-  double xi = 0, yi = 0, zi = 0;
-  double2 qi[6];
-  for (int c = 0; c < 6; ++c) qi[c] = make_double2(0, 0);
+  const int64_t j0 = split * jps, j1 = j0 + jps < N ? j0 + jps : N;
+  const bool live = i < N, eff_t = live && i >= nc;
+  const bool any_eff_t = __any(eff_t);
+  const double inv_n = w.k0 / w.k;
+  double x = 0, y = 0, z = 0;
   if (live) {
-    xi = d.pos[3 * i];
-    yi = d.pos[3 * i + 1];
-    zi = d.pos[3 * i + 2];
-    for (int c = 0; c < 3; ++c) qi[c] = qc[3 * i + c];
-    if (i >= nc)
-      for (int c = 0; c < 3; ++c) qi[3 + c] = qc[3 * N + 3 * (i - nc) + c];
+    x = d.pos[3 * i];
+    y = d.pos[3 * i + 1];
+    z = d.pos[3 * i + 2];
   }
-  double acc = 0;
-  for (int64_t t0 = 0; t0 < N; t0 += FFT) {
-    const int nt = (int)(N - t0 < FFT ? N - t0 : FFT);
+  double2 E[NR][3], H[NR][3];
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) E[r][a] = H[r][a] = make_double2(0, 0);
+  for (int64_t t0 = j0; t0 < j1; t0 += FFT) {
+    const int nt = (int)(j1 - t0 < FFT ? j1 - t0 : FFT);
     __syncthreads();
-    for (int t = threadIdx.x; t < nt; t += 256) {
-      const int64_t j = t0 + t;
-      for (int a = 0; a < 3; ++a) spos[t][a] = d.pos[3 * j + a];
-      for (int c = 0; c < 3; ++c) sq[t][c] = qc[3 * j + c];
-      for (int c = 0; c < 3; ++c) sq[t][3 + c] = j >= nc ? qc[3 * N + 3 * (j - nc) + c] : make_double2(0, 0);
+    for (int t = threadIdx.x; t < nt * NR; t += 256) {
+      const int64_t j = t0 + t / NR;
+      const int r = t % NR;
+      const double2* qc = q + (r0 + r) * ldq;
+      const bool rv = r0 + r < nrhs;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double2 p = rv ? qc[3 * j + a] : make_double2(0, 0);
+        sq[t / NR][r][a] = cscale(p, inv_n);
+        sq[t / NR][r][3 + a] = rv && j >= nc ? qc[3 * N + 3 * (j - nc) + a] : make_double2(0, 0);
+        if (r == 0) spos[t / NR][a] = d.pos[3 * j + a];
+      }
     }
     __syncthreads();
     if (!live) continue;
-    for (int t = 0; t < nt; ++t) {
-      if (t0 + t == i) continue;
-      Green g;
-      green_eh(xi - spos[t][0], yi - spos[t][1], zi - spos[t][2], w, true, g);
-      double2 s = make_double2(0, 0);
-      for (int a = 0; a < 6; ++a) {
-        double2 v = make_double2(0, 0);
-        for (int b = 0; b < 6; ++b) cfma(v, g6(g, w.eps_env, a, b), sq[t][b]);
-        cfma(s, cconj(qi[a]), v);
+    const int ncell_in_tile = (int)(nc - t0 > 0 ? (nc - t0 < nt ? nc - t0 : nt) : 0);
+    auto sweep = [&](auto hs, auto ht, int ta, int tb) __attribute__((always_inline)) {
+      constexpr bool HS = decltype(hs)::value, HT = decltype(ht)::value;
+      for (int t = ta; t < tb; ++t) {
+        if (t0 + t == i) continue;
+        const double R[3] = {x - spos[t][0], y - spos[t][1], z - spos[t][2]};
+        const Dyad g = dyad_at<HS || HT>(fma(R[2], R[2], fma(R[1], R[1], R[0] * R[0])), w.k);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          dyad_electric(E[r], g, R, sq[t][r][0], sq[t][r][1], sq[t][r][2]);
+          if (HT) dyad_magnetic<1>(H[r], g, R, sq[t][r][0], sq[t][r][1], sq[t][r][2]);
+          if (HS) {
+            dyad_magnetic<-1>(E[r], g, R, sq[t][r][3], sq[t][r][4], sq[t][r][5]);
+            if (HT) dyad_electric(H[r], g, R, sq[t][r][3], sq[t][r][4], sq[t][r][5]);
+          }
+        }
       }
-      acc += s.y;
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (any_eff_t) {
+      sweep(no, yes, 0, ncell_in_tile);
+      sweep(yes, yes, ncell_in_tile, nt);
+    } else {
+      sweep(no, no, 0, ncell_in_tile);
+      sweep(yes, no, ncell_in_tile, nt);
     }
   }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    // Im conj(P_i) . N + Im conj(m_i) . H
+    double acc = 0;
+    if (live && r0 + r < nrhs) {
+      const double2* qc = q + (r0 + r) * ldq;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double2 p = cscale(qc[3 * i + a], inv_n);
+        acc += p.x * E[r][a].y - p.y * E[r][a].x;
+        if (eff_t) {
+          const double2 m = qc[3 * N + 3 * (i - nc) + a];
+          acc += m.x * H[r][a].y - m.y * H[r][a].x;
+        }
+      }
+    }
     __syncthreads();
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+      if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0 && r0 + r < nrhs) partial[(r0 + r) * nblk + blockIdx.x] = red[0];
   }
-  if (threadIdx.x == 0) partial[r * nblk + blockIdx.x] = red[0];
 }
 
-int64_t sca_ff_blocks(int64_t N) { return (N + 255) / 256; }
+// splits of the sources: about 256 workgroups per group of right-hand sides, at
+// least one LDS tile each
+static int sca_ff_splits(int64_t N) {
+  const int64_t tb = (N + 255) / 256;
+  return (int)std::max<int64_t>(1, std::min<int64_t>((N + FFT - 1) / FFT, 256 / tb));
+}
+int64_t sca_ff_blocks(int64_t N) { return (N + 255) / 256 * sca_ff_splits(N); }
 
 hipError_t launch_sca_ff(const DipoleView& d, const Wave& w, const double2* q, int64_t ldq, int64_t nrhs,
                          double* partial, int64_t nblk, hipStream_t st) {
   if (nrhs <= 0 || d.N <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sca_ff_kernel, dim3((unsigned)nblk, (unsigned)nrhs), dim3(256), 0, st, d, w, q, ldq, partial,
-                     nblk);
+  const int ns = sca_ff_splits(d.N);
+  const int64_t jps = ((d.N + ns - 1) / ns + FFT - 1) / FFT * FFT;  // trailing splits may be empty (partial sum 0)
+  if (nrhs == 1)
+    hipLaunchKernelGGL(sca_ff_kernel<1>, dim3((unsigned)nblk, 1), dim3(256), 0, st, d, w, q, ldq, nrhs, ns, jps, partial,
+                       nblk);
+  else
+    hipLaunchKernelGGL(sca_ff_kernel<4>, dim3((unsigned)nblk, (unsigned)((nrhs + 3) / 4)), dim3(256), 0, st, d, w, q, ldq,
+                       nrhs, ns, jps, partial, nblk);
   return hipGetLastError();
 }
 
