@@ -64,6 +64,29 @@ struct DevBuf {
   template <typename T> T* as() const { return static_cast<T*>(p); }
 };
 
+// pinned host memory, grown on demand
+struct HostBuf {
+  void* p = nullptr;
+  size_t cap = 0;
+  hipError_t ensure(size_t bytes) {
+    if (bytes <= cap && p) return hipSuccess;
+    release();
+    hipError_t e = hipHostMalloc(&p, bytes);
+    if (e != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();
+      return e;
+    }
+    cap = bytes;
+    return hipSuccess;
+  }
+  void release() {
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    cap = 0;
+  }
+};
+
 __global__ void fill_i32_kernel(int* a, int n, int v) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = v;
@@ -107,6 +130,7 @@ struct gdm_ctx {
   DevBuf Lam, adj;  // adjoint field and adjoint workspace
   DevBuf part;      // split-k partial sums of the small-RHS refinement residual
   DevBuf iter;      // workspace of gdm_solve_iterative
+  HostBuf iter_host;  // the scalars its kernels hand to the host
   DevBuf src;       // unit point sources of gdm_ldos / gdm_green_tensor: positions, moments, F0, q, fields
   // batched spectra: workspaces and the measured batch configuration per size class
   DevBuf bM64, bM32, bipiv, bws, bvec, bpart, bsmall, bpos, bwl;
@@ -910,6 +934,7 @@ void gdm_destroy(gdm_ctx* c) {
   (void)hipSetDevice(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   for (DevBuf* b : c->buffers()) b->release();
+  c->iter_host.release();
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
   for (auto& e : c->sev)
@@ -1143,13 +1168,14 @@ gdm_status gdm_solve_iterative(gdm_ctx* c, double wl, int64_t nrhs, const double
   const DipoleView d = view_of(c, self_term(c, w));
   HIPCHK(c, c->iter.ensure(iter_workspace_bytes(c->N, n, nrhs, restart, c->num_cu)));
   HIPCHK(c, c->X.ensure(sizeof(double2) * n * nrhs));
+  HIPCHK(c, c->iter_host.ensure(gmres_host_bytes(nrhs, restart)));
   IterWork iw;
   iter_workspace_carve(c->iter.p, c->N, n, nrhs, restart, c->num_cu, iw);
   double2* X = c->X.as<double2>();
   HIPCHK(c, hipEventRecord(c->ev[0], c->stream));
   GmresStats gs;
   HIPCHK(c, gmres_solve(d, w, iw, n, nrhs, reinterpret_cast<const double2*>(f0), X, tol, max_iter, restart, c->stream,
-                        gs, &c->prof));
+                        gs, c->iter_host.p, &c->prof));
   HIPCHK(c, launch_apply_alpha(view_of(c, make_double2(0, 0)), X, n, reinterpret_cast<double2*>(q_out), n, nrhs,
                                c->stream));
   if (f_out) HIPCHK(c, launch_copy_d(X, n, reinterpret_cast<double2*>(f_out), n, n, nrhs, c->stream));

@@ -13,13 +13,14 @@ struct IterWork {
   double2* V;     // [restart + 1][nrhs][n] Krylov basis
   double2* z;     // [nrhs][n] preconditioned vector
   double2* q;     // [nrhs][n] moments A z of the product
-  double2* t;     // [nrhs][n] scratch
+  double2* t;     // [nrhs][n] scratch between cycles
   double2* part;  // [nsplit][nrhs][n] partial coupling sums
   double2* inv;   // [nblk][PC_MAXD][PC_MAXD] block inverses (column-major)
-  double2* h;     // [2][restart + 1][nrhs] Gram-Schmidt coefficients of the two passes
-  double* nrm;    // [2][nrhs] norms
+  double2* hp;    // [2][nrhs][restart + 1][C] parts of the Gram-Schmidt products of the two passes (in t)
+  double* np;     // [nrhs][C] parts of squared norms
   double2* y;     // [restart + 1][nrhs] least-squares solution of a cycle
   int nsplit = 1;
+  int E = 128, C = 1;  // entries per workgroup of the vector kernels, workgroups per right-hand side
   int64_t nblk = 0;
   size_t bytes = 0;
 };
@@ -44,6 +45,8 @@ hipError_t launch_matvec(const DipoleView& d, const Wave& w, const IterWork& iw,
 // at a restart) or max_iter iterations.
 hipError_t gmres_solve(const DipoleView& d, const Wave& w, const IterWork& iw, int64_t n, int64_t nrhs,
                        const double2* B, double2* X, double tol, int max_iter, int restart, hipStream_t st,
-                       GmresStats& gs, Prof* prof);
+                       GmresStats& gs, void* host, Prof* prof);
+// pinned host memory that gmres_solve's kernels write their scalars to
+size_t gmres_host_bytes(int64_t nrhs, int restart);
 
 }  // namespace gdm

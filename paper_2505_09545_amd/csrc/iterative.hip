@@ -319,27 +319,230 @@ __global__ void __launch_bounds__(64) precond_apply_kernel(DipoleView d, const d
 // ---------------------------------------------------------------------------
 // Krylov vector kernels on [nrhs][n] arrays (basis vector i at V + i vs)
 // ---------------------------------------------------------------------------
-// h[i][r] = sum_k conj(V_i[r][k]) w[r][k]: one workgroup per (i, r), fixed order
-__global__ void __launch_bounds__(256) mdot_kernel(const double2* __restrict__ V, int64_t vs,
-                                                    const double2* __restrict__ w, int64_t n, int nrhs,
-                                                    double2* __restrict__ h) {
-  __shared__ double2 red[256];
-  const int i = blockIdx.x, r = blockIdx.y;
-  const double2* a = V + i * vs + (int64_t)r * n;
-  const double2* b = w + (int64_t)r * n;
-  double2 s = make_double2(0, 0);
-  for (int64_t k = threadIdx.x; k < n; k += 256) {
-    const double2 av = a[k], bv = b[k];
-    s.x += av.x * bv.x + av.y * bv.y;
-    s.y += av.x * bv.y - av.y * bv.x;
+// An Arnoldi step after the product is three launches of arnoldi_kernel and one
+// of scale_precond_kernel, each a pass over the basis or over W that also begins
+// the next reduction: workgroup c of a right-hand side owns the entries
+// [c E, (c + 1) E), leaves its part of every scalar product in hp (norm: np), and
+// the next launch's workgroups add the parts in a fixed order.  Bound by the
+// traffic of the basis from 10^4 unknowns on, below by launches and latency.
+// Per step (15 basis vectors, the mean of a cycle of 30): n = 9900 24 us, n = 69 000
+// 57 us; as ten kernels (one workgroup per product and norm) 74 and 268 us and two
+// copies to the host.
+constexpr int AR_T = 512;  // threads: 4 groups of 128 entries in sums, 8 waves in products
+constexpr int AR_G = 4;
+
+// entries of a workgroup's part (at most AR_EMAX, about 128 parts below that)
+constexpr int AR_EMAX = 1024;
+static int arnoldi_entries(int64_t n) {
+  const int64_t e = (n + 128 * 128 - 1) / (128 * 128) * 128;
+  return (int)(e < AR_EMAX ? e : AR_EMAX);
+}
+static int arnoldi_parts(int64_t n) { return (int)((n + arnoldi_entries(n) - 1) / arnoldi_entries(n)); }
+
+__device__ inline double2 wave_sum(double2 s) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    s.x += __shfl_xor(s.x, off);
+    s.y += __shfl_xor(s.y, off);
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) red[threadIdx.x] = cadd(red[threadIdx.x], red[threadIdx.x + off]);
+  return s;
+}
+__device__ inline double wave_sum(double s) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+  return s;
+}
+
+struct ArnoldiArgs {
+  const double2* V;     // basis, vector i of right-hand side r at V + i vs + r n
+  double2* W;           // the new vector (not scaled yet)
+  int64_t vs, n;
+  int m1, j1, E, C;     // rows of hp (restart + 1), basis vectors, entries per part, parts
+  const double2* hin;   // [nrhs][m1][C]: the products that W is to lose
+  double2* hout;        // [nrhs][m1][C]: products with the W formed here
+  double* np;           // [nrhs][C]: parts of ||W||^2
+  double2* host;        // [nrhs][m1] totals of hin, in host memory
+  // the coupling product (as in coupling_finish_kernel)
+  const double2 *part, *x, *q;
+  int nsplit;
+  int64_t stride, ncell3;
+  double2 self_c;
+};
+
+enum { AR_PRODUCT = 0, AR_AGAIN = 1, AR_NORM = 2 };
+
+// AR_PRODUCT: W = x - sum_s part[s] - S q, products with the basis
+// AR_AGAIN:   W -= sum_i h_i V_i, products with the basis
+// AR_NORM:    W -= sum_i h_i V_i, parts of the norm
+template <int MODE>
+__global__ void __launch_bounds__(AR_T) arnoldi_kernel(ArnoldiArgs A) {
+  extern __shared__ double2 ar_lds[];
+  double2* const wl = ar_lds;             // [E] this part of W
+  double2* const red = ar_lds + A.E;      // [AR_G][128]
+  double2* const h = red + AR_G * 128;    // [j1]
+  const int c = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int g = tid >> 7, l = tid & 127;
+  const int64_t k0 = (int64_t)c * A.E;
+  const int ne = (int)(A.n - k0 < A.E ? A.n - k0 : A.E);
+  const double2* const V = A.V + (int64_t)r * A.n + k0;
+  double2* const W = A.W + (int64_t)r * A.n + k0;
+  if constexpr (MODE != AR_PRODUCT) {
+    const double2* hi = A.hin + (int64_t)r * A.m1 * A.C;
+    for (int i = wave; i < A.j1; i += AR_T / 64) {
+      double2 s = make_double2(0, 0);
+      for (int b = lane; b < A.C; b += 64) s = cadd(s, hi[(int64_t)i * A.C + b]);
+      s = wave_sum(s);
+      if (lane == 0) {
+        h[i] = s;
+        if (c == 0) A.host[(int64_t)r * A.m1 + i] = s;
+      }
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) h[(int64_t)i * nrhs + r] = red[0];
+  // the sum over splits or basis vectors, a contiguous range of them per group of 128 threads
+  const int ns = MODE == AR_PRODUCT ? A.nsplit : A.j1;
+  const int per = (ns + AR_G - 1) / AR_G;
+  const int s0 = g * per < ns ? g * per : ns, s1 = s0 + per < ns ? s0 + per : ns;
+  double nn = 0;
+  for (int e0 = 0; e0 < ne; e0 += 128) {
+    const int e = e0 + l;
+    double2 s = make_double2(0, 0);
+    if (e < ne) {
+      if constexpr (MODE == AR_PRODUCT) {
+        const double2* p = A.part + (int64_t)r * A.n + k0 + e;
+#pragma unroll 8
+        for (int t = s0; t < s1; ++t) s = cadd(s, p[(int64_t)t * A.stride]);
+      } else {
+#pragma unroll 8
+        for (int t = s0; t < s1; ++t) cfma(s, h[t], V[(int64_t)t * A.vs + e]);
+      }
+    }
+    red[g * 128 + l] = s;
+    __syncthreads();
+    if (g == 0 && e < ne) {
+#pragma unroll
+      for (int t = 1; t < AR_G; ++t) s = cadd(s, red[t * 128 + l]);
+      double2 v;
+      if constexpr (MODE == AR_PRODUCT) {
+        const int64_t u = k0 + e;
+        v = csub(A.x[(int64_t)r * A.n + u], s);
+        if (u < A.ncell3) v = csub(v, cmul(A.self_c, A.q[(int64_t)r * A.n + u]));
+      } else {
+        v = csub(W[e], s);
+      }
+      W[e] = v;
+      if constexpr (MODE == AR_NORM) nn += v.x * v.x + v.y * v.y;
+      else wl[e] = v;
+    }
+    __syncthreads();
+  }
+  if constexpr (MODE == AR_NORM) {
+    double* const rn = reinterpret_cast<double*>(red);
+    nn = wave_sum(nn);
+    if (lane == 0 && wave < 2) rn[wave] = nn;
+    __syncthreads();
+    if (tid == 0) A.np[(int64_t)r * A.C + c] = rn[0] + rn[1];
+  } else {
+    // products: wave w takes the vectors w, w + 8, ..., four at a time
+    double2* ho = A.hout + (int64_t)r * A.m1 * A.C + c;
+    constexpr int NWV = AR_T / 64, U = 4;
+    for (int i0 = wave; i0 < A.j1; i0 += NWV * U) {
+      double2 s[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) s[u] = make_double2(0, 0);
+      for (int e = lane; e < ne; e += 64) {
+        const double2 b = wl[e];
+        double2 a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = i0 + NWV * u < A.j1 ? V[(int64_t)(i0 + NWV * u) * A.vs + e] : make_double2(0, 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          s[u].x += a[u].x * b.x + a[u].y * b.y;
+          s[u].y += a[u].x * b.y - a[u].y * b.x;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i0 + NWV * u >= A.j1) break;
+        const double2 t = wave_sum(s[u]);
+        if (lane == 0) ho[(int64_t)(i0 + NWV * u) * A.C] = t;
+      }
+    }
+  }
+}
+
+// V_0 = b - y (y null: b) and the parts of its norm
+__global__ void __launch_bounds__(AR_T) residual_kernel(const double2* __restrict__ b, const double2* __restrict__ y,
+                                                         double2* __restrict__ V0, int64_t n, int E, int C,
+                                                         double* __restrict__ np) {
+  __shared__ double red[AR_T / 64];
+  const int c = blockIdx.x;
+  const int64_t base = (int64_t)blockIdx.y * n;
+  const int64_t k1 = (int64_t)(c + 1) * E < n ? (int64_t)(c + 1) * E : n;
+  double s = 0;
+  for (int64_t k = (int64_t)c * E + threadIdx.x; k < k1; k += AR_T) {
+    double2 v = b[base + k];
+    if (y) v = csub(v, y[base + k]);
+    V0[base + k] = v;
+    s += v.x * v.x + v.y * v.y;
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < AR_T / 64; ++i) s += red[i];
+    np[(int64_t)blockIdx.y * C + c] = s;
+  }
+}
+
+// One wave per preconditioner block and right-hand side: v = v / ||v|| (0 if the
+// norm is 0), z = P v and the moments q = A z of the block's dipoles.
+__global__ void __launch_bounds__(64) scale_precond_kernel(DipoleView d, const double2* __restrict__ inv, int64_t n,
+                                                            const double* __restrict__ np, int C, double2* __restrict__ v,
+                                                            double2* __restrict__ z, double2* __restrict__ q,
+                                                            double* __restrict__ host) {
+  __shared__ double2 vl[PC_MAXD], zl[PC_MAXD];
+  const int64_t b = blockIdx.x;
+  const int64_t r = blockIdx.y;
+  const PcBlock p = pc_block(d, b);
+  const int tid = threadIdx.x;
+  const int64_t u = r * n + (tid < p.D ? pc_unknown(d, p, tid) : 0);
+  double2 x = make_double2(0, 0);
+  if (tid < p.D) x = v[u];
+  double s = 0;
+  for (int c = tid; c < C; c += 64) s += np[r * C + c];
+  const double nrm = sqrt(wave_sum(s));
+  if (b == 0 && tid == 0) host[r] = nrm;
+  const double f = nrm > 0 ? 1.0 / nrm : 0.0;
+  x = cscale(x, f);
+  if (tid < p.D) vl[tid] = x;
+  __syncthreads();
+  if (tid < p.D) {
+    v[u] = x;
+    const double2* A = inv + b * (int64_t)PC_MAXD * PC_MAXD + tid;
+    double2 t = make_double2(0, 0);
+#pragma unroll 12
+    for (int c = 0; c < p.D; ++c) cfma(t, A[(int64_t)c * PC_MAXD], vl[c]);
+    z[u] = t;
+    zl[tid] = t;
+  }
+  __syncthreads();
+  if (tid < p.D) {
+    const int slot = tid / 3, a = tid % 3;
+    const int ncell = p.nd - p.ne;
+    if (slot < ncell) {
+      q[u] = cmul(d.alpha_c[p.d0 + slot], zl[tid]);
+    } else {
+      const bool mag = slot >= p.nd;
+      const int e = mag ? slot - p.nd : slot - ncell;  // effective dipole of the block
+      const double2* al = d.alpha6 + (p.d0 + ncell + e - d.nc) * 36 + (a + (mag ? 3 : 0)) * 6;
+      double2 t = make_double2(0, 0);
+#pragma unroll
+      for (int c = 0; c < 6; ++c) cfma(t, al[c], zl[c < 3 ? 3 * (ncell + e) + c : 3 * (p.nd + e) + c - 3]);
+      q[u] = t;
+    }
+  }
 }
 
 // out[r][k] = beta out[r][k] + sgn sum_{i < m} c[i][r] V_i[r][k]
@@ -354,43 +557,10 @@ __global__ void mcomb_kernel(const double2* __restrict__ V, int64_t vs, const do
   out[idx] = make_double2(beta * o.x + sgn * s.x, beta * o.y + sgn * s.y);
 }
 
-// out[r] = ||w[r]||_2: one workgroup per r, fixed order
-__global__ void __launch_bounds__(256) norm_kernel(const double2* __restrict__ w, int64_t n, double* __restrict__ out) {
-  __shared__ double red[256];
-  const int r = blockIdx.x;
-  const double2* a = w + (int64_t)r * n;
-  double s = 0;
-  for (int64_t k = threadIdx.x; k < n; k += 256) s += a[k].x * a[k].x + a[k].y * a[k].y;
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[r] = sqrt(red[0]);
-}
-
-// v[r][k] = w[r][k] / s[r] (0 where s[r] = 0)
-__global__ void scale_kernel(const double2* __restrict__ w, const double* __restrict__ s, double2* __restrict__ v,
-                             int64_t n, int nrhs) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)nrhs * n) return;
-  const double sr = s[idx / n];
-  const double f = sr > 0 ? 1.0 / sr : 0.0;
-  v[idx] = cscale(w[idx], f);
-}
-
 // a[i] += b[i]
 __global__ void add_kernel(double2* __restrict__ a, const double2* __restrict__ b, int64_t count) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < count) a[idx] = cadd(a[idx], b[idx]);
-}
-
-// out[i] = a[i] - b[i]
-__global__ void sub_kernel(const double2* __restrict__ a, const double2* __restrict__ b, double2* __restrict__ out,
-                           int64_t count) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < count) out[idx] = csub(a[idx], b[idx]);
 }
 
 __global__ void zero_kernel(double2* __restrict__ a, int64_t count) {
@@ -432,11 +602,16 @@ void iter_workspace_carve(void* base, int64_t N, int64_t n, int64_t nrhs, int re
   w.V = reinterpret_cast<double2*>(take((size_t)(restart + 1) * vec));
   w.z = reinterpret_cast<double2*>(take(vec));
   w.q = reinterpret_cast<double2*>(take(vec));
-  w.t = reinterpret_cast<double2*>(take(vec));
+  // the parts of the scalar products (two passes) share the scratch vector, which
+  // is used between cycles only
+  w.E = arnoldi_entries(n);
+  w.C = arnoldi_parts(n);
+  const size_t hp = (size_t)nrhs * (restart + 1) * w.C * sizeof(double2);
+  w.t = reinterpret_cast<double2*>(take(std::max(vec, 2 * hp)));
+  w.hp = w.t;
   w.part = reinterpret_cast<double2*>(take((size_t)w.nsplit * vec));
   w.inv = reinterpret_cast<double2*>(take((size_t)w.nblk * PC_MAXD * PC_MAXD * sizeof(double2)));
-  w.h = reinterpret_cast<double2*>(take(2 * (size_t)(restart + 1) * nrhs * sizeof(double2)));
-  w.nrm = reinterpret_cast<double*>(take(2 * (size_t)nrhs * sizeof(double)));
+  w.np = reinterpret_cast<double*>(take((size_t)nrhs * w.C * sizeof(double)));
   w.y = reinterpret_cast<double2*>(take((size_t)(restart + 1) * nrhs * sizeof(double2)));
   w.bytes = off + 256;
 }
@@ -446,11 +621,9 @@ hipError_t launch_precond_build(const DipoleView& d, const Wave& w, const IterWo
   return hipGetLastError();
 }
 
-// y = M x for nrhs vectors (x, y: [nrhs][n]; y may not alias x)
-hipError_t launch_matvec(const DipoleView& d, const Wave& w, const IterWork& iw, int64_t n, int64_t nrhs,
-                         const double2* x, double2* y, hipStream_t st) {
-  hipError_t e = launch_apply_alpha(d, x, n, iw.q, n, nrhs, st);
-  if (e != hipSuccess) return e;
+// the partial coupling sums of the moments iw.q into iw.part
+static hipError_t launch_coupling(const DipoleView& d, const Wave& w, const IterWork& iw, int64_t n, int64_t nrhs,
+                                  hipStream_t st) {
   const int64_t jps = ((d.N + iw.nsplit - 1) / iw.nsplit + 31) / 32 * 32;
   const dim3 grid((unsigned)((d.N + 255) / 256), (unsigned)iw.nsplit);
   for (int r0 = 0; r0 < nrhs; r0 += 2) {
@@ -459,6 +632,15 @@ hipError_t launch_matvec(const DipoleView& d, const Wave& w, const IterWork& iw,
     else
       hipLaunchKernelGGL(coupling_kernel<1>, grid, dim3(256), 0, st, d, w, iw.q, n, nrhs, r0, jps, iw.part);
   }
+  return hipGetLastError();
+}
+
+// y = M x for nrhs vectors (x, y: [nrhs][n]; y may not alias x)
+hipError_t launch_matvec(const DipoleView& d, const Wave& w, const IterWork& iw, int64_t n, int64_t nrhs,
+                         const double2* x, double2* y, hipStream_t st) {
+  hipError_t e = launch_apply_alpha(d, x, n, iw.q, n, nrhs, st);
+  if (e != hipSuccess) return e;
+  if ((e = launch_coupling(d, w, iw, n, nrhs, st)) != hipSuccess) return e;
   const int64_t count = nrhs * n;
   hipLaunchKernelGGL(coupling_finish_kernel, dim3(nblocks(count)), dim3(256), 0, st, iw.part, iw.nsplit, count, x,
                      iw.q, d.self_c, 3 * d.nc, n, y, count);
@@ -472,9 +654,13 @@ hipError_t launch_precond_apply(const DipoleView& d, const IterWork& iw, int64_t
   return hipGetLastError();
 }
 
+size_t gmres_host_bytes(int64_t nrhs, int restart) {
+  return (size_t)nrhs * (2 * (restart + 1) * sizeof(double2) + sizeof(double));
+}
+
 hipError_t gmres_solve(const DipoleView& d, const Wave& w, const IterWork& iw, int64_t n, int64_t nrhs,
                        const double2* B, double2* X, double tol, int max_iter, int restart, hipStream_t st,
-                       GmresStats& gs, Prof* prof) {
+                       GmresStats& gs, void* host, Prof* prof) {
   typedef std::complex<double> cd;
   hipError_t e;
 #define GCHK(x)                        \
@@ -486,12 +672,35 @@ hipError_t gmres_solve(const DipoleView& d, const Wave& w, const IterWork& iw, i
   const int m = restart;
   gs = GmresStats{};
   GCHK(launch_precond_build(d, w, iw, st));
-  // ||b|| per column
-  std::vector<double> bn(nrhs), rn(nrhs), hbuf;
-  hipLaunchKernelGGL(norm_kernel, dim3((unsigned)nrhs), dim3(256), 0, st, B, n, iw.nrm);
-  GCHK(hipMemcpyAsync(bn.data(), iw.nrm, sizeof(double) * nrhs, hipMemcpyDeviceToHost, st));
-  GCHK(hipStreamSynchronize(st));
   hipLaunchKernelGGL(zero_kernel, dim3(nblocks(count)), dim3(256), 0, st, X, count);
+  // scalar results, which the kernels write to host memory: products of both
+  // passes [2][nrhs][m + 1], then norms [nrhs]
+  const double2* const hh = static_cast<const double2*>(host);
+  double2* const hdev = static_cast<double2*>(host);
+  const int64_t hs = nrhs * (m + 1);
+  const double* const hn = reinterpret_cast<const double*>(hh + 2 * hs);
+  double* const ndev = reinterpret_cast<double*>(hdev + 2 * hs);
+  struct Event {
+    hipEvent_t e = nullptr;
+    ~Event() {
+      if (e) (void)hipEventDestroy(e);
+    }
+  } ready;
+  GCHK(hipEventCreateWithFlags(&ready.e, hipEventDisableTiming));
+  const dim3 agrid((unsigned)iw.C, (unsigned)nrhs);
+  auto scale_precond = [&](double2* v) -> hipError_t {  // v / ||v||, z, q; the norm to the host
+    hipLaunchKernelGGL(scale_precond_kernel, dim3((unsigned)iw.nblk, (unsigned)nrhs), dim3(64), 0, st, d, iw.inv, n, iw.np,
+                       iw.C, v, iw.z, iw.q, ndev);
+    hipError_t r = hipGetLastError();
+    return r != hipSuccess ? r : hipEventRecord(ready.e, st);
+  };
+  auto coupling = [&]() -> hipError_t {
+    hipError_t r;
+    if (prof && (r = prof->begin(st, PROF_ITER_MATVEC, (double)d.N * (double)d.N * (double)nrhs)) != hipSuccess) return r;
+    if ((r = launch_coupling(d, w, iw, n, nrhs, st)) != hipSuccess) return r;
+    return prof ? prof->end(st) : hipSuccess;
+  };
+  std::vector<double> bn(nrhs), rn(nrhs);
   std::vector<std::vector<cd>> H(nrhs), G(nrhs);
   std::vector<std::vector<cd>> cs(nrhs), sn(nrhs);
   std::vector<double> relres(nrhs, 1.0);
@@ -499,18 +708,17 @@ hipError_t gmres_solve(const DipoleView& d, const Wave& w, const IterWork& iw, i
   while (true) {
     // r = b - M x (x = 0 at the start: r = b), V_0 = r / ||r||
     double2* V0 = iw.V;
-    if (first) {
-      GCHK(hipMemcpyAsync(V0, B, sizeof(double2) * count, hipMemcpyDeviceToDevice, st));
-    } else {
+    if (!first) {
       if (prof) GCHK(prof->begin(st, PROF_ITER_MATVEC, (double)d.N * (double)d.N * (double)nrhs));
       GCHK(launch_matvec(d, w, iw, n, nrhs, X, iw.t, st));
       if (prof) GCHK(prof->end(st));
-      hipLaunchKernelGGL(sub_kernel, dim3(nblocks(count)), dim3(256), 0, st, B, iw.t, V0, count);  // V0 = b - M x
     }
+    hipLaunchKernelGGL(residual_kernel, agrid, dim3(AR_T), 0, st, B, first ? nullptr : iw.t, V0, n, iw.E, iw.C, iw.np);
+    GCHK(scale_precond(V0));
+    GCHK(hipEventSynchronize(ready.e));
+    std::copy(hn, hn + nrhs, rn.begin());
+    if (first) bn = rn;
     first = false;
-    hipLaunchKernelGGL(norm_kernel, dim3((unsigned)nrhs), dim3(256), 0, st, V0, n, iw.nrm);
-    GCHK(hipMemcpyAsync(rn.data(), iw.nrm, sizeof(double) * nrhs, hipMemcpyDeviceToHost, st));
-    GCHK(hipStreamSynchronize(st));
     bool done = true;
     for (int64_t r = 0; r < nrhs; ++r) {
       relres[r] = bn[r] > 0 ? rn[r] / bn[r] : 0.0;
@@ -518,7 +726,6 @@ hipError_t gmres_solve(const DipoleView& d, const Wave& w, const IterWork& iw, i
     }
     gs.relres = *std::max_element(relres.begin(), relres.end());
     if (done || gs.iters >= max_iter) break;
-    hipLaunchKernelGGL(scale_kernel, dim3(nblocks(count)), dim3(256), 0, st, V0, iw.nrm, V0, n, (int)nrhs);
     for (int64_t r = 0; r < nrhs; ++r) {
       H[r].assign((size_t)(m + 1) * m, cd(0, 0));
       G[r].assign(m + 1, cd(0, 0));
@@ -526,41 +733,60 @@ hipError_t gmres_solve(const DipoleView& d, const Wave& w, const IterWork& iw, i
       cs[r].assign(m, cd(0, 0));
       sn[r].assign(m, cd(0, 0));
     }
+    GCHK(coupling());
     int jdone = 0;
+    double res_prev = gs.relres, res_now = gs.relres;  // largest residual after the last two steps
     for (int j = 0; j < m && gs.iters < max_iter; ++j) {
-      double2* Vj = iw.V + j * vs;
-      double2* W = iw.V + (j + 1) * vs;
-      // W = M P V_j
-      GCHK(launch_precond_apply(d, iw, n, nrhs, Vj, iw.z, st));
-      if (prof) GCHK(prof->begin(st, PROF_ITER_MATVEC, (double)d.N * (double)d.N * (double)nrhs));
-      GCHK(launch_matvec(d, w, iw, n, nrhs, iw.z, W, st));
-      if (prof) GCHK(prof->end(st));
-      // classical Gram-Schmidt, twice: h = V^H W, W -= V h
-      for (int pass = 0; pass < 2; ++pass) {
-        double2* hp = iw.h + (size_t)pass * (m + 1) * nrhs;
-        hipLaunchKernelGGL(mdot_kernel, dim3((unsigned)(j + 1), (unsigned)nrhs), dim3(256), 0, st, iw.V, vs, W, n,
-                           (int)nrhs, hp);
-        hipLaunchKernelGGL(mcomb_kernel, dim3(nblocks(count)), dim3(256), 0, st, iw.V, vs, hp, j + 1, -1.0, 1.0, W,
-                           n, (int)nrhs);
-      }
-      hipLaunchKernelGGL(norm_kernel, dim3((unsigned)nrhs), dim3(256), 0, st, W, n, iw.nrm);
-      hipLaunchKernelGGL(scale_kernel, dim3(nblocks(count)), dim3(256), 0, st, W, iw.nrm, W, n, (int)nrhs);
-      hbuf.resize(2 * (size_t)(m + 1) * nrhs * 2 + nrhs);
-      GCHK(hipMemcpyAsync(hbuf.data(), iw.h, sizeof(double2) * 2 * (m + 1) * nrhs, hipMemcpyDeviceToHost, st));
-      GCHK(hipMemcpyAsync(hbuf.data() + 4 * (size_t)(m + 1) * nrhs, iw.nrm, sizeof(double) * nrhs,
-                          hipMemcpyDeviceToHost, st));
-      GCHK(hipStreamSynchronize(st));
+      // W = M P V_j; classical Gram-Schmidt, twice: h = V^H W, W -= V h
+      ArnoldiArgs A;
+      A.V = iw.V;
+      A.W = iw.V + (j + 1) * vs;
+      A.vs = vs;
+      A.n = n;
+      A.m1 = m + 1;
+      A.j1 = j + 1;
+      A.E = iw.E;
+      A.C = iw.C;
+      A.hin = nullptr;
+      A.hout = iw.hp;
+      A.np = iw.np;
+      A.host = nullptr;
+      A.part = iw.part;
+      A.x = iw.z;
+      A.q = iw.q;
+      A.nsplit = iw.nsplit;
+      A.stride = count;
+      A.ncell3 = 3 * d.nc;
+      A.self_c = d.self_c;
+      const size_t lds = sizeof(double2) * (size_t)(iw.E + AR_G * 128 + j + 1);
+      hipLaunchKernelGGL(arnoldi_kernel<AR_PRODUCT>, agrid, dim3(AR_T), lds, st, A);
+      A.hin = iw.hp;
+      A.hout = iw.hp + hs * iw.C;
+      A.host = hdev;
+      hipLaunchKernelGGL(arnoldi_kernel<AR_AGAIN>, agrid, dim3(AR_T), lds, st, A);
+      A.hin = A.hout;
+      A.hout = nullptr;
+      A.host = hdev + hs;
+      hipLaunchKernelGGL(arnoldi_kernel<AR_NORM>, agrid, dim3(AR_T), lds, st, A);
+      GCHK(scale_precond(A.W));
+      // the next product starts while the host works on this step, unless the
+      // residual, falling as in the last step, would then have converged
+      const bool more = j + 1 < m && gs.iters + 1 < max_iter;
+      const bool ahead = more && res_now * res_now > 0.5 * tol * res_prev;
+      if (ahead) GCHK(coupling());
+      GCHK(hipEventSynchronize(ready.e));
       ++gs.iters;
       jdone = j + 1;
       bool all = true;
+      double res = 0.0;
       for (int64_t r = 0; r < nrhs; ++r) {
         // Hessenberg column j: h of both passes, then ||W||
         std::vector<cd> col(j + 2);
         for (int i = 0; i <= j; ++i) {
-          const size_t a = 2 * ((size_t)i * nrhs + r), b2 = 2 * ((size_t)(m + 1) * nrhs + (size_t)i * nrhs + r);
-          col[i] = cd(hbuf[a] + hbuf[b2], hbuf[a + 1] + hbuf[b2 + 1]);
+          const double2 h1 = hh[r * (m + 1) + i], h2 = hh[hs + r * (m + 1) + i];
+          col[i] = cd(h1.x + h2.x, h1.y + h2.y);
         }
-        col[j + 1] = cd(hbuf[4 * (size_t)(m + 1) * nrhs + r], 0);
+        col[j + 1] = cd(hn[r], 0);
         // earlier rotations
         for (int i = 0; i < j; ++i) {
           const cd t0 = cs[r][i] * col[i] + sn[r][i] * col[i + 1];
@@ -586,9 +812,13 @@ hipError_t gmres_solve(const DipoleView& d, const Wave& w, const IterWork& iw, i
         G[r][j] = cs[r][j] * g0;
         G[r][j + 1] = -std::conj(sn[r][j]) * g0;
         relres[r] = bn[r] > 0 ? std::abs(G[r][j + 1]) / bn[r] : 0.0;
+        res = std::max(res, relres[r]);
         all = all && relres[r] <= 0.5 * tol;
       }
       if (all) break;
+      res_prev = res_now;
+      res_now = res;
+      if (more && !ahead) GCHK(coupling());
     }
     // y = H^-1 g (upper triangular, jdone x jdone), then x += P V y
     std::vector<double2> yh((size_t)(m + 1) * nrhs, make_double2(0, 0));

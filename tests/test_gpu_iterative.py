@@ -162,3 +162,42 @@ def test_iterative_stops_at_max_iter_with_noconv(ctx):
     with pytest.raises(gdm.GDMError) as ei:
         ctx.solve_iterative(w["wavelength"], f0, restart=5000)
     assert ei.value.status == gdm.GDM_E_ARG
+
+
+@pytest.mark.parametrize("cells,eff,nrhs,restart", [(1, 0, 1, 1), (43, 0, 2, 7), (44, 0, 3, 9), (0, 8, 1, 30), (0, 9, 4, 2),
+                                                    (81, 20, 2, 33), (300, 60, 1, 70)])
+def test_arnoldi_step_edges(ctx, cells, eff, nrhs, restart):
+    """Parts of 128 unknowns, blocks of 8 dipoles, more basis vectors than a wave's
+    four: the solution of the same system in LAPACK.  A residual of 1e-12 and
+    a condition below 10^2: 1e-10."""
+    rng = np.random.default_rng(cells + eff)
+    r = gi.cuboid_cells(7, 7, (cells + 48) // 49, 6.0)[:cells] if cells else np.zeros((0, 3))
+    re = np.stack([60.0 + 70.0 * np.arange(eff), 20.0 * (np.arange(eff) % 2), 15.0 * (np.arange(eff) % 3)], 1)
+    w = dict(r_cell=r, step=6.0, eps_cell=np.full(cells, 4.0 + 0.3j), n_env=1.1, wavelength=610.0, r_eff=re,
+             alpha_eff=gi.mie_like_alpha6(rng, eff, 610.0, 1.1))
+    D = O.Dipoles(dict(w, r_probe=np.zeros((0, 3))))
+    ctx.set_environment(1.1)
+    ctx.set_structure(r, 6.0, w["eps_cell"], re if eff else None, w["alpha_eff"] if eff else None)
+    f0 = rng.standard_normal((nrhs, ctx.n)) + 1j * rng.standard_normal((nrhs, ctx.n))
+    _, f = ctx.solve_iterative(610.0, torch.as_tensor(f0), tol=1e-12, restart=restart, max_iter=3000)
+    assert relcol(f.cpu().numpy(), np.linalg.solve(O.assemble(D), f0.T).T) <= 1e-10
+
+
+def test_arnoldi_parts_at_their_largest(ctx):
+    """n = 133 200: parts of 1024 unknowns, more than 128 of them.  Rows of the
+    residual against the oracle's sums, by the reported residual norm."""
+    m = 149
+    rng = np.random.default_rng(5)
+    re = np.stack(np.meshgrid(np.arange(m), np.arange(m), indexing="ij"), -1).reshape(-1, 2)[:22200]
+    re = np.concatenate([500.0 * re, 0.0 * re[:, :1]], 1)
+    w = dict(r_cell=np.zeros((0, 3)), step=6.0, eps_cell=np.zeros(0, complex), n_env=1.0, wavelength=610.0, r_eff=re,
+             alpha_eff=0.02 * gi.mie_like_alpha6(rng, len(re), 610.0, 1.0), r_probe=np.zeros((0, 3)))
+    D = O.Dipoles(w)
+    ctx.set_environment(1.0)
+    ctx.set_structure(w["r_cell"], 6.0, w["eps_cell"], re, w["alpha_eff"])
+    f0 = rng.standard_normal((1, ctx.n)) + 1j * rng.standard_normal((1, ctx.n))
+    _, f = ctx.solve_iterative(610.0, torch.as_tensor(f0), tol=1e-10, restart=20, max_iter=40)
+    rows = np.array([0, 3 * 11000 + 1, ctx.n // 2 - 1, ctx.n // 2, ctx.n - 1])
+    got, scale = O.matvec_rows(D, rows, f[0].cpu().numpy())
+    bound = ctx.info.backward_err * np.linalg.norm(f0) * 1.01 + 1e-12 * (scale + np.abs(f0[0, rows]))
+    assert ctx.info.backward_err <= 1e-10 and np.all(np.abs(got - f0[0, rows]) <= bound)
