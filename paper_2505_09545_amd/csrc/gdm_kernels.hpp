@@ -154,6 +154,14 @@ hipError_t launch_gemm_update(int64_t m, int64_t n, int64_t k, const void* A, in
                               int64_t ldb, void* C, int64_t ldc, hipStream_t st, int nbatch = 1, int64_t sA = 0,
                               int64_t sB = 0, int64_t sC = 0);
 
+// Block step of the triangular solves with more than SKINNY_MAX_RHS right-hand
+// sides (solve_step.hip): C[m x nrhs] -= A[m x k] X[k x nrhs], k <= 128, with the
+// triangle mask (akind) and the second destination of GemmMask.
+template <typename T>
+hipError_t launch_solve_step(int64_t m, int64_t k, const void* A, int64_t lda, const void* X, int64_t ldx, void* C,
+                             int64_t ldc, int64_t nrhs, hipStream_t st, GemmMask mk = GemmMask{}, int nbatch = 1,
+                             int64_t sA = 0, int64_t sX = 0, int64_t sC = 0);
+
 // Small-RHS block steps of the triangular solves (solve_small.hip).  All take
 // an optional batch of nbatch independent items (item z: A + z sA, X/B + z sX/sB,
 // C + z sC; partial-sum buffers must hold nbatch times the per-item need).

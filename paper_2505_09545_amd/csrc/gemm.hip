@@ -19,16 +19,12 @@
 //     (the bulk of the trailing update, the FP64 residual), 4 complex k per
 //     stage for one system's products, 8 for batched launches;
 //   32 x 32 x 8 (WM 2, WN 1) for launches of fewer than two 64 x 64 tiles per
-//     CU (look-ahead update, U12 blocks, solve steps): four times the
-//     workgroups, for products whose time is set by latency rather than by the
-//     matrix cores.  Measured on the 66-RHS solves: 8 complex k per stage
-//     11.6 ms, 16: 12.4, 32: 14.7, 64: 17.6 (the smaller stage leaves more
-//     workgroups resident per CU); wider tiles over all 66 columns: 16.5.
+//     CU: four times the workgroups, for products whose time is set by latency
+//     rather than by the matrix cores.
 //     One system's products over 64 <= k <= 128 (16 complex k per stage)
 //     load their whole k range into registers before the first stage, so a
-//     launch waits for memory once instead of once per stage (FP32+IR step
-//     72.6 -> 72.0 ms; FP64 takes it in two halves of 64, whose registers
-//     would otherwise spill).
+//     launch waits for memory once instead of once per stage (FP64 takes it in
+//     two halves of 64, whose registers would otherwise spill).
 // Per thread and stage the big tile loads one (4 k) or two (8 k) complex
 // elements of A and as many of B, the small one one of each.
 // Workgroups are remapped so that each of the 8 XCDs works on a contiguous
@@ -562,10 +558,9 @@ static hipError_t launch_cfg(int64_t m, int64_t n, int64_t k, const cplx<T>* a, 
                              int64_t ldb, cplx<T>* c, int64_t ldc, hipStream_t st, GemmMask mk, int nbatch, int64_t sA,
                              int64_t sB, int64_t sC) {
   if (use_small_tiles(m, n, nbatch)) {
-    // one system's products over k >= 64 (the solve steps, L21 and U12 blocks,
-    // the look-ahead columns) with 16 complex k per stage: half the stages of
-    // their latency-bound k loop (FP32+IR step 72.9 -> 72.2 ms; 32 measured
-    // the same); the batched launches keep 8
+    // one system's products over k >= 64 with 16 complex k per stage: half the
+    // stages of their latency-bound k loop (32 measured the same); the batched
+    // launches keep 8
     if (nbatch == 1 && k >= 64 && k <= 128 && GEMM_SMALL_PREFETCH)
       return launch_tiles<T, MODE, TRANSA, ROLE, 2, 1, 16, sizeof(T) == 8 ? 4 : 8>(m, n, k, a, lda, b, ldb, c, ldc, st,
                                                                                 mk, nbatch, sA, sB, sC);
@@ -649,6 +644,10 @@ hipError_t launch_gemm_update(int64_t m, int64_t n, int64_t k, const void* A, in
   if (GEMM_UPDATE_3M && !use_small_tiles(m, n, nbatch))
     return launch_update_3m<T>(m, n, k, static_cast<const cplx<T>*>(A), lda, static_cast<const cplx<T>*>(B), ldb,
                                static_cast<cplx<T>*>(C), ldc, st, nbatch, sA, sB, sC);
+  // below the 64 x 64 tiles' range (look-ahead columns, small matrices): 16 x 32
+  // tiles without LDS staging (FP64, 128 columns, m = 3600 on average: 19.5 us; the
+  // 32 x 32 tiles 22.7)
+  if (nbatch == 1 && k <= 128) return launch_solve_step<T>(m, k, A, lda, B, ldb, C, ldc, n, st);
   return launch_cfg<T, 0, 0, 1>(m, n, k, static_cast<const cplx<T>*>(A), lda, static_cast<const cplx<T>*>(B), ldb,
                                 static_cast<cplx<T>*>(C), ldc, st, GemmMask{}, nbatch, sA, sB, sC);
 }

@@ -1615,8 +1615,8 @@ hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, c
         m.sc2 = sX;
         e = small ? launch_skinny_n<T>(n - k0, b.w, A + k0 + k0 * ld, ld, B + k0, ldb, B + k0, ldb, nr, st, m, NB, sA,
                                        sB, sB)
-                  : launch_gemm<T>(0, 0, n - k0, nr, b.w, A + k0 + k0 * ld, ld, B + k0, ldb, B + k0, ldb, st, m, NB,
-                                   sA, sB, sB);
+                  : launch_solve_step<T>(n - k0, b.w, A + k0 + k0 * ld, ld, B + k0, ldb, B + k0, ldb, nr, st, m, NB, sA,
+                                         sB, sB);
         if (e != hipSuccess) return e;
       }
       // backward on Y: rows [0, k0 + w) -= [U01 U11^-1 ; I - U11^-1] Y_b, rows [k0, k0 + w) into B
@@ -1631,7 +1631,7 @@ hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, c
         m.ldc2 = ldb;
         m.sc2 = sB;
         e = small ? launch_skinny_n<T>(k0 + b.w, b.w, A + k0 * ld, ld, Y + k0, n, Y, n, nr, st, m, NB, sA, sX, sX)
-                  : launch_gemm<T>(0, 0, k0 + b.w, nr, b.w, A + k0 * ld, ld, Y + k0, n, Y, n, st, m, NB, sA, sX, sX);
+                  : launch_solve_step<T>(k0 + b.w, b.w, A + k0 * ld, ld, Y + k0, n, Y, n, nr, st, m, NB, sA, sX, sX);
         if (e != hipSuccess) return e;
       }
     } else {

@@ -85,3 +85,23 @@ def test_getrf_fp32_column_scales(ctx):
     ref = np.linalg.solve(A, B.T).T
     err = np.linalg.norm(X.cpu().numpy() * D[None, :] - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= 8 * n * 1.2e-7, err
+
+
+@pytest.mark.parametrize("dtype,n,nrhs", [(d, n, r) for d in (torch.complex64, torch.complex128)
+                                          for n, r in ((5, 9), (16, 16), (64, 17), (65, 33), (127, 32), (129, 66), (300, 40),
+                                                       (700, 9), (700, 131))])
+def test_solve_step_edges(ctx, dtype, n, nrhs):
+    """Block steps of the solves with more than eight right-hand sides at the edges
+    of their 16-row and 32-column tiles, k of 64 and below; the bound of
+    test_getrf_fp32_column_scales in each precision."""
+    eps = 1.2e-7 if dtype == torch.complex64 else 2.3e-16
+    rng = np.random.default_rng(n + nrhs)
+    A = 2 * np.eye(n) + (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(2 * n)
+    B = rng.standard_normal((nrhs, n)) + 1j * rng.standard_normal((nrhs, n))
+    F = torch.as_tensor(A.T.copy()).to(device="cuda", dtype=dtype).contiguous()
+    X = torch.as_tensor(B).to(device="cuda", dtype=dtype).contiguous()
+    ctx.getrf(F)
+    ctx.getrs(F, X, 0)
+    ref = np.linalg.solve(A, B.T).T
+    err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 8 * max(n, 16) * eps, err
