@@ -242,6 +242,8 @@ struct LUPlan {
   int nb = 0;
   int max_wg = 0;  // number of CUs: upper bound on panel workgroups
   int pb = 1;      // panel columns per pivot exchange (1: partial pivoting; 2, 4, 8: tournament)
+  int nbatch = 1;         // systems factored together
+  int64_t lds_bytes = 0;  // LDS of a CU
   bool spec = false;  // speculative panels (diagonal pivots checked against partial pivoting; pb = 1 plan)
   std::vector<LUBlock> blocks;
 };

@@ -7,7 +7,7 @@
 //   1. panel: factor A[k0:n, k0:k0+w] with partial pivoting (pivot = largest
 //      |re|+|im| in the column, lowest row on ties).  One cooperative launch of
 //      G workgroups; each holds R rows of the panel in LDS and the workgroups
-//      agree on every pivot through one device-wide barrier per column.
+//      agree on every pivot through one device-wide exchange per column.
 //   2. the panel also lists the block's net row permutation (<= 2w rows move,
 //      read off the row labels), which is applied to the trailing columns and,
 //      in the solve, to the right-hand sides.  Interchanges are never applied
@@ -462,6 +462,340 @@ __global__ void __launch_bounds__(256) panel_kernel(cplx<T>* __restrict__ A, int
       for (int u = 0; u < LB; ++u) dst[(c0 + u) * ld] = v[u];
     }
     for (int c = wfull; c < w; ++c) dst[c * ld] = tile[c * R + lr];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 1a. the same panel with the column loop in one wave (at most 64 rows per workgroup)
+// ---------------------------------------------------------------------------
+// The panel is taken in sub-panels of SUBW columns.  Wave 0 runs a sub-panel's
+// columns by itself, one row per lane with its SUBW entries in registers, so a
+// column has no barrier: choice of the candidate (DPP), its key, then its row
+// and the reciprocal of its pivot published; the other workgroups' keys; the
+// winner's row, which goes through LDS to every lane; multipliers and the rank-1
+// update of at most SUBW - 1 columns.  The remaining columns of the panel are
+// updated once per sub-panel, by all four waves: the owners publish the pivot
+// rows' entries there, every workgroup subtracts L11 times the earlier U rows (one
+// column per thread), then the rank-SUBW update goes to the matrix cores.
+// What bounds it is the chain of a column: the key's trip through memory to
+// workgroups on other dies (0.75 us of waiting behind the rank-1 update that it
+// overlaps), the load of the winner's row (0.4) and the choice of the next
+// candidate (0.35).  n = 3001: 2.6 us per column in FP32, 2.9 in FP64; panel_kernel,
+// with three barriers per column and all remaining columns updated from LDS, 2.9
+// and 5.1.  (Any 24 to 56 rows per workgroup measure the same.)
+//
+// Exchange buffers: keys as in panel_kernel; rows [2][gitem][SUBW NW] words, the
+// record of a workgroup's candidate: multipliers of the sub-panel's columns before
+// j, the reciprocal of the pivot in place of column j, the columns after it; then the pivot
+// rows' remaining columns [2][SUBW][wwmax], double-buffered by the parity of the
+// sub-panel (an owner writes a slot again after the keys of a whole sub-panel,
+// which every workgroup publishes after it has read the slot).
+constexpr int SUBW = 16;
+// words between two workgroups' keys: 4 workgroups to a 128-byte line (a line each: 12.0
+// instead of 11.7 ms for n = 3001 in FP64, since every workgroup reads them all)
+constexpr int PW_KEYS = 4;
+
+template <typename CT>
+static __host__ __device__ inline size_t panel_wave_lds(int w, int R) {
+  const int rest = w > SUBW ? w - SUBW : 0;
+  return ((size_t)w * R + (size_t)SUBW * rest + SUBW * (SUBW + 1) + 64) * sizeof(CT) + (size_t)(R + w + SUBW) * 4;
+}
+
+__device__ inline uint32_t wave_max_u32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, false));  // row_half_mirror
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xf, 0xf, false));  // row_mirror
+  const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+  return max(max(a, b), max(c, d));
+}
+// The largest key of the wave and a lane that holds it (-1 if it is 0): the upper
+// words first, the lower ones only if they tie.
+__device__ inline u64 wave_argmax(u64 key, int& src) {
+  const uint32_t hi = wave_max_u32((uint32_t)(key >> 32));
+  unsigned long long who = __ballot((uint32_t)(key >> 32) == hi);
+  if (__builtin_popcountll(who) != 1) {
+    const uint32_t lo = wave_max_u32((uint32_t)(key >> 32) == hi ? (uint32_t)key : 0u);
+    who = __ballot((uint32_t)(key >> 32) == hi && (uint32_t)key == lo);
+  }
+  const int l = (int)__builtin_ctzll(who);
+  const u64 k = ((u64)hi << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, l);
+  src = k ? l : -1;
+  return k;
+}
+
+// the keys of all workgroups, KPL per lane: the winner's key and workgroup
+template <int KPL>
+__device__ inline u64 gather_keys(const u64* cand, int G, uint32_t E, int lane, int& gp, int* bad) {
+  const u64* pk[2 * KPL];
+  uint32_t v[2 * KPL];
+#pragma unroll
+  for (int i = 0; i < KPL; ++i) {
+    const int g = lane + 64 * i < G ? lane + 64 * i : lane % G;
+    pk[2 * i] = cand + PW_KEYS * g;
+    pk[2 * i + 1] = pk[2 * i] + 1;
+  }
+  ll_get_n<2 * KPL>(pk, E, v, bad);
+  u64 best = 0;
+  int bg = 0;
+#pragma unroll
+  for (int i = 0; i < KPL; ++i) {
+    const u64 k = ((u64)v[2 * i] << 32) | (0xffffffffu - v[2 * i + 1]);
+    if (k > best) {
+      best = k;
+      bg = lane + 64 * i < G ? lane + 64 * i : lane % G;
+    }
+  }
+  int src;
+  const u64 k = wave_argmax(best, src);
+  gp = src >= 0 ? __builtin_amdgcn_readlane(bg, src) : -1;
+  return k;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) panel_wave_kernel(cplx<T>* __restrict__ A, int64_t ld, int64_t n, int64_t k0, int w,
+                                                          int R, int G, int32_t* __restrict__ ipiv, LUWork ws,
+                                                          uint32_t epoch0, int32_t* __restrict__ mdst,
+                                                          int32_t* __restrict__ msrc, int32_t* __restrict__ mcount, int mcap) {
+  using CT = cplx<T>;
+  constexpr int NW = sizeof(CT) / 4, RW = SUBW * NW;  // words per complex, per record
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int restmax = w > SUBW ? w - SUBW : 0;
+  CT* tile = reinterpret_cast<CT*>(smem_raw);              // [w][R]
+  CT* ub = tile + (size_t)w * R;                           // [SUBW][restmax] pivot rows, then U, right of the sub-panel
+  CT* lp = ub + (size_t)SUBW * restmax;                    // [SUBW][SUBW] the pivot rows' records, SUBW unused
+  CT* spare = lp + SUBW * (SUBW + 1);                      // [64] takes the stores past a sub-panel's last column
+  int32_t* lab = reinterpret_cast<int32_t*>(spare + 64);   // [R] row labels (final positions)
+  int32_t* pl = lab + R;                                   // [w] pivot positions
+  int32_t* mine = pl + w;                                  // [SUBW] local row of the sub-panel's pivot, or -1
+  __shared__ int bad;
+  const int g = blockIdx.x, tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t rbase = k0 + (int64_t)g * R;
+  const int myR = (int)(n - rbase < (int64_t)R ? (n - rbase > 0 ? n - rbase : 0) : R);
+  if (tid == 0) bad = 0;
+  // a wave's lanes are rows; columns dealt to the waves, LB loads in flight
+  constexpr int LB = 128 / (int)sizeof(CT);
+  if (lane < myR) {
+    const CT* src = A + rbase + lane + k0 * ld;
+    for (int c0 = wave; c0 < w; c0 += 4 * LB) {
+      CT v[LB];
+#pragma unroll
+      for (int u = 0; u < LB; ++u) v[u] = src[(int64_t)(c0 + 4 * u < w ? c0 + 4 * u : w - 1) * ld];
+#pragma unroll
+      for (int u = 0; u < LB; ++u)
+        if (c0 + 4 * u < w) tile[(c0 + 4 * u) * R + lane] = v[u];
+    }
+  }
+  if (tid < myR) lab[tid] = (int32_t)(rbase + tid);
+  __syncthreads();
+  int zero_col = -1;  // wave 0
+  u64* const ubase = ws.rows + 2 * (size_t)ws.gitem * RW;
+  for (int s0 = 0, sp = 0; s0 < w; s0 += SUBW, sp ^= 1) {
+    const int sw = w - s0 < SUBW ? w - s0 : SUBW;
+    if (wave == 0) {
+      int32_t mylab = lane < myR ? lab[lane] : -1;
+      if (lane < SUBW) mine[lane] = -1;
+      CT x[SUBW];  // this row's columns j, j + 1, ... (shifted along with j)
+#pragma unroll
+      for (int c = 0; c < SUBW; ++c) {
+        x[c].x = x[c].y = 0;
+        if (lane < myR && c < sw) x[c] = tile[(s0 + c) * R + lane];
+      }
+      // this workgroup's candidate of column j (its entries in v), its key published
+      auto candidate = [&](int j, const CT& v) -> int {
+        const uint32_t E = epoch0 + (uint32_t)(s0 + j);
+        u64* cand = ws.cand + (size_t)((s0 + j) & 1) * ws.gitem * PW_KEYS + PW_KEYS * g;
+        int src;
+        const u64 k = wave_argmax(mylab >= (int32_t)(k0 + s0 + j) ? pivot_key(v, (uint32_t)mylab) : 0, src);
+        if (lane < 2)
+          ll_put(cand + lane, E, lane ? (k ? 0xffffffffu - (uint32_t)k : 0xffffffffu) : (uint32_t)(k >> 32));
+        return src;
+      };
+      int lrow = candidate(0, x[0]);
+      int late = 0;  // a word did not come
+      for (int j = 0; j < sw; ++j) {
+        const int32_t gj = (int32_t)(k0 + s0 + j);
+        const uint32_t E = epoch0 + (uint32_t)(s0 + j);
+        const int par = (s0 + j) & 1;
+        const u64* cand = ws.cand + (size_t)par * ws.gitem * PW_KEYS;
+        u64* rows = ws.rows + (size_t)par * ws.gitem * RW;
+        if (lrow >= 0 && lane < RW) {
+          // (the row's earlier columns are its multipliers, the later ones are current)
+          const int c = s0 + lane / NW;
+          const CT* e = tile + (size_t)(c < w ? c : w - 1) * R + lrow;
+          uint32_t word = reinterpret_cast<const uint32_t*>(e)[lane % NW];
+          const CT piv = tile[(size_t)(s0 + j) * R + lrow];
+          CT inv;
+          inv.x = inv.y = 0;
+          if (piv.x != 0 || piv.y != 0) inv = cinv_t(piv);
+#pragma unroll
+          for (int q = 0; q < NW; ++q) word = lane == j * NW + q ? cword(inv, q) : word;
+          ll_put(&rows[(size_t)g * RW + lane], E, word);
+        }
+        int gp;
+        u64 k;
+        if (G <= 64) k = gather_keys<1>(cand, G, E, lane, gp, &late);
+        else if (G <= 128) k = gather_keys<2>(cand, G, E, lane, gp, &late);
+        else k = gather_keys<4>(cand, G, E, lane, gp, &late);
+        if (gp < 0 || __any(late)) {
+          late = 1;
+          break;
+        }
+        if (lane < RW) reinterpret_cast<uint32_t*>(lp + j * SUBW)[lane] = ll_get(rows + (size_t)gp * RW + lane, E, &late);
+        const int32_t plabel = (int32_t)(0xffffffffu - (uint32_t)(k & 0xffffffffu));
+        // interchange of positions gj <-> plabel
+        if (g == gp && lane == lrow) {
+          mylab = gj;
+          mine[j] = lrow;
+        } else if (mylab == gj) {
+          mylab = plabel;
+        }
+        if (lane == 0) pl[s0 + j] = plabel;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const CT* urow = lp + j * SUBW + j;
+        CT u[SUBW];  // the reciprocal, then the pivot row (the last ones past its end: not used)
+#pragma unroll
+        for (int c = 0; c < SUBW; ++c) u[c] = urow[c];
+        if (u[0].x == 0 && u[0].y == 0 && zero_col < 0) zero_col = s0 + j;
+        const bool active = mylab > gj;
+        const CT l = cmul_t(x[0], u[0]);
+        // the next column first: its candidate's key travels while the rest is updated
+        x[0] = r1_upd(x[1], l, u[1]);
+        const CT x1 = x[0];
+        if (j + 1 < sw) lrow = candidate(j + 1, x1);
+        static_for<SUBW - 2>([&](auto c) { x[c + 1] = r1_upd(x[c + 2], l, u[c + 2]); });
+        if (active) {
+          CT* trow = tile + (size_t)(s0 + j) * R + lane;
+          trow[0] = l;
+          static_for<SUBW - 1>([&](auto c) {
+            CT* p = j + c + 1 < sw ? trow + (c + 1) * R : spare + lane;
+            *p = x[c];
+          });
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+      if (lane < myR) lab[lane] = mylab;
+      if (late) bad = 1;
+    }
+    __syncthreads();
+    if (bad) {
+      if (tid == 0) __hip_atomic_store(&ws.err[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    const int c1 = s0 + sw, rest = w - c1;
+    if (rest <= 0) break;
+    // the pivot rows' remaining columns: owners publish theirs, everyone reads all
+    const uint32_t E = epoch0 + (uint32_t)(c1 - 1);
+    u64* const uw = ubase + (size_t)sp * SUBW * ws.wwmax;
+    const int words = rest * NW;
+    for (int i = 0; i < SUBW; ++i) {
+      const int lr = mine[i];
+      if (lr < 0) continue;
+      for (int t = tid; t < words; t += 256)
+        ll_put(uw + (size_t)i * ws.wwmax + t, E, reinterpret_cast<const uint32_t*>(tile + (size_t)(c1 + t / NW) * R + lr)[t % NW]);
+    }
+    {
+      // wave v reads rows 4 v .. 4 v + 3, 64 B words of each in flight together
+      uint32_t* const dst = reinterpret_cast<uint32_t*>(ub);
+      constexpr int B = 3;
+      for (int t0 = 0; t0 < words; t0 += 64 * B) {
+        const u64* p[4 * B];
+        uint32_t v[4 * B];
+#pragma unroll
+        for (int b = 0; b < 4 * B; ++b) {
+          const int t = t0 + 64 * (b % B) + lane;
+          p[b] = uw + (size_t)(4 * wave + b / B) * ws.wwmax + (t < words ? t : lane % words);
+        }
+        ll_get_n<4 * B>(p, E, v, &bad);
+#pragma unroll
+        for (int b = 0; b < 4 * B; ++b) {
+          const int t = t0 + 64 * (b % B) + lane;
+          if (t < words) dst[(size_t)(4 * wave + b / B) * restmax * NW + t] = v[b];
+        }
+      }
+    }
+    __syncthreads();
+    if (bad) {
+      if (tid == 0) __hip_atomic_store(&ws.err[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    // U rows: one column per thread
+    if (tid < rest) {
+      CT u[SUBW];
+#pragma unroll
+      for (int i = 0; i < SUBW; ++i) u[i] = ub[i * restmax + tid];
+      static_for<SUBW>([&](auto i) {
+        static_for<decltype(i)::value>([&](auto p) { u[i] = r1_upd(u[i], lp[i * SUBW + p], u[p]); });
+        ub[i * restmax + tid] = u[i];
+      });
+    }
+    __syncthreads();
+    const int32_t last = (int32_t)(k0 + c1 - 1);
+    for (int i = 0; i < SUBW; ++i) {
+      const int lr = mine[i];
+      if (lr >= 0)
+        for (int c = tid; c < rest; c += 256) tile[(size_t)(c1 + c) * R + lr] = ub[i * restmax + c];
+    }
+    // rank-SUBW update of the rows still active: 16 x 16 tiles dealt to the waves
+    {
+      const int lr16 = lane & 15, lk = lane >> 4;
+      const int rt = (myR + 15) >> 4, nt = rt * ((rest + 15) >> 4);
+      for (int t = wave; t < nt; t += 4) {
+        const int row = 16 * (t % rt) + lr16, crow = row < myR ? row : myR - 1;
+        const int cc = 16 * (t / rt);
+        const int uc = cc + lr16 < rest ? cc + lr16 : rest - 1;
+        typename acc_of<T>::type re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+        CT l[4], u[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          l[q] = tile[(size_t)(s0 + 4 * q + lk) * R + crow];
+          u[q] = ub[(4 * q + lk) * restmax + uc];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          re = mfma16(u[q].x, l[q].x, re);
+          im = mfma16(u[q].x, l[q].y, im);
+          re = mfma16(-u[q].y, l[q].y, re);
+          im = mfma16(u[q].y, l[q].x, im);
+        }
+        if (row < myR && lab[row] > last) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int c = cc + (sizeof(T) == 8 ? lk + 4 * q : 4 * lk + q);
+            if (c < rest) {
+              CT* p = tile + (size_t)(c1 + c) * R + row;
+              CT v = *p;
+              v.x -= re[q];
+              v.y -= im[q];
+              *p = v;
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (g == 0) {
+    for (int j = tid; j < w; j += 256) ipiv[k0 + j] = pl[j];
+    if (tid == 0 && zero_col >= 0) atomicMin(&ws.err[1], (int)(k0 + zero_col));
+  }
+  if (tid < myR) {
+    const int32_t orig = (int32_t)(rbase + tid);
+    if (lab[tid] != orig) {
+      const int slot = __hip_atomic_fetch_add(mcount, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (slot < mcap) {
+        mdst[slot] = lab[tid];
+        msrc[slot] = orig;
+      }
+    }
+  }
+  if (lane < myR) {
+    CT* dst = A + lab[lane] + k0 * ld;
+    for (int c = wave; c < w; c += 4) dst[c * ld] = tile[c * R + lane];
   }
 }
 
@@ -1205,6 +1539,8 @@ LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch,
   p.pb = pb;
   // the panels of all items run in one launch and must all be resident
   p.max_wg = num_cu / nbatch > 0 ? num_cu / nbatch : 1;
+  p.nbatch = nbatch;
+  p.lds_bytes = lds_bytes;
   // row workgroups of one panel: with tournament pivoting, one root workgroup
   // per 32 of them must be resident too (G + ceil(G / 32) <= max_wg)
   const int avail = pb > 1 ? std::max(1, 32 * p.max_wg / 33) : p.max_wg;
@@ -1324,11 +1660,27 @@ static const void* panel_fn(int pb) {
   }
 }
 
+// Whether block b's panel takes the kernel whose columns are one wave's work: one
+// system, pivots one column at a time, a workgroup's rows one per lane, its LDS
+// and exchange buffers as they are.  (FP32 from n = 8192 on and FP64 from about 14 000
+// have more rows per workgroup in the first blocks.)
+template <typename T>
+static bool panel_in_wave(const LUPlan& p, const LUBlock& b, int gitem) {
+  return p.pb <= 1 && p.nbatch == 1 && b.R <= 64 && b.G <= 256 &&
+         (p.nb <= SUBW || (int64_t)gitem * (p.nb - SUBW) >= (int64_t)SUBW * p.nb) &&
+         panel_wave_lds<cplx<T>>(b.w, b.R) + 256 <= (size_t)p.lds_bytes;
+}
+
 // One panel launch: G row workgroups (plus the roots of a tournament panel) per item.
 template <typename T>
-static void launch_panel(int pb, const LUBlock& b, int NB, size_t lds, hipStream_t st, cplx<T>* A, int64_t ld,
+static void launch_panel(int pb, bool in_wave, const LUBlock& b, int NB, size_t lds, hipStream_t st, cplx<T>* A, int64_t ld,
                          int64_t n, int32_t* ipiv, const LUWork& ws, uint32_t epoch, int64_t sA, int64_t sipiv,
                          int32_t* dst, int32_t* src, int32_t* npr, int mcap) {
+  if (in_wave) {
+    hipLaunchKernelGGL(panel_wave_kernel<T>, dim3(b.G), dim3(256), panel_wave_lds<cplx<T>>(b.w, b.R), st, A, ld, n, b.k0,
+                       b.w, b.R, b.G, ipiv, ws, epoch, dst, src, npr, mcap);
+    return;
+  }
   const dim3 grid(b.G + (pb > 1 ? tp_roots(b.G) : 0), NB);
 #define GDM_PANEL_ARGS A, ld, n, b.k0, b.w, b.R, b.G, ipiv, ws, epoch, sA, sipiv, dst, src, npr, mcap
   switch (pb) {
@@ -1361,8 +1713,9 @@ hipError_t lu_prepare(const LUPlan& plan) {
     }
   }
   for (const LUBlock& b : plan.blocks) {
-    const size_t need = panel_lds_bytes(b.w, b.R, sizeof(cplx<T>), plan.pb);
-    const void* fn = panel_fn<T>(plan.pb);
+    const bool in_wave = panel_in_wave<T>(plan, b, plan.max_wg);
+    const size_t need = in_wave ? panel_wave_lds<cplx<T>>(b.w, b.R) : panel_lds_bytes(b.w, b.R, sizeof(cplx<T>), plan.pb);
+    const void* fn = in_wave ? reinterpret_cast<const void*>(&panel_wave_kernel<T>) : panel_fn<T>(plan.pb);
     if (!fn) return hipErrorInvalidValue;
     size_t& cur = lds_set[fn];
     if (need > 64 * 1024 && need > cur) {
@@ -1452,7 +1805,7 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
     if (plan.spec) {
       LUCHK(launch_diag_lu<T>(A, ld, nb, k0, w, ipiv, flag, tinv, st, NB, sA, sipiv, ws.s_npairs, ws.s_tinv));
     } else {
-      launch_panel<T>(plan.pb, b, NB, lds, st, A, ld, n, ipiv, ws, epoch, sA, sipiv, dst, src, npr, 2 * nb);
+      launch_panel<T>(plan.pb, panel_in_wave<T>(plan, b, ws.gitem), b, NB, lds, st, A, ld, n, ipiv, ws, epoch, sA, sipiv, dst, src, npr, 2 * nb);
       epoch += (uint32_t)w;
       LUCHK(hipGetLastError());
       LUCHK(launch_tile_inv<T>(A, ld, nb, k0, w, tinv, st, NB, sA, ws.s_tinv));

@@ -1,4 +1,4 @@
-// Device helpers shared by the LU's kernels (lu.hip, tiles.hip).
+// Device helpers shared by the LU's kernels (lu.hip, tiles.hip, solve_step.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <utility>
@@ -6,6 +6,14 @@
 #include "gdm_common.hpp"
 
 namespace gdm {
+
+// 16 x 16 x 4 products; rows of the result in register q of lane group lk: 4 lk + q
+// (FP32), lk + 4 q (FP64)
+template <typename T> struct acc_of;
+template <> struct acc_of<double> { using type = v4d; };
+template <> struct acc_of<float> { using type = v4f; };
+__device__ inline v4d mfma16(double a, double b, v4d c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+__device__ inline v4f mfma16(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 template <typename CT> __device__ inline CT cmul_t(CT a, CT b) {
   CT r;

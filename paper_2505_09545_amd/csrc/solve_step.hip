@@ -16,18 +16,9 @@
 
 #include "gdm_common.hpp"
 #include "gdm_kernels.hpp"
+#include "lu_common.hpp"
 
 namespace gdm {
-
-namespace {
-
-template <typename T> struct acc_of;
-template <> struct acc_of<double> { using type = v4d; };
-template <> struct acc_of<float> { using type = v4f; };
-__device__ inline v4d mfma16(double a, double b, v4d c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-__device__ inline v4f mfma16(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
-}  // namespace
 
 // KS: k per lane and wave (8: k <= 128, 4: k <= 64)
 template <typename T, int NCT, int KS>

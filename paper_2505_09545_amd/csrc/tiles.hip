@@ -27,12 +27,6 @@ namespace gdm {
 
 namespace {
 
-template <typename T> struct acc_of;
-template <> struct acc_of<double> { using type = v4d; };
-template <> struct acc_of<float> { using type = v4f; };
-__device__ inline v4d mfma16(double a, double b, v4d c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-__device__ inline v4f mfma16(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
 // Tile row (0..15) of accumulator register q in lane group lk = lane / 16: the
 // FP32 MFMA returns rows 4 lk + q, the FP64 one rows lk + 4 q.
 template <typename T> __device__ inline int rof(int lk, int q) { return sizeof(T) == 8 ? lk + 4 * q : 4 * lk + q; }

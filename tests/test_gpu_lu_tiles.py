@@ -105,3 +105,36 @@ def test_solve_step_edges(ctx, dtype, n, nrhs):
     ref = np.linalg.solve(A, B.T).T
     err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= 8 * max(n, 16) * eps, err
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("n", [2, 16, 17, 33, 127, 150, 520, 2100])
+def test_panel_pivots(ctx, n, dtype):
+    """Pivots of the searching panels at the edges of their 16-column steps and
+    workgroups (32 rows), against LAPACK's (the same |re| + |im|; Gaussian entries,
+    whose largest differ by far more than the rounding here)."""
+    from scipy.linalg import lu_factor
+    rng = np.random.default_rng(7 * n)
+    A = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))
+    F = torch.as_tensor(A.T.copy()).to(device="cuda", dtype=dtype).contiguous()
+    piv = ctx.getrf(F).cpu().numpy()
+    ref = lu_factor(A.astype(np.complex128 if dtype == torch.complex128 else np.complex64))[1]
+    assert np.array_equal(piv, ref), np.nonzero(piv != ref)[0][:5]
+
+
+def test_panels_of_many_and_few_rows(ctx):
+    """n = 8300 in FP32: the first blocks have more rows per workgroup than a wave
+    has lanes, the later ones fewer; the residual of one solve in FP64."""
+    n = 8300
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A = torch.randn(n, n, dtype=torch.complex64, device="cuda", generator=g) / n ** 0.5
+    A += 2 * torch.roll(torch.eye(n, dtype=torch.complex64, device="cuda"), 17, 0)
+    B = torch.randn(1, n, dtype=torch.complex64, device="cuda", generator=g)
+    F, X = A.clone(), B.clone()
+    ctx.getrf(F)
+    ctx.getrs(F, X, 0)
+    x, b = X[0].to(torch.complex128), B[0].to(torch.complex128)
+    res = torch.zeros_like(b)
+    for k in range(0, n, 1000):  # storage row k is column k of the matrix
+        res += (A[k:k + 1000].to(torch.complex128) * x[k:k + 1000, None]).sum(0)
+    assert float((res - b).norm() / b.norm()) <= 8 * n * 1.2e-7
