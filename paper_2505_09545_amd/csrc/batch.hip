@@ -12,6 +12,7 @@
 // q = alpha F, and the cross sections C Im(F0^* q), C Im(F^* q) (cells carry no
 // radiation-reaction term), C = 4 pi k0 / (n_env |e0|^2).
 #include "gdm_batch.hpp"
+#include "gdm_misc.hpp"
 
 namespace gdm {
 
@@ -102,21 +103,6 @@ __global__ void batch_apply_alpha_kernel(const double2* __restrict__ alpha, cons
   const int64_t col = blockIdx.y;
   if (u >= n) return;
   q[col * n + u] = cmul(alpha[col / npw], F[col * n + u]);
-}
-
-// rows[z n + i] = sum_j |M_z[i, j]| (one thread per row, columns in order)
-__global__ void batch_rowsum_kernel(const double2* __restrict__ M, int64_t ld, int64_t n, int64_t sM,
-                                    double* __restrict__ rows) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t z = blockIdx.y;
-  if (i >= n) return;
-  const double2* m = M + z * sM + i;
-  double s = 0;
-  for (int64_t j = 0; j < n; ++j) {
-    const double2 v = m[j * ld];
-    s += sqrt(v.x * v.x + v.y * v.y);
-  }
-  rows[z * n + i] = s;
 }
 
 // minf[z] = max_i rows[z n + i]
@@ -260,8 +246,8 @@ hipError_t launch_batch_apply_alpha(const double2* alpha, const double2* F, doub
 }
 
 hipError_t launch_batch_minf(const double2* M, int64_t n, int B, double* rows, double* minf, hipStream_t st) {
-  hipLaunchKernelGGL(batch_rowsum_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)B), dim3(256), 0, st, M, n, n,
-                     n * n, rows);
+  const hipError_t e = launch_rowsum_abs(M, n, n, rows, st, B, n * n);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(batch_rowmax_kernel, dim3((unsigned)B), dim3(256), 0, st, rows, n, minf);
   return hipGetLastError();
 }

@@ -138,3 +138,23 @@ def test_panels_of_many_and_few_rows(ctx):
     for k in range(0, n, 1000):  # storage row k is column k of the matrix
         res += (A[k:k + 1000].to(torch.complex128) * x[k:k + 1000, None]).sum(0)
     assert float((res - b).norm() / b.norm()) <= 8 * n * 1.2e-7
+
+
+@pytest.mark.parametrize("cells", [1, 21, 22, 85, 86, 171, 343])
+def test_row_norm_edges(ctx, cells):
+    """The infinity norm in the backward error (64 rows and 256 columns per
+    workgroup): an unrefined FP32 solution's error of about 1e-7, whose residual
+    keeps six digits."""
+    import gdm_inputs as gi
+    rng = np.random.default_rng(cells)
+    r = gi.cuboid_cells(7, 7, 7, 7.0)[:cells]
+    ctx.set_environment(1.0)
+    ctx.set_structure(r, 7.0, rng.uniform(2.0, 14.0, cells) + 0.1j)
+    M = ctx.assemble(640.0).cpu().numpy()
+    ctx.factorize(640.0, 1)
+    f0 = rng.standard_normal((1, ctx.n)) + 1j * rng.standard_normal((1, ctx.n))
+    _, f = ctx.solve(torch.as_tensor(f0), tol=1.0)
+    x = f.cpu().numpy()[0]
+    res = np.abs(f0[0] - M @ x).max()
+    be = res / (np.abs(M).sum(1).max() * np.abs(x).max() + np.abs(f0).max())
+    assert abs(ctx.info.backward_err - be) <= 1e-6 * be + 1e-15, (ctx.info.backward_err, be)
