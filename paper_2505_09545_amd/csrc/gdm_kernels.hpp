@@ -170,6 +170,16 @@ template <typename T>
 hipError_t launch_skinny_n(int64_t m, int64_t k, const void* A, int64_t lda, const void* X, int64_t ldx, void* C,
                            int64_t ldc, int64_t nrhs, hipStream_t st, GemmMask mk = GemmMask{}, int nbatch = 1,
                            int64_t sA = 0, int64_t sX = 0, int64_t sC = 0);
+// y[c] -= sum_k A[k + c lda] z[k], k < w <= 128, c < ncols (leading dimension ldb of
+// y and z, item stride sB)
+template <typename T>
+hipError_t launch_skinny_push(int w, int64_t ncols, const void* A, int64_t lda, const void* z, void* y, int64_t ldb,
+                              int64_t nrhs, hipStream_t st, int nbatch = 1, int64_t sA = 0, int64_t sB = 0);
+// x_b -= tri(D_b)^T x_b for all diagonal blocks D_b (nb <= 128 wide): the strict
+// lower triangle, or the upper one with the diagonal
+template <typename T>
+hipError_t launch_skinny_diag_t(bool lower, int64_t n, int nb, const void* A, int64_t lda, void* x, int64_t ldb,
+                                int64_t nrhs, hipStream_t st, int nbatch = 1, int64_t sA = 0, int64_t sB = 0);
 // C[mo x nrhs] -= A0^T B0 + mask(A1)^T B1 with A0 (k0 x mo) and A1 (k1 x mo)
 // stored column-major; split over k into chunks whose partial sums go to
 // `part` (capacity part_elems complex), then added to C in a fixed order.

@@ -1989,16 +1989,26 @@ hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, c
       }
     } else {
       // M^T = U^T L_k^T P_k ... L_1^T P_1.  U^T forward, with V = U01 U11^-1 stored above the diagonal:
-      //   z_b = U11^-T g_b - V^T z_above = g_b - V^T z_above - (I - U11^-1)^T g_b
-      // (both products read the pre-step B; the split-k partials are added afterwards)
-      for (int bi = 0; bi < nblk; ++bi) {
+      //   z_b = U11^-T g_b - V_b^T z_above, the first term of all blocks at once
+      if ((e = launch_skinny_diag_t<T>(false, n, nb, A, ld, B, ldb, nr, st, NB, sA, sB)) != hipSuccess) return e;
+      for (int bi = 0; bi + 1 < nblk; ++bi) {
         const LUBlock& b = plan.blocks[bi];
-        const int64_t k0 = b.k0;
-        if ((e = launch_skinny_t<T>(b.w, nr, A + k0 * ld, ld, B, ldb, k0, A + k0 + k0 * ld, ld, B + k0, ldb, b.w,
-                                    GEMM_MASK_LOWER, X, part_elems, B + k0, ldb, st, NB, sA, sB, sB)) != hipSuccess)
+        const int64_t k0 = b.k0, c1 = k0 + b.w;
+        if ((e = launch_skinny_push<T>(b.w, n - c1, A + k0 + c1 * ld, ld, B + k0, B + c1, ldb, nr, st, NB, sA, sB)) !=
+            hipSuccess)
           return e;
       }
       // then for b = k..1: z_b = L11^-T z_b - (L21 L11^-1)^T z_below, and z = P_b^T z
+      if (!perm) {
+        if ((e = launch_skinny_diag_t<T>(true, n, nb, A, ld, B, ldb, nr, st, NB, sA, sB)) != hipSuccess) return e;
+        for (int bi = nblk - 1; bi > 0; --bi) {
+          const LUBlock& b = plan.blocks[bi];
+          if ((e = launch_skinny_push<T>(b.w, b.k0, A + b.k0, ld, B + b.k0, B, ldb, nr, st, NB, sA, sB)) != hipSuccess)
+            return e;
+        }
+        continue;
+      }
+      // (interchanges move rows between a block's sum and the next: gathered block by block)
       for (int bi = nblk - 1; bi >= 0; --bi) {
         const LUBlock& b = plan.blocks[bi];
         const int64_t k0 = b.k0, c1 = k0 + b.w;
@@ -2008,9 +2018,8 @@ hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, c
           return e;
         const int32_t* dst = ws.pairs + bi * 4 * (size_t)nb;
         const int32_t* src = dst + 2 * nb;
-        if (perm)
-          hipLaunchKernelGGL(row_permute_inv_kernel<T>, dim3((unsigned)nr, NB), dim3(256), 0, st, B, ldb, (int64_t)0,
-                             dst, src, ws.npairs + bi, sB, ws.s_pairs, ws.s_npairs);
+        hipLaunchKernelGGL(row_permute_inv_kernel<T>, dim3((unsigned)nr, NB), dim3(256), 0, st, B, ldb, (int64_t)0, dst,
+                           src, ws.npairs + bi, sB, ws.s_pairs, ws.s_npairs);
       }
     }
   }

@@ -4,11 +4,16 @@
 // The forward/backward steps update many rows from one 128-wide block (an
 // m x k product with k <= 256); with 1-8 right-hand sides a 64 x 64 matrix-core
 // tile would be almost empty, so a plain VALU kernel streams the block once:
-// one row per lane, the k range split over the four waves of a workgroup, the
-// right-hand sides staged in LDS, the waves' partial sums combined in LDS.
+// one row per lane, the k range split over the eight waves of a workgroup (at k =
+// 128 every load of a wave is in flight at once, before the right-hand sides are
+// staged in LDS), the waves' partial sums combined in LDS.  Bound by latency:
+// k = 128, FP32, one column, m = 3000 on average 5.4 us (four waves, X first: 7.7); FP64,
+// eight columns, m = 1500 9.9 us (14.6).
 //
-// The steps of a transposed solve produce one 128-row block from a long
-// product (k up to n): C[w x nr] -= op(A)^T B, and the transposed refinement
+// A transposed solve subtracts a block's part from the later columns as soon as it
+// is known (skinny_push_kernel).  Where interchanges come between the blocks (L^T
+// of a pivoting panel's factors), a step instead gathers its 128-row block from a
+// long product (k up to n): C[w x nr] -= op(A)^T B, and the transposed refinement
 // residual is the same shape with w = n.  Each output is the dot product of a
 // stored column of A with B: one wave per column, lanes along k (coalesced
 // column reads), the k range split into chunks of KC rows, one partial sum per
@@ -43,19 +48,21 @@ __device__ inline void cfma_t(cplx<T>& acc, const cplx<T>& a, const cplx<T>& b) 
 
 // C[m x nr] -= A[m x k] X[k x nr]; rows [ar0, ar0 + adw) of A are a square
 // block of which only the `akind` triangle is read.  64 rows per workgroup, the
-// k range split over its four waves.
+// k range split over its eight waves.
 // With PART, blockIdx.z selects the k chunk [z SK_KMAX, (z + 1) SK_KMAX) of a
 // longer product and the sums go to part[(z * nrhs + r) * m + row] instead.
 // Batch: blockIdx.z = item (x nchunk + chunk with PART); item z reads A + z sA,
 // X + z sX and writes C + z sC (PART: its own nchunk x nrhs x m partials).
 template <typename T, int NR, bool PART>
-__global__ void __launch_bounds__(256) skinny_n_kernel(int64_t m, int64_t k, const cplx<T>* __restrict__ A,
+__global__ void __launch_bounds__(512) skinny_n_kernel(int64_t m, int64_t k, const cplx<T>* __restrict__ A,
                                                         int64_t lda, const cplx<T>* __restrict__ X, int64_t ldx,
                                                         cplx<T>* __restrict__ C, int64_t ldc, int64_t nrhs,
                                                         GemmMask mk, int nchunk, int64_t sA, int64_t sX, int64_t sC) {
   using CT = cplx<T>;
-  __shared__ CT xs[SK_KMAX][NR];
-  __shared__ CT red[3][64][NR];
+  constexpr int NWV = 8;
+  // X (SK_KMAX x NR), then the waves' sums
+  constexpr int LE = SK_KMAX * NR > NWV * 64 * NR ? SK_KMAX * NR : NWV * 64 * NR;
+  __shared__ CT lds[LE];
   const int64_t item = PART ? blockIdx.z / nchunk : blockIdx.z;
   const int64_t chunk = PART ? blockIdx.z - item * nchunk : 0;
   A += item * sA;
@@ -69,75 +76,70 @@ __global__ void __launch_bounds__(256) skinny_n_kernel(int64_t m, int64_t k, con
   }
   const int64_t r0 = (int64_t)blockIdx.y * NR;
   const int nr = (int)(nrhs - r0 < NR ? nrhs - r0 : NR);
-  for (int t = threadIdx.x; t < k * NR; t += 256) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row0 = (int64_t)blockIdx.x * 64;
+  const int64_t row = row0 + lane < m ? row0 + lane : m - 1;  // (rows past the end: not stored)
+  const int kn = (int)k, kq = (kn + NWV - 1) / NWV;
+  const int ka = wave * kq, kb = ka + kq < kn ? ka + kq : kn;
+  // the first KB (for k = 128 all) of the wave's columns are in flight before X is staged
+  constexpr int KB = 16;
+  CT a[KB];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < KB; ++u) a[u] = A[row + (int64_t)(k0 + u < kn ? k0 + u : kn - 1) * lda];
+  };
+  load(ka);
+  for (int t = threadIdx.x; t < kn * NR; t += 512) {
     const int kk = t / NR, r = t % NR;
     CT v;
     v.x = 0;
     v.y = 0;
     if (r < nr) v = X[kk + (r0 + r) * ldx];
-    xs[kk][r] = v;
+    lds[kk * NR + r] = v;
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * 64 + lane;
-  const int64_t kq = (k + 3) / 4;
-  const int64_t ka = wave * kq, kb = ka + kq < k ? ka + kq : k;
   CT acc[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) acc[r].x = acc[r].y = 0;
-  if (row < m) {
-    const bool masked = mk.akind && row >= mk.ar0 && row < mk.ar0 + mk.adw;
-    // KB loads in flight per lane, then their products (a load and its use in
-    // one loop body put one memory latency per k on the path); the masked
-    // triangle is stored, so it is read and replaced by zero
-    constexpr int KB = 16;
-    for (int64_t k0 = ka; k0 < kb; k0 += KB) {
-      CT a[KB];
+  // the masked triangle is stored, so it is read and replaced by zero
+  const bool masked = mk.akind && row >= mk.ar0 && row < mk.ar0 + mk.adw;
+  for (int k0 = ka; k0 < kb; k0 += KB) {
+    if (k0 != ka) load(k0);
 #pragma unroll
-      for (int u = 0; u < KB; ++u) {
-        a[u].x = 0;
-        a[u].y = 0;
-        if (k0 + u < kb) a[u] = A[row + (k0 + u) * lda];
-      }
+    for (int u = 0; u < KB; ++u) {
+      const int kk = k0 + u;
+      if (kk < kb) {
+        CT v = a[u];
+        if (masked && !sk_keep(mk.akind, row - mk.ar0, kk)) v.x = v.y = 0;
 #pragma unroll
-      for (int u = 0; u < KB; ++u) {
-        const int64_t kk = k0 + u;
-        if (kk < kb) {
-          CT v = a[u];
-          if (masked && !sk_keep(mk.akind, row - mk.ar0, kk)) v.x = v.y = 0;
-#pragma unroll
-          for (int r = 0; r < NR; ++r) cfma_t<T>(acc[r], v, xs[kk][r]);
-        }
+        for (int r = 0; r < NR; ++r) cfma_t<T>(acc[r], v, lds[kk * NR + r]);
       }
     }
   }
-  if (wave > 0)
-#pragma unroll
-    for (int r = 0; r < NR; ++r) red[wave - 1][lane][r] = acc[r];
   __syncthreads();
-  if (wave == 0 && row < m) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if (r >= nr) break;  // compile-time indices into acc (no private-memory copy)
-      CT s = acc[r];
+  for (int r = 0; r < NR; ++r) lds[(r * NWV + wave) * 64 + lane] = acc[r];
+  __syncthreads();
+  // wave r of the workgroup finishes right-hand side r
+  const int r = wave;
+  if (r >= nr || row0 + lane >= m) return;
+  CT s = lds[r * NWV * 64 + lane];
 #pragma unroll
-      for (int w = 0; w < 3; ++w) {
-        s.x += red[w][lane][r].x;
-        s.y += red[w][lane][r].y;
-      }
-      if (PART) {
-        C[(chunk * nrhs + r0 + r) * m + row] = s;
-      } else {
-        // rows [ar0, ar0 + adw) optionally to the second destination mk.c2
-        CT c = C[row + (r0 + r) * ldc];
-        c.x -= s.x;
-        c.y -= s.y;
-        if (mk.c2 && row >= mk.ar0 && row < mk.ar0 + mk.adw)
-          static_cast<CT*>(mk.c2)[item * mk.sc2 + (row - mk.ar0) + (r0 + r) * mk.ldc2] = c;
-        else
-          C[row + (r0 + r) * ldc] = c;
-      }
-    }
+  for (int w = 1; w < NWV; ++w) {
+    s.x += lds[(r * NWV + w) * 64 + lane].x;
+    s.y += lds[(r * NWV + w) * 64 + lane].y;
+  }
+  if (PART) {
+    C[(chunk * nrhs + r0 + r) * m + row] = s;
+  } else {
+    // rows [ar0, ar0 + adw) optionally to the second destination mk.c2
+    CT c = C[row + (r0 + r) * ldc];
+    c.x -= s.x;
+    c.y -= s.y;
+    if (mk.c2 && row >= mk.ar0 && row < mk.ar0 + mk.adw)
+      static_cast<CT*>(mk.c2)[item * mk.sc2 + (row - mk.ar0) + (r0 + r) * mk.ldc2] = c;
+    else
+      C[row + (r0 + r) * ldc] = c;
   }
 }
 
@@ -261,6 +263,126 @@ __global__ void skinny_reduce_kernel(const cplx<T>* __restrict__ part, int nchun
   *p = c;
 }
 
+// Transposed solves, block by block downwards (upwards): once a block's unknowns
+// z are known their part of every later column is subtracted,
+//   y[c] -= sum_k A[k + c lda] z[k], k < w <= 128,
+// one launch per block and no partial sums (gathering a block's own sum from all
+// known unknowns took a product and a reduction: 11.5 us and two launches per
+// block at n = 6000, this 4.2).  A wave takes four columns, lanes along k.
+// Bound by latency: the block row is 3 MB on average.
+template <typename T, int NR>
+__global__ void __launch_bounds__(256) skinny_push_kernel(int w, int64_t ncols, const cplx<T>* __restrict__ A, int64_t lda,
+                                                           const cplx<T>* __restrict__ z, cplx<T>* __restrict__ y,
+                                                           int64_t ldb, int64_t nrhs, int64_t sA, int64_t sB) {
+  using CT = cplx<T>;
+  constexpr int CPW = 4;
+  A += blockIdx.z * sA;
+  z += blockIdx.z * sB;
+  y += blockIdx.z * sB;
+  const int64_t r0 = (int64_t)blockIdx.y * NR;
+  const int nr = (int)(nrhs - r0 < NR ? nrhs - r0 : NR);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t c0 = ((int64_t)blockIdx.x * 4 + wave) * CPW;
+  if (c0 >= ncols) return;
+  CT a[CPW][2], b[2][NR], zero;
+  zero.x = zero.y = 0;
+#pragma unroll
+  for (int c = 0; c < CPW; ++c)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = lane + 64 * h;
+      a[c][h] = A[(k < w ? k : w - 1) + (c0 + c < ncols ? c0 + c : ncols - 1) * lda];
+    }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      b[h][r] = zero;
+      if (lane + 64 * h < w && r < nr) b[h][r] = z[lane + 64 * h + (r0 + r) * ldb];
+    }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (lane + 64 * h >= w)
+#pragma unroll
+      for (int c = 0; c < CPW; ++c) a[c][h] = zero;
+  // lane c + CPW r keeps column c of right-hand side r
+  static_assert(CPW * NR <= 64, "one lane per result");
+  CT sum = zero;
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) {
+      CT s = zero;
+      cfma_t<T>(s, a[c][0], b[0][r]);
+      cfma_t<T>(s, a[c][1], b[1][r]);
+      s.x = wave_sum(s.x);
+      s.y = wave_sum(s.y);
+      if (lane == c + CPW * r) sum = s;
+    }
+  const int c = lane % CPW, r = lane / CPW;
+  if (r < nr && c0 + c < ncols) {
+    CT* p = y + c0 + c + (r0 + r) * ldb;
+    CT v = *p;
+    v.x -= sum.x;
+    v.y -= sum.y;
+    *p = v;
+  }
+}
+
+// x_b = x_b - tri(D_b)^T x_b for every diagonal block b (LOWER false: its upper
+// triangle with the diagonal, I - U11^-1; true: its strict lower one, I - L11^-1):
+// one workgroup of 16 waves per block, in place.
+template <typename T, int NR, bool LOWER>
+__global__ void __launch_bounds__(1024) skinny_diag_t_kernel(int64_t n, int nb, const cplx<T>* __restrict__ A, int64_t lda,
+                                                              cplx<T>* __restrict__ x, int64_t ldb, int64_t nrhs,
+                                                              int64_t sA, int64_t sB) {
+  using CT = cplx<T>;
+  const int64_t k0 = (int64_t)blockIdx.x * nb;
+  const int w = (int)(n - k0 < nb ? n - k0 : nb);
+  A += blockIdx.z * sA + k0 + k0 * lda;
+  x += blockIdx.z * sB + k0;
+  const int64_t r0 = (int64_t)blockIdx.y * NR;
+  const int nr = (int)(nrhs - r0 < NR ? nrhs - r0 : NR);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  CT b[2][NR], zero;
+  zero.x = zero.y = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      b[h][r] = zero;
+      if (lane + 64 * h < w && r < nr) b[h][r] = x[lane + 64 * h + (r0 + r) * ldb];
+    }
+  CT a[8][2];
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c = 8 * wave + u, k = lane + 64 * h;
+      a[u][h] = A[(k < w ? k : w - 1) + (int64_t)(c < w ? c : w - 1) * lda];
+      if (k >= w || (LOWER ? k <= c : k > c)) a[u][h] = zero;
+    }
+  __syncthreads();  // every wave has read x
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int c = 8 * wave + u;
+      CT s = zero;
+      cfma_t<T>(s, a[u][0], b[0][r]);
+      cfma_t<T>(s, a[u][1], b[1][r]);
+      s.x = wave_sum(s.x);
+      s.y = wave_sum(s.y);
+      // (column c is a row of x that lane c % 64 holds)
+      if (lane == c % 64 && c < w && r < nr) {
+        CT v = c < 64 ? b[0][r] : b[1][r];
+        v.x -= s.x;
+        v.y -= s.y;
+        x[c + (r0 + r) * ldb] = v;
+      }
+    }
+}
+
 static int pick_nr(int64_t nrhs) { return nrhs <= 1 ? 1 : nrhs <= 2 ? 2 : nrhs <= 4 ? 4 : 8; }
 
 template <typename T>
@@ -275,10 +397,10 @@ hipError_t launch_skinny_n(int64_t m, int64_t k, const void* A, int64_t lda, con
   const auto* x = static_cast<const cplx<T>*>(X);
   auto* c = static_cast<cplx<T>*>(C);
   switch (NRp) {
-    case 1: hipLaunchKernelGGL((skinny_n_kernel<T, 1, false>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
-    case 2: hipLaunchKernelGGL((skinny_n_kernel<T, 2, false>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
-    case 4: hipLaunchKernelGGL((skinny_n_kernel<T, 4, false>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
-    default: hipLaunchKernelGGL((skinny_n_kernel<T, 8, false>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
+    case 1: hipLaunchKernelGGL((skinny_n_kernel<T, 1, false>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
+    case 2: hipLaunchKernelGGL((skinny_n_kernel<T, 2, false>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
+    case 4: hipLaunchKernelGGL((skinny_n_kernel<T, 4, false>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
+    default: hipLaunchKernelGGL((skinny_n_kernel<T, 8, false>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, c, ldc, nrhs, mk, 1, sA, sX, sC); break;
   }
   return hipGetLastError();
 }
@@ -303,10 +425,10 @@ hipError_t launch_skinny_n_long(int64_t m, int64_t k, const void* A, int64_t lda
   const GemmMask mk{};
   const int nc = (int)nchunk;
   switch (NRp) {
-    case 1: hipLaunchKernelGGL((skinny_n_kernel<T, 1, true>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
-    case 2: hipLaunchKernelGGL((skinny_n_kernel<T, 2, true>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
-    case 4: hipLaunchKernelGGL((skinny_n_kernel<T, 4, true>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
-    default: hipLaunchKernelGGL((skinny_n_kernel<T, 8, true>), grid, dim3(256), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
+    case 1: hipLaunchKernelGGL((skinny_n_kernel<T, 1, true>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
+    case 2: hipLaunchKernelGGL((skinny_n_kernel<T, 2, true>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
+    case 4: hipLaunchKernelGGL((skinny_n_kernel<T, 4, true>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
+    default: hipLaunchKernelGGL((skinny_n_kernel<T, 8, true>), grid, dim3(512), 0, st, m, k, a, lda, x, ldx, p, m, nrhs, mk, nc, sA, sX, (int64_t)0); break;
   }
   const int64_t tot = m * nrhs;
   hipLaunchKernelGGL(skinny_reduce_kernel<T>, dim3((unsigned)((tot + 255) / 256), (unsigned)nbatch), dim3(256), 0, st, p,
@@ -325,6 +447,59 @@ hipError_t launch_partial_reduce(const void* part, int nchunk, int64_t mo, int64
 }
 template hipError_t launch_partial_reduce<double>(const void*, int, int64_t, int64_t, void*, int64_t, hipStream_t);
 template hipError_t launch_partial_reduce<float>(const void*, int, int64_t, int64_t, void*, int64_t, hipStream_t);
+
+template <typename T>
+hipError_t launch_skinny_push(int w, int64_t ncols, const void* A, int64_t lda, const void* z, void* y, int64_t ldb,
+                              int64_t nrhs, hipStream_t st, int nbatch, int64_t sA, int64_t sB) {
+  if (w <= 0 || ncols <= 0 || nrhs <= 0 || nbatch <= 0) return hipSuccess;
+  if (w > 128 || nbatch > 65535) return hipErrorInvalidValue;
+  const int NRp = pick_nr(nrhs);
+  if ((nrhs + NRp - 1) / NRp > 65535) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((ncols + 15) / 16), (unsigned)((nrhs + NRp - 1) / NRp), (unsigned)nbatch);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, w, ncols, static_cast<const cplx<T>*>(A), lda,
+                       static_cast<const cplx<T>*>(z), static_cast<cplx<T>*>(y), ldb, nrhs, sA, sB);
+  };
+  switch (NRp) {
+    case 1: go(skinny_push_kernel<T, 1>); break;
+    case 2: go(skinny_push_kernel<T, 2>); break;
+    case 4: go(skinny_push_kernel<T, 4>); break;
+    default: go(skinny_push_kernel<T, 8>); break;
+  }
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_skinny_diag_t(bool lower, int64_t n, int nb, const void* A, int64_t lda, void* x, int64_t ldb,
+                                int64_t nrhs, hipStream_t st, int nbatch, int64_t sA, int64_t sB) {
+  if (n <= 0 || nrhs <= 0 || nbatch <= 0) return hipSuccess;
+  if (nb <= 0 || nb > 128 || nbatch > 65535) return hipErrorInvalidValue;
+  const int NRp = nrhs <= 1 ? 1 : nrhs <= 2 ? 2 : 4;  // (8 right-hand sides would spill in FP64)
+  if ((nrhs + NRp - 1) / NRp > 65535) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((n + nb - 1) / nb), (unsigned)((nrhs + NRp - 1) / NRp), (unsigned)nbatch);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(1024), 0, st, n, nb, static_cast<const cplx<T>*>(A), lda,
+                       static_cast<cplx<T>*>(x), ldb, nrhs, sA, sB);
+  };
+  if (lower) {
+    if (NRp == 1) go(skinny_diag_t_kernel<T, 1, true>);
+    else if (NRp == 2) go(skinny_diag_t_kernel<T, 2, true>);
+    else go(skinny_diag_t_kernel<T, 4, true>);
+  } else {
+    if (NRp == 1) go(skinny_diag_t_kernel<T, 1, false>);
+    else if (NRp == 2) go(skinny_diag_t_kernel<T, 2, false>);
+    else go(skinny_diag_t_kernel<T, 4, false>);
+  }
+  return hipGetLastError();
+}
+#define GDM_INST(T)                                                                                                       \
+  template hipError_t launch_skinny_push<T>(int, int64_t, const void*, int64_t, const void*, void*, int64_t, int64_t,    \
+                                            hipStream_t, int, int64_t, int64_t);                                          \
+  template hipError_t launch_skinny_diag_t<T>(bool, int64_t, int, const void*, int64_t, void*, int64_t, int64_t,         \
+                                              hipStream_t, int, int64_t, int64_t);
+GDM_INST(double)
+GDM_INST(float)
+#undef GDM_INST
 
 int64_t skinny_t_chunks(int64_t k0, int64_t k1) {
   return (k0 + SK_KC - 1) / SK_KC + (k1 + SK_KC - 1) / SK_KC;

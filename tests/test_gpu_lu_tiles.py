@@ -158,3 +158,22 @@ def test_row_norm_edges(ctx, cells):
     res = np.abs(f0[0] - M @ x).max()
     be = res / (np.abs(M).sum(1).max() * np.abs(x).max() + np.abs(f0).max())
     assert abs(ctx.info.backward_err - be) <= 1e-6 * be + 1e-15, (ctx.info.backward_err, be)
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("n,nrhs", [(1, 1), (64, 2), (65, 4), (127, 1), (129, 5), (140, 8), (300, 9), (513, 1), (700, 20)])
+def test_few_column_steps(ctx, n, nrhs, dtype):
+    """Both solves with 1, 2, 4 and 8 columns at a time, remainders of them, and
+    the edges of 64 rows, 4 columns and 128-wide blocks: the bound above."""
+    rng = np.random.default_rng(n + nrhs)
+    A = 2 * np.eye(n) + (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(2 * n)
+    A = A[rng.permutation(n)]
+    B = rng.standard_normal((nrhs, n)) + 1j * rng.standard_normal((nrhs, n))
+    F = torch.as_tensor(A.T.copy()).to(device="cuda", dtype=dtype).contiguous()
+    ctx.getrf(F)
+    for trans in (0, 1):
+        X = torch.as_tensor(B).to(device="cuda", dtype=dtype).contiguous()
+        ctx.getrs(F, X, trans)
+        ref = np.linalg.solve(A.T if trans else A, B.T).T
+        err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert err.max() <= 8 * max(n, 16) * (2.2e-16 if dtype == torch.complex128 else 1.2e-7), (trans, err)
