@@ -484,9 +484,12 @@ static bool batch_shape_for(gdm_ctx* c, int64_t n, int B, int nb_max, bool ir, B
   const int eb = ir ? 4 : 8;
   sh.n = n;
   sh.B = B;
-  sh.plan = lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, panel_pb(c, true));
+  const int pb = panel_pb(c, true);
+  sh.plan = lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, pb);
   sh.nb = sh.plan.nb;
-  return sh.plan.nb >= 32 && lu_plan_fits(sh.plan) && sh.plan.max_wg * B <= c->num_cu;
+  // (group sizes are those whose searching panels would fit, also for speculative ones)
+  const LUPlan search = pb ? sh.plan : lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, 1);
+  return search.nb >= 32 && lu_plan_fits(search) && search.max_wg * B <= c->num_cu;
 }
 
 static size_t batch_item_bytes(int64_t n, bool ir) { return (size_t)n * n * (ir ? 24 : 16); }

@@ -169,3 +169,20 @@ def test_batch_full_config3_vs_golden(ctx):
     err = np.max(np.abs(got - ref["cs"]) / np.abs(ref["cs"]))
     assert err < 1e-10, err
     assert float(be.max()) <= 1e-14
+
+
+def test_batch_of_more_rows_than_search_panels_hold(ctx):
+    """16 systems of n = 2550: 128-wide speculative blocks, which a pivot search of
+    16 systems at a time would not fit; two items against the oracle."""
+    structs = [gi.box_cells(np.array([50.0, 50.0, 42.0]), 10.0)[:850]]
+    wl = np.linspace(450.0, 800.0, 16)
+    eps = (2.2 + 0.05j * np.arange(16))[None, :]
+    khat, e0 = gi.normal_incidence_xy()
+    ctx.set_environment(1.0)
+    before = ctx.pivot_fallbacks()
+    cs, be = ctx.batch_spectra(structs, 10.0, wl, eps, khat, e0, prec=1)
+    assert ctx.pivot_fallbacks() == before and bool((be <= 1e-14).all())
+    for l in (0, 13):
+        ref = oracle_cs(structs[0], 10.0, eps[0, l], wl[l], khat, e0)
+        # (relative to the extinction: the first item absorbs nothing, the difference of two equal numbers)
+        assert np.max(np.abs(cs[0, l].cpu().numpy() - ref) / ref[:, :1]) < 1e-10
