@@ -232,7 +232,13 @@ template <typename T>
 static gdm_status run_lu(gdm_ctx* c, void* A, int64_t n, int64_t ld, LUPlan& plan, DevBuf& ws, DevBuf& ipiv,
                          int32_t* ipiv_out, gdm_info* info, const std::function<hipError_t()>& rebuild = nullptr) {
   plan = lu_plan(n, (int)sizeof(T), c->num_cu, c->lds_bytes, 1, 128, panel_pb(c, (bool)rebuild));
-  const size_t wsb = lu_workspace_bytes(plan, (int)sizeof(T), c->num_cu);
+  size_t wsb = lu_workspace_bytes(plan, (int)sizeof(T), c->num_cu);
+  LUPlan search;  // the plan that a failed speculative factorisation is repeated with
+  if (plan.spec) {
+    search = lu_plan(n, (int)sizeof(T), c->num_cu, c->lds_bytes, 1, 128, 1);
+    if (!lu_plan_fits(search)) HIPCHK(c, hipErrorInvalidValue);
+    wsb = std::max(wsb, lu_workspace_bytes(search, (int)sizeof(T), c->num_cu));
+  }
   HIPCHK(c, ws.ensure(wsb));
   LUWork w;
   lu_workspace_carve(ws.p, plan, (int)sizeof(T), c->num_cu, w);
@@ -258,7 +264,9 @@ static gdm_status run_lu(gdm_ctx* c, void* A, int64_t n, int64_t ld, LUPlan& pla
     c->spec_first_failed_block = (int32_t)(failed - flags.begin());
     ++c->pivot_fallbacks;
     HIPCHK(c, rebuild());
-    plan.spec = false;
+    plan = search;
+    lu_workspace_carve(ws.p, plan, (int)sizeof(T), c->num_cu, w);
+    w.events = &c->lu_events;
     HIPCHK(c, lu_factor<T>(A, ld, plan, w, piv, c->stream, &c->prof, c->lookahead ? c->side : nullptr));
     HIPCHK(c, hipMemcpyAsync(err, w.err, sizeof(err), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -1546,11 +1546,12 @@ LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch,
   const int avail = pb > 1 ? std::max(1, 32 * p.max_wg / 33) : p.max_wg;
   const int cbytes = 2 * elem_bytes;
   int nb = nb_max >= 16 && nb_max <= 128 ? nb_max : 128;
-  // the panel must fit: ceil(n / avail) rows x nb columns in LDS (a batch's
-  // speculative panels do not: its failed items are factored again one by one, so
-  // the plan never searches pivots.  128 instead of 64 columns halve the traffic of
-  // the updates: spectra of four structures up to n = 4500, 16 systems at a time: 64.9 -> 53.0 ms)
-  while (nb > 16 && !(p.spec && nbatch > 1)) {
+  // the panel must fit: ceil(n / avail) rows x nb columns in LDS (not a speculative
+  // one, which keeps no rows there; a failed factorisation is repeated with a
+  // plan of its own.  128 instead of 64 columns halve the traffic of the updates:
+  // spectra of four structures up to n = 4500, 16 systems at a time, 64.9 -> 53.0 ms;
+  // one FP32 factorisation of n = 69 000 7.5 -> 4.1 s)
+  while (nb > 16 && !p.spec) {
     const int64_t R = (n + avail - 1) / avail;
     if (R <= panel_rows_max(nb, lds_bytes, cbytes, pb)) break;
     nb /= 2;
@@ -1585,7 +1586,7 @@ LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch,
 }
 
 bool lu_plan_fits(const LUPlan& p) {
-  if (p.spec && p.nbatch > 1) return true;
+  if (p.spec) return true;
   for (const LUBlock& b : p.blocks)
     if (b.G + (p.pb > 1 ? tp_roots(b.G) : 0) > p.max_wg || (int64_t)b.G * b.R < p.n - b.k0) return false;
   return true;
@@ -1716,7 +1717,7 @@ hipError_t lu_prepare(const LUPlan& plan) {
       diag_set = true;
     }
   }
-  if (plan.spec && plan.nbatch > 1) return hipSuccess;
+  if (plan.spec) return hipSuccess;
   for (const LUBlock& b : plan.blocks) {
     const bool in_wave = panel_in_wave<T>(plan, b, plan.max_wg);
     const size_t need = in_wave ? panel_wave_lds<cplx<T>>(b.w, b.R) : panel_lds_bytes(b.w, b.R, sizeof(cplx<T>), plan.pb);
