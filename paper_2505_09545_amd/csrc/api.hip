@@ -532,7 +532,7 @@ static gdm_status batch_enqueue_group(gdm_ctx* c, const BatchShape& sh, const Ba
     if (e != hipSuccess) return e;
     if (npw <= SKINNY_MAX_RHS)
       return launch_skinny_n_long<double>(n, n, b.M64, n, b.X, n, b.R, n, npw, b.part, b.part_elems, st, B, nn, sv, sv);
-    return launch_gemm<double>(0, 0, n, npw, n, b.M64, n, b.X, n, b.R, n, st, GemmMask{}, B, nn, sv, sv);
+    return launch_gemm<double>(0, 0, n, npw, n, b.M64, n, b.X, n, b.R, n, st, B, nn, sv, sv);
   };
   if (!ir) {
     HIPCHK(c, launch_copy_d(b.F0, n, b.X, n, n, cols, st));

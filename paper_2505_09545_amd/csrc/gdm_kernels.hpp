@@ -116,20 +116,16 @@ hipError_t launch_assemble(const DipoleView& d, const struct Wave& w, void* M, i
 hipError_t launch_assemble_dual(const DipoleView& d, const struct Wave& w, double2* M64, float2* M32, int64_t ld,
                                 hipStream_t st);
 
-// Optional operand masks: rows [ar0, ar0 + adw) of op(A) are a square block
-// (row r - ar0, column k) of which only one triangle is read (kind below); a
-// B mask keeps the triangle of B (row k, column j).  Masked-out elements read
-// as zero.
-enum { GEMM_MASK_NONE = 0, GEMM_MASK_STRICT_LOWER = 1, GEMM_MASK_UPPER = 2, GEMM_MASK_LOWER = 3,
-       GEMM_MASK_STRICT_UPPER = 4 };
+// A block step of the solves: rows [ar0, ar0 + adw) of A are a square block (row
+// r - ar0, column k) of which only one triangle is read (the rest counts as zero).
+enum { GEMM_MASK_NONE = 0, GEMM_MASK_STRICT_LOWER = 1, GEMM_MASK_UPPER = 2, GEMM_MASK_STRICT_UPPER = 3 };
 struct GemmMask {
   int akind = 0;
   int64_t ar0 = 0, adw = 0;
-  int bkind = 0;
-  // Optional second destination (launch_gemm only): rows [ar0, ar0 + adw) of
-  // the result go to c2 (row r - ar0, leading dimension ldc2, item stride sc2)
-  // instead of C; mode 0 still reads their old values from C.  With it a
-  // product may read its B operand from those rows of C in place.
+  // Optional second destination: rows [ar0, ar0 + adw) of the result go to c2
+  // (row r - ar0, leading dimension ldc2, item stride sc2) instead of C; their
+  // old values still come from C.  With it a product may read its X operand from
+  // those rows of C in place.
   void* c2 = nullptr;
   int64_t ldc2 = 0, sc2 = 0;
 };
@@ -139,8 +135,7 @@ struct GemmMask {
 // nbatch > 1: independent products, item z at A + z sA, B + z sB, C + z sC.
 template <typename T>
 hipError_t launch_gemm(int mode, int transA, int64_t m, int64_t n, int64_t k, const void* A, int64_t lda,
-                       const void* B, int64_t ldb, void* C, int64_t ldc, hipStream_t st, GemmMask mk = GemmMask{},
-                       int nbatch = 1, int64_t sA = 0, int64_t sB = 0, int64_t sC = 0);
+                       const void* B, int64_t ldb, void* C, int64_t ldc, hipStream_t st, int nbatch = 1, int64_t sA = 0, int64_t sB = 0, int64_t sC = 0);
 // C = A B on the 3M kernel (64 x 64 tiles; no masks, no transpose); nbatch
 // independent products, item z at A + z sA, B + z sB, C + z sC.
 template <typename T>

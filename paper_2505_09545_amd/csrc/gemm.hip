@@ -1,7 +1,8 @@
 // Complex GEMM on the CDNA matrix cores, used for the trailing update of the
 // blocked right-looking LU (arXiv:2505.09545, Sec. "Numerical solution": the
-// coupled system is solved by LU decomposition), for the blocked triangular
-// solves and for the FP64 residual of iterative refinement.
+// coupled system is solved by LU decomposition; FP32 updates of blocks of 64 or
+// 128 columns have kernels of their own) and for the FP64 residual of iterative
+// refinement.
 //
 // Storage: column-major, interleaved complex.  Viewed as real matrices, an
 // m x k complex A is a 2m x k real matrix whose rows alternate (re, im).  The
@@ -57,18 +58,6 @@ template <> struct acc_of<float> { using type = v4f; };
 __device__ inline v4d mfma16(double a, double b, v4d c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 __device__ inline v4f mfma16(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-// Operand masks (used by the triangular-block solves): an element (r, c) of a
-// masked square block is kept iff the relation holds, else read as zero.
-__device__ inline bool mask_keep(int kind, int64_t r, int64_t c) {
-  switch (kind) {
-    case GEMM_MASK_STRICT_LOWER: return r > c;
-    case GEMM_MASK_UPPER: return r <= c;
-    case GEMM_MASK_LOWER: return r >= c;
-    case GEMM_MASK_STRICT_UPPER: return r < c;
-    default: return true;
-  }
-}
-
 // Order of the output tiles: the tile columns are cut into NBLK blocks (8 or
 // 16: one or two per XCD range of the remap) and each block is walked by
 // groups of GM tile rows, a group covering all of the block's columns before
@@ -98,7 +87,7 @@ template <typename T, int MODE, int TRANSA, int ROLE, int WM, int WN, int BK, bo
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) cgemm_kernel(int64_t m, int64_t n, int64_t k, const cplx<T>* __restrict__ A,
                                                      int64_t lda, const cplx<T>* __restrict__ B, int64_t ldb,
                                                      cplx<T>* __restrict__ C, int64_t ldc, int tiles_m, int tiles,
-                                                     GemmMask mk, int64_t sA, int64_t sB, int64_t sC) {
+                                                     int64_t sA, int64_t sB, int64_t sC) {
   using CT = cplx<T>;
   constexpr int BM = 16 * WM;  // complex rows per tile
   constexpr int BN = 32 * WN;  // columns per tile
@@ -145,9 +134,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
       const int64_t gm = m0 + mc, gk = kb + kc;
       CT v;
       v.x = 0; v.y = 0;
-      bool keep = gm < m && gk < k;
-      if (mk.akind && gm >= mk.ar0 && gm < mk.ar0 + mk.adw) keep = keep && mask_keep(mk.akind, gm - mk.ar0, gk);
-      if (keep) v = TRANSA == 0 ? A[gm + gk * lda] : A[gk + gm * lda];
+      if (gm < m && gk < k) v = TRANSA == 0 ? A[gm + gk * lda] : A[gk + gm * lda];
       ra[i] = v;
     }
 #pragma unroll
@@ -157,9 +144,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
       const int64_t gn = n0 + nc, gk2 = kb + kc2;
       CT u;
       u.x = 0; u.y = 0;
-      bool keepb = gn < n && gk2 < k;
-      if (mk.bkind) keepb = keepb && mask_keep(mk.bkind, gk2, gn);
-      if (keepb) u = B[gk2 + gn * ldb];
+      if (gn < n && gk2 < k) u = B[gk2 + gn * ldb];
       rb[i] = u;
     }
   };
@@ -269,12 +254,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
     }
   }
   // epilogue: lane holds real rows 4*lk + {0..3} = two complex rows of column lane%16
-  // (general products only: rows [ar0, ar0 + adw) optionally written to mk.c2)
-  CT* const c2 = ROLE == 0 && mk.c2 ? static_cast<CT*>(mk.c2) + (int64_t)blockIdx.y * mk.sc2 : nullptr;
-  auto dest = [&](int64_t row, int64_t col) -> CT* {
-    if (ROLE == 0 && c2 && row >= mk.ar0 && row < mk.ar0 + mk.adw) return c2 + (row - mk.ar0) + col * mk.ldc2;
-    return C + row + col * ldc;
-  };
   if constexpr (MODE == 0 && (CB || NST > 0)) {
     // Every C load issued before the first store (a load after a store to the
     // same array waits for it, since the compiler cannot tell the addresses
@@ -294,7 +273,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
           CT c = cold[bm][bn][h];
           c.x -= acc[bm][bn][2 * h];
           c.y -= acc[bm][bn][2 * h + 1];
-          *dest(row, col) = c;
+          C[row + col * ldc] = c;
         }
     return;
   }
@@ -314,12 +293,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
           CT c = C[row + col * ldc];
           c.x -= vr;
           c.y -= vi;
-          *dest(row, col) = c;
+          C[row + col * ldc] = c;
         } else {
           CT c;
           c.x = vr;
           c.y = vi;
-          *dest(row, col) = c;
+          C[row + col * ldc] = c;
         }
       }
     }
@@ -531,7 +510,7 @@ static int gemm_num_cu() {
 // Launch with the tile shape (WM, WN, BK); tile counts checked by the caller's shape.
 template <typename T, int MODE, int TRANSA, int ROLE, int WM, int WN, int BK, int NST = 0>
 static hipError_t launch_tiles(int64_t m, int64_t n, int64_t k, const cplx<T>* a, int64_t lda, const cplx<T>* b,
-                               int64_t ldb, cplx<T>* c, int64_t ldc, hipStream_t st, GemmMask mk, int nbatch,
+                               int64_t ldb, cplx<T>* c, int64_t ldc, hipStream_t st, int nbatch,
                                int64_t sA, int64_t sB, int64_t sC) {
   const int64_t tm = (m + 16 * WM - 1) / (16 * WM), tn = (n + 32 * WN - 1) / (32 * WN);
   if (tm * tn > INT32_MAX) return hipErrorInvalidValue;
@@ -540,10 +519,10 @@ static hipError_t launch_tiles(int64_t m, int64_t n, int64_t k, const cplx<T>* a
   // loads in flight
   if (NST == 0 && nbatch > 1)
     hipLaunchKernelGGL((cgemm_kernel<T, MODE, TRANSA, ROLE, WM, WN, BK, true>), dim3(tiles, nbatch), dim3(256), 0, st, m,
-                       n, k, a, lda, b, ldb, c, ldc, (int)tm, tiles, mk, sA, sB, sC);
+                       n, k, a, lda, b, ldb, c, ldc, (int)tm, tiles, sA, sB, sC);
   else
     hipLaunchKernelGGL((cgemm_kernel<T, MODE, TRANSA, ROLE, WM, WN, BK, false, NST>), dim3(tiles, nbatch), dim3(256), 0,
-                       st, m, n, k, a, lda, b, ldb, c, ldc, (int)tm, tiles, mk, sA, sB, sC);
+                       st, m, n, k, a, lda, b, ldb, c, ldc, (int)tm, tiles, sA, sB, sC);
   return hipGetLastError();
 }
 
@@ -555,30 +534,29 @@ static bool use_small_tiles(int64_t m, int64_t n, int nbatch) {
 
 template <typename T, int MODE, int TRANSA, int ROLE>
 static hipError_t launch_cfg(int64_t m, int64_t n, int64_t k, const cplx<T>* a, int64_t lda, const cplx<T>* b,
-                             int64_t ldb, cplx<T>* c, int64_t ldc, hipStream_t st, GemmMask mk, int nbatch, int64_t sA,
+                             int64_t ldb, cplx<T>* c, int64_t ldc, hipStream_t st, int nbatch, int64_t sA,
                              int64_t sB, int64_t sC) {
   if (use_small_tiles(m, n, nbatch)) {
     // one system's products over k >= 64 with 16 complex k per stage: half the
     // stages of their latency-bound k loop (32 measured the same); the batched
     // launches keep 8
     if (nbatch == 1 && k >= 64 && k <= 128 && GEMM_SMALL_PREFETCH)
-      return launch_tiles<T, MODE, TRANSA, ROLE, 2, 1, 16, sizeof(T) == 8 ? 4 : 8>(m, n, k, a, lda, b, ldb, c, ldc, st,
-                                                                                mk, nbatch, sA, sB, sC);
+      return launch_tiles<T, MODE, TRANSA, ROLE, 2, 1, 16, sizeof(T) == 8 ? 4 : 8>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
     if (nbatch == 1 && k >= 64)
-      return launch_tiles<T, MODE, TRANSA, ROLE, 2, 1, 16>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
-    return launch_tiles<T, MODE, TRANSA, ROLE, 2, 1, 8>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
+      return launch_tiles<T, MODE, TRANSA, ROLE, 2, 1, 16>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
+    return launch_tiles<T, MODE, TRANSA, ROLE, 2, 1, 8>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
   }
   // 4 complex k per stage for the products of one system (update GEMM: FP32
   // 87.5 -> 90, FP64 40 -> 45 TFLOP/s; FP64 step 158.6 -> 148.8 ms), 8 for
   // batched launches (83 vs 78 systems/s on the batched spectra)
   if (nbatch == 1)
-    return launch_tiles<T, MODE, TRANSA, ROLE, 4, 2, 4>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
-  return launch_tiles<T, MODE, TRANSA, ROLE, 4, 2, 8>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
+    return launch_tiles<T, MODE, TRANSA, ROLE, 4, 2, 4>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
+  return launch_tiles<T, MODE, TRANSA, ROLE, 4, 2, 8>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
 }
 
 template <typename T>
 hipError_t launch_gemm(int mode, int transA, int64_t m, int64_t n, int64_t k, const void* A, int64_t lda,
-                       const void* B, int64_t ldb, void* C, int64_t ldc, hipStream_t st, GemmMask mk, int nbatch,
+                       const void* B, int64_t ldb, void* C, int64_t ldc, hipStream_t st, int nbatch,
                        int64_t sA, int64_t sB, int64_t sC) {
   if (m <= 0 || n <= 0 || nbatch <= 0) return hipSuccess;
   if (nbatch > 65535) return hipErrorInvalidValue;
@@ -586,10 +564,10 @@ hipError_t launch_gemm(int mode, int transA, int64_t m, int64_t n, int64_t k, co
   const auto* b = static_cast<const cplx<T>*>(B);
   auto* c = static_cast<cplx<T>*>(C);
   if (k <= 0 && mode == 0) return hipSuccess;  // C - 0
-  if (mode == 0 && transA == 0) return launch_cfg<T, 0, 0, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
-  if (mode == 0) return launch_cfg<T, 0, 1, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
-  if (transA == 0) return launch_cfg<T, 1, 0, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
-  return launch_cfg<T, 1, 1, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, mk, nbatch, sA, sB, sC);
+  if (mode == 0 && transA == 0) return launch_cfg<T, 0, 0, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
+  if (mode == 0) return launch_cfg<T, 0, 1, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
+  if (transA == 0) return launch_cfg<T, 1, 0, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
+  return launch_cfg<T, 1, 1, 0>(m, n, k, a, lda, b, ldb, c, ldc, st, nbatch, sA, sB, sC);
 }
 
 // The FP32 update with the 64 x 64 tile: 3M products (cgemm3m_update_kernel).
@@ -649,7 +627,7 @@ hipError_t launch_gemm_update(int64_t m, int64_t n, int64_t k, const void* A, in
   // 32 x 32 tiles 22.7)
   if (nbatch == 1 && k <= 128) return launch_solve_step<T>(m, k, A, lda, B, ldb, C, ldc, n, st);
   return launch_cfg<T, 0, 0, 1>(m, n, k, static_cast<const cplx<T>*>(A), lda, static_cast<const cplx<T>*>(B), ldb,
-                                static_cast<cplx<T>*>(C), ldc, st, GemmMask{}, nbatch, sA, sB, sC);
+                                static_cast<cplx<T>*>(C), ldc, st, nbatch, sA, sB, sC);
 }
 template hipError_t launch_gemm_update<double>(int64_t, int64_t, int64_t, const void*, int64_t, const void*, int64_t,
                                                void*, int64_t, hipStream_t, int, int64_t, int64_t, int64_t);
@@ -657,8 +635,8 @@ template hipError_t launch_gemm_update<float>(int64_t, int64_t, int64_t, const v
                                               void*, int64_t, hipStream_t, int, int64_t, int64_t, int64_t);
 
 template hipError_t launch_gemm<double>(int, int, int64_t, int64_t, int64_t, const void*, int64_t, const void*,
-                                        int64_t, void*, int64_t, hipStream_t, GemmMask, int, int64_t, int64_t, int64_t);
+                                        int64_t, void*, int64_t, hipStream_t, int, int64_t, int64_t, int64_t);
 template hipError_t launch_gemm<float>(int, int, int64_t, int64_t, int64_t, const void*, int64_t, const void*,
-                                       int64_t, void*, int64_t, hipStream_t, GemmMask, int, int64_t, int64_t, int64_t);
+                                       int64_t, void*, int64_t, hipStream_t, int, int64_t, int64_t, int64_t);
 
 }  // namespace gdm

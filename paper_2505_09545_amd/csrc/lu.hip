@@ -39,12 +39,6 @@ namespace gdm {
 
 constexpr uint32_t SPIN_LIMIT = 1u << 22;
 
-__device__ inline unsigned long long shfl_xor_u64(unsigned long long v, int m) {
-  const unsigned lo = __shfl_xor((unsigned)(v & 0xffffffffu), m);
-  const unsigned hi = __shfl_xor((unsigned)(v >> 32), m);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
 __global__ void zero_u64_kernel(unsigned long long* a, size_t na, unsigned long long* b, size_t nb,
                                 int32_t* c, size_t nc) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;

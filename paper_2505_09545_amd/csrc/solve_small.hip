@@ -34,7 +34,6 @@ __device__ inline bool sk_keep(int kind, int64_t r, int64_t c) {
   switch (kind) {
     case GEMM_MASK_STRICT_LOWER: return r > c;
     case GEMM_MASK_UPPER: return r <= c;
-    case GEMM_MASK_LOWER: return r >= c;
     case GEMM_MASK_STRICT_UPPER: return r < c;
     default: return true;
   }
