@@ -30,20 +30,21 @@ import numpy as np
 PEAK_FP32_MFMA = 157.3   # TFLOP/s, MI355X dense FP32 matrix
 PEAK_FP64_MFMA = 78.6    # TFLOP/s, MI355X dense FP64 matrix
 PEAK_HBM = 8000.0        # GB/s
+UPDATE_BYTES_PER_FLOP = 16.0 / (8 * 128)  # a complex float read and written per 128 complex products
 
 
 def update_gemm_traffic():
-    """HBM bytes per launch of the trailing-update GEMM from the committed
-    rocprofv3 FETCH_SIZE / WRITE_SIZE summary, or None if the GEMM source has
-    changed since those counters were taken."""
+    """HBM bytes per launch of the trailing update from the committed
+    rocprofv3 FETCH_SIZE / WRITE_SIZE summary, or None if the update's source
+    has changed since those counters were taken."""
     import hashlib
     here = os.path.dirname(os.path.abspath(__file__))
     try:
         rec = json.load(open(os.path.join(here, "profiles", "update_gemm_fp32_n12000_traffic.json")))
-        src = open(os.path.join(here, "paper_2505_09545_amd", "csrc", "gemm.hip"), "rb").read()
+        src = open(os.path.join(here, "paper_2505_09545_amd", "csrc", "update_split.hip"), "rb").read()
     except OSError:
         return None
-    if hashlib.sha256(src).hexdigest() != rec.get("gemm_source_sha256"):
+    if hashlib.sha256(src).hexdigest() != rec.get("source_sha256"):
         return None
     return rec["bytes_per_launch"]
 
@@ -479,10 +480,14 @@ def main() -> int:
         "ir_iters": ir_iters,
         "backward_err": be,
         **res,
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_MFMA, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_MFMA, "traffic": update_gemm_traffic(),
-                     "kernel": "cgemm3m_update_kernel (LU trailing update, bulk: the columns after the next "
-                               "panel's, side stream; the last launches with the small tile use cgemm_kernel)",
+        # the update's products run on the f16 matrix cores (three per real
+        # product, 833 TFLOP/s by the 8 m n k count); what bounds it is the
+        # traffic of the trailing matrix, 16 bytes per entry and 128 k
+        "roofline": {"bound": "hbm", "achieved": achieved * 1e3 * UPDATE_BYTES_PER_FLOP, "peak": PEAK_HBM, "unit": "GB/s",
+                     "frac": achieved * 1e3 * UPDATE_BYTES_PER_FLOP / PEAK_HBM, "traffic": update_gemm_traffic(),
+                     "tflops_8mnk": achieved,
+                     "kernel": "update_split_stream_kernel (LU trailing update, bulk: the columns after the next "
+                               "panel's, side stream; below 2e7 entries update_split_kernel)",
                      "launches_per_step": up["launches"] / args.steps,
                      "avg_launch_ms": up["ms"] / max(up["launches"], 1),
                      "flops_per_launch": up["work"] / max(up["launches"], 1)},

@@ -447,9 +447,8 @@ gdm_status gdm_profile_mask(gdm_ctx* ctx, int32_t mask);
  * pairs x n_rhs), 10 LU trailing-update GEMM of the next panel's columns (the
  * look-ahead product; work = real flops), 11 matrix-free product of
  * gdm_solve_iterative (work = dipole pairs x n_rhs), 12 the rest of a
- * speculative panel: L21 = A21 U11^-1 (the triangle's inverse and the
- * product) and the pivot check (work = real flops 8 (n - k) w^2 of the
- * product). */
+ * speculative panel: L21 = A21 U11^-1 and the pivot check, with U12 where one
+ * launch does both (work = real flops 8 w^2 per row and column). */
 gdm_status gdm_profile_read(gdm_ctx* ctx, double* out, int32_t n_out);
 
 #ifdef __cplusplus
