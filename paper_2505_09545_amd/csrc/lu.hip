@@ -474,7 +474,7 @@ __global__ void __launch_bounds__(256) panel_kernel(cplx<T>* __restrict__ A, int
 // What bounds it is the chain of a column: the key's trip through memory to
 // workgroups on other dies (0.75 us of waiting behind the rank-1 update that it
 // overlaps), the load of the winner's row (0.4) and the choice of the next
-// candidate (0.35).  n = 3001: 2.6 us per column in FP32, 2.9 in FP64; panel_kernel,
+// candidate (0.35).  n = 3001: 2.5 us per column in FP32, 2.8 in FP64; panel_kernel,
 // with three barriers per column and all remaining columns updated from LDS, 2.9
 // and 5.1.  (Any 24 to 56 rows per workgroup measure the same.)
 //
@@ -686,16 +686,17 @@ __global__ void __launch_bounds__(256) panel_wave_kernel(cplx<T>* __restrict__ A
     const uint32_t E = epoch0 + (uint32_t)(c1 - 1);
     u64* const uw = ubase + (size_t)sp * SUBW * ws.wwmax;
     const int words = rest * NW;
-    for (int i = 0; i < SUBW; ++i) {
-      const int lr = mine[i];
-      if (lr < 0) continue;
+    const int own = mine[lane % SUBW];
+    const uint32_t ours = (uint32_t)__ballot(own >= 0) & ((1u << SUBW) - 1);  // pivots that are rows of this workgroup
+    for (uint32_t left = ours; left; left &= left - 1) {
+      const int i = __builtin_ctz(left), lr = __builtin_amdgcn_readlane(own, i);
       for (int t = tid; t < words; t += 256)
         ll_put(uw + (size_t)i * ws.wwmax + t, E, reinterpret_cast<const uint32_t*>(tile + (size_t)(c1 + t / NW) * R + lr)[t % NW]);
     }
     {
       // wave v reads rows 4 v .. 4 v + 3, 64 B words of each in flight together
       uint32_t* const dst = reinterpret_cast<uint32_t*>(ub);
-      constexpr int B = 3;
+      constexpr int B = 4;  // one round trip for 112 columns in FP32, two in FP64
       for (int t0 = 0; t0 < words; t0 += 64 * B) {
         const u64* p[4 * B];
         uint32_t v[4 * B];
@@ -729,10 +730,9 @@ __global__ void __launch_bounds__(256) panel_wave_kernel(cplx<T>* __restrict__ A
     }
     __syncthreads();
     const int32_t last = (int32_t)(k0 + c1 - 1);
-    for (int i = 0; i < SUBW; ++i) {
-      const int lr = mine[i];
-      if (lr >= 0)
-        for (int c = tid; c < rest; c += 256) tile[(size_t)(c1 + c) * R + lr] = ub[i * restmax + c];
+    for (uint32_t left = ours; left; left &= left - 1) {
+      const int i = __builtin_ctz(left), lr = __builtin_amdgcn_readlane(own, i);
+      for (int c = tid; c < rest; c += 256) tile[(size_t)(c1 + c) * R + lr] = ub[i * restmax + c];
     }
     // rank-SUBW update of the rows still active: 16 x 16 tiles dealt to the waves
     {
