@@ -54,6 +54,8 @@ typedef enum {
   GDM_E_STATE = 7            /* call order violated (e.g. solve before factorize) */
 } gdm_status;
 
+/* (FP32_IR: the factors are held in FP32; the products of their trailing updates
+ * take operands split into two 16-bit numbers, 23 bits together.) */
 typedef enum { GDM_PREC_FP64 = 0, GDM_PREC_FP32_IR = 1 } gdm_precision;
 
 /* Self-term of the cubic mesh cells.  STATIC is the paper's
@@ -410,7 +412,8 @@ int32_t gdm_batch_tuning(const gdm_ctx* ctx, int32_t* out, int32_t max_entries);
  * column-major n x n, leading dimension lda, factored in place; ipiv [n]
  * receives 0-based pivot rows.  The factors are in the library's factored form
  * (row interchanges applied right of each block only) and are meant for
- * gdm_getrs with the same context, which keeps the block permutations. */
+ * gdm_getrs with the same context, which keeps the block permutations.  All
+ * products are in the matrix's own precision. */
 gdm_status gdm_getrf(gdm_ctx* ctx, int dtype, int64_t n, void* A, int64_t lda, int32_t* ipiv, gdm_info* info);
 /* Solve op(A) X = B in place with the factors of the last gdm_getrf on this
  * context (trans 0: A, 1: A^T without conjugation); B n x nrhs, ldb >= n. */

@@ -227,15 +227,17 @@ static int panel_pb(const gdm_ctx* c, bool can_rebuild) {
 }
 
 // rebuild (may be null): writes the matrix into A again, so that a speculative
-// factorisation whose check failed can be repeated with the pivot search.
+// factorisation whose check failed can be repeated with the pivot search.  Where
+// it can, the matrix stays at hand and FP32 factors are refined on it.
 template <typename T>
 static gdm_status run_lu(gdm_ctx* c, void* A, int64_t n, int64_t ld, LUPlan& plan, DevBuf& ws, DevBuf& ipiv,
                          int32_t* ipiv_out, gdm_info* info, const std::function<hipError_t()>& rebuild = nullptr) {
-  plan = lu_plan(n, (int)sizeof(T), c->num_cu, c->lds_bytes, 1, 128, panel_pb(c, (bool)rebuild));
+  const bool refined = (bool)rebuild;
+  plan = lu_plan(n, (int)sizeof(T), c->num_cu, c->lds_bytes, 1, 128, panel_pb(c, (bool)rebuild), refined);
   size_t wsb = lu_workspace_bytes(plan, (int)sizeof(T), c->num_cu);
   LUPlan search;  // the plan that a failed speculative factorisation is repeated with
   if (plan.spec) {
-    search = lu_plan(n, (int)sizeof(T), c->num_cu, c->lds_bytes, 1, 128, 1);
+    search = lu_plan(n, (int)sizeof(T), c->num_cu, c->lds_bytes, 1, 128, 1, refined);
     if (!lu_plan_fits(search)) HIPCHK(c, hipErrorInvalidValue);
     wsb = std::max(wsb, lu_workspace_bytes(search, (int)sizeof(T), c->num_cu));
   }
@@ -493,7 +495,7 @@ static bool batch_shape_for(gdm_ctx* c, int64_t n, int B, int nb_max, bool ir, B
   sh.n = n;
   sh.B = B;
   const int pb = panel_pb(c, true);
-  sh.plan = lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, pb);
+  sh.plan = lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, pb, ir);
   sh.nb = sh.plan.nb;
   // (group sizes are those whose searching panels would fit, also for speculative ones)
   const LUPlan search = pb ? sh.plan : lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, 1);

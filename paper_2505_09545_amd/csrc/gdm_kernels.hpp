@@ -250,6 +250,7 @@ struct LUPlan {
   int nbatch = 1;         // systems factored together
   int64_t lds_bytes = 0;  // LDS of a CU
   bool spec = false;  // speculative panels (diagonal pivots checked against partial pivoting; pb = 1 plan)
+  bool split = false;  // FP32: trailing updates from operands split in two f16 (update_split.hip)
   std::vector<LUBlock> blocks;
 };
 
@@ -284,7 +285,13 @@ struct LUWork {
 // pivots; 2, 4 or 8: tournament pivoting, reduced when the candidates of the
 // widest panel would exceed 1024 or its rows would not fit the LDS; 0:
 // speculative panels, a partial-pivoting plan with `spec` set).
-LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch = 1, int nb_max = 128, int pb = 1);
+// refined: the factors serve solves that are refined on the matrix in FP64, so
+// that FP32 updates may take split operands, whose error is bounded by the
+// largest entries of a row of L and a column of U (update_split.hip).  Factors of
+// a caller's matrix have nothing behind them: their updates are FP32 products,
+// accurate entry by entry whatever the scales of rows and columns.
+LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch = 1, int nb_max = 128, int pb = 1,
+               bool refined = false);
 // one-time host-side kernel settings for a plan (call before graph capture)
 template <typename T>
 hipError_t lu_prepare(const LUPlan& plan);

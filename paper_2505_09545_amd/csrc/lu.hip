@@ -1523,7 +1523,7 @@ static int64_t panel_rows_max(int w, int64_t lds_bytes, int cbytes, int pb) {
 // root workgroups of a tournament panel over G row workgroups
 static int tp_roots(int G) { return (G + 31) / 32; }
 
-LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch, int nb_max, int pb) {
+LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch, int nb_max, int pb, bool refined) {
   LUPlan p;
   p.n = n;
   if (nbatch < 1) nbatch = 1;
@@ -1551,6 +1551,8 @@ LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch,
     nb /= 2;
   }
   p.nb = nb;
+  // (whole blocks of 128 or 64 columns; the planes hold no others)
+  p.split = refined && elem_bytes == 4 && (nb == 128 || nb == 64) && nb < n;
   // Workgroups of one panel.  Measured on n = 12 000: an FP32 panel over at most
   // 128 CUs is as fast per column as one over all 256 and leaves the other CUs
   // to the look-ahead update (140 vs 150 ms per factorisation + solve step); an
@@ -1638,9 +1640,8 @@ void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu,
   w.tmp = take((size_t)nbatch * w.s_tmp * cb);
   w.s_tinv = (int64_t)(al256(nblk * (size_t)tinv_block_elems(p.nb) * cb) / cb);
   w.tinv = take((size_t)nbatch * w.s_tinv * cb);
-  // split operands of the FP32 trailing updates (whole blocks of 128 or 64; the
-  // updates read whole 128-wide tiles from any multiple of 64 columns on)
-  w.s_split = elem_bytes == 4 && (p.nb == 128 || p.nb == 64) && (int64_t)nb < p.n ? split_bytes(p.n - (int64_t)nb + 128, p.nb) : 0;
+  // split operands (the updates read whole 128-wide tiles from any multiple of 64 columns on)
+  w.s_split = p.split ? split_bytes(p.n - (int64_t)nb + 128, p.nb) : 0;
   w.split = reinterpret_cast<unsigned char*>(w.s_split ? take((size_t)nbatch * 3 * w.s_split) : nullptr);
   w.events = nullptr;
   w.bytes = off + 256;
@@ -1830,10 +1831,10 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
       if ((r = hipGetLastError()) != hipSuccess) return r;
       return P.end(s);
     };
-    // FP32 updates read split operands: L21's planes alternate between two
-    // buffers (the next panel writes its own while this step's bulk update still
-    // reads), U12's columns go to disjoint parts of one
-    const bool split_ops = ws.s_split > 0 && w == nb;
+    // split operands: L21's planes alternate between two buffers (the next panel
+    // writes its own while this step's bulk update still reads), U12's columns go
+    // to disjoint parts of one
+    const bool split_ops = plan.split && w == nb;
     const int64_t ssplit = 3 * ws.s_split, pl_bytes = split_planes_bytes(plan.n - nb + 128, nb);
     SplitOut lout, uout;
     if (split_ops) {

@@ -1,10 +1,16 @@
 // FP32 trailing update C -= L U of the blocked LU (arXiv:2505.09545, Sec.
-// "Numerical solution") on the f16 matrix cores, to FP32 accuracy.  Every row of
-// L and every column of U is scaled by a power of two (exact, undone in the
-// epilogue) so that its largest entry lies in [2^13, 2^14), and every scaled
-// entry is the sum of two f16 numbers h + l (22 to 24 significant bits, entries
-// down to 2^-16 of the row's largest; smaller ones to 2^-39 of it).  Of the four
-// products of two such sums h h' + (h l' + l h') are kept, accumulated in FP32.
+// "Numerical solution") on the f16 matrix cores, for factors whose solutions are
+// refined in FP64.  Every row of L and every column of U is scaled by a power of
+// two (exact, undone in the epilogue) so that its largest entry lies in [2^13,
+// 2^14), and every scaled entry is the sum of two f16 numbers h + l: off by at most
+// 2^-23 of the entry, or 2^-38 of the row's largest if that is more (below 2^-15
+// of it).  Of the four products of two such sums h h' + (h l' + l h') are kept,
+// accumulated in FP32.  So the error of an entry of C has, beside that of an FP32
+// product, up to 2^-38 (max_k |l_ik| sum_k |u_kj| + max_k |u_kj| sum_k |l_ik|).
+// That stays below FP32 rounding unless the rows of the matrix differ in size by
+// 2^15 and more within a block (scales of whole rows or columns of C do not
+// matter, scales along k do): a coupling matrix (A^-1 - G) A has its scales on the
+// columns, a caller's matrix may have them anywhere and takes FP32 products.
 // The f16 cores do 16 times the FP32 ones' rate, so the three products of each of
 // the four real products of a complex one cost a quarter of the 3M form in FP32
 // matrix instructions, which this replaces.  Error against 64 bits: see the
@@ -315,8 +321,8 @@ int64_t split_bytes(int64_t rows, int k) { return split_planes_bytes(rows, k) + 
 int64_t split_planes_bytes(int64_t rows, int k) { return ((rows + 127) / 128) * 4 * (int64_t)((k + 15) / 16) * 4096; }
 
 // Error against 64 bits (of one update, relative to sum |l| |u| per entry; L and U
-// Gaussian, the same with entries spread over e^(2 N), and with rows and columns
-// spread over e^(3 N) on top): rms 1.3e-8, 6.0e-8, 6.1e-8, largest of 6000 7.1e-8,
+// Gaussian, the same with entries spread over e^(2 N), and with rows of L and columns
+// of U, not k, spread over e^(3 N) on top): rms 1.3e-8, 6.0e-8, 6.1e-8, largest of 6000 7.1e-8,
 // 3.2e-7, 3.7e-7; the 3M form in FP32 instructions 2.0e-8, 9.2e-8, 9.3e-8 and
 // 1.1e-7, 7.2e-7, 6.0e-7.
 //

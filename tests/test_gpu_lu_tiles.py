@@ -177,3 +177,36 @@ def test_few_column_steps(ctx, n, nrhs, dtype):
         ref = np.linalg.solve(A.T if trans else A, B.T).T
         err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
         assert err.max() <= 8 * max(n, 16) * (2.2e-16 if dtype == torch.complex128 else 1.2e-7), (trans, err)
+
+
+@pytest.mark.parametrize("trans", [0, 1])
+@pytest.mark.parametrize("n,rows,cols", [(256, "two", 0), (700, "two", 0), (273, "spread", 0), (700, "spread", 0),
+                                         (300, "steps", 0), (273, "spread", 20), (1900, "steps", 20)])
+def test_getrf_fp32_row_scales(ctx, n, rows, cols, trans):
+    """Rows (and columns) scaled by powers of two within and across the 128-wide
+    blocks of the updates, whose products then pair small entries of L with large
+    ones of U: groups of 2^0 and 2^-30, exponents sorted from 0 to -60, halved
+    64 times a block.  The scales fall along the diagonal of 2 I + G / sqrt n, so
+    the pivots stay on it (shuffled) and every rounding is that of the unscaled
+    matrix: the bound above holds for the solution with the scales undone."""
+    rng = np.random.default_rng(n)
+    A = 2 * np.eye(n) + (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(2 * n)
+    R = {"two": np.where(np.arange(n) < 100, 0, -30), "spread": -np.sort(rng.integers(0, 61, n)),
+         "steps": -(np.arange(n) % 128) // 2 * (np.arange(n) < 128) - 64 * (np.arange(n) >= 128)}[rows]
+    R, C = 2.0 ** R, 2.0 ** -rng.integers(0, cols + 1, n)
+    B = rng.standard_normal((2, n)) + 1j * rng.standard_normal((2, n))
+    p = rng.permutation(n)  # the matrix is (R A C)[p]
+    F = torch.as_tensor((R[:, None] * A * C[None, :])[p].T.copy()).to(device="cuda", dtype=torch.complex64).contiguous()
+    ctx.getrf(F)
+    if trans:  # (C A^T R) y = C b with y in the order of p
+        X = torch.as_tensor(B * C).to(device="cuda", dtype=torch.complex64).contiguous()
+        ctx.getrs(F, X, 1)
+        got = np.empty_like(B)
+        got[:, p] = X.cpu().numpy()
+        got, ref = got * R, np.linalg.solve(A.T, B.T).T
+    else:
+        X = torch.as_tensor((B * R)[:, p]).to(device="cuda", dtype=torch.complex64).contiguous()
+        ctx.getrs(F, X, 0)
+        got, ref = X.cpu().numpy() * C, np.linalg.solve(A, B.T).T
+    err = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 8 * n * 1.2e-7, err
