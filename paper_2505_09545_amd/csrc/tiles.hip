@@ -199,9 +199,18 @@ __device__ inline bool tri_wave(const cplx<T>* __restrict__ D, int64_t ld, int w
   bool bad = false;
   // tile of step i: ascending, TRI_RIGHT_LOWER descending
   auto tl = [](int i) { return KIND == TRI_RIGHT_LOWER ? NT - 1 - i : i; };
+  // (tiles past w have no inverse: nothing is read there, and zeros keep them out of
+  // the tiles that TRI_RIGHT_LOWER takes after them)
+  auto tile_inv = [&](int s) {
+    Frag<T> f;
+    if (FULL || 16 * s < w) return load_inv<T, TR>(ti, s, lr, lk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f.re[q] = f.im[q] = 0;
+    return f;
+  };
   constexpr int PRE = sizeof(T) == 8 ? 1 : 2;
   Frag<T> pre[PRE];  // operands of the next step's first products, loaded a step ahead
-  Frag<T> inv = load_inv<T, TR>(ti, tl(0), lr, lk);
+  Frag<T> inv = tile_inv(tl(0));
   static_for<NT>([&](auto step) {
     constexpr int S = decltype(step)::value;
     const int s = tl(S);
@@ -225,7 +234,7 @@ __device__ inline bool tri_wave(const cplx<T>* __restrict__ D, int64_t ld, int w
     Tile<T> y = tile_zero<T>();
     const Frag<T> iv = inv;
     if constexpr (S + 1 < NT) {
-      inv = load_inv<T, TR>(ti, tl(S + 1), lr, lk);
+      inv = tile_inv(tl(S + 1));
       static_for<(S + 1 < PRE ? S + 1 : PRE)>([&](auto p) { pre[p] = frag(tl(S + 1), tl(p)); });
     }
     tile_mac<T>(y, iv, b);

@@ -186,3 +186,27 @@ def test_batch_of_more_rows_than_search_panels_hold(ctx):
         ref = oracle_cs(structs[0], 10.0, eps[0, l], wl[l], khat, e0)
         # (relative to the extinction: the first item absorbs nothing, the difference of two equal numbers)
         assert np.max(np.abs(cs[0, l].cpu().numpy() - ref) / ref[:, :1]) < 1e-10
+
+
+def test_batch_of_32_wide_searching_panels(ctx):
+    """16 FP64 systems of n = 2454 with the pivot search: their panels fit the LDS
+    only 32 columns wide (the last block 22), two 16 x 16 tiles per block where the
+    triangular solves are laid out for four.  Against the oracle for one item and
+    against the speculative factorisation for all (condition numbers below 100:
+    1e-10 of the extinction is twice n eps times that)."""
+    say("batch 32-wide searching panels")
+    structs = [gi.box_cells(np.array([50.0, 50.0, 42.0]), 10.0)[:818]]
+    wl = np.linspace(450.0, 800.0, 16)
+    eps = (2.2 + 0.05j * np.arange(16))[None, :]
+    khat, e0 = gi.normal_incidence_xy()
+    ctx.set_environment(1.0)
+    spec, _ = ctx.batch_spectra(structs, 10.0, wl, eps, khat, e0, prec=0)
+    ctx.set_pivoting(1)
+    try:
+        cs, _ = ctx.batch_spectra(structs, 10.0, wl, eps, khat, e0, prec=0)
+    finally:
+        ctx.set_pivoting(0)
+    cs, spec = cs.cpu().numpy(), spec.cpu().numpy()
+    assert np.max(np.abs(cs - spec) / spec[..., :1]) < 1e-10
+    ref = oracle_cs(structs[0], 10.0, eps[0, 13], wl[13], khat, e0)
+    assert np.max(np.abs(cs[0, 13] - ref) / ref[:, :1]) < 1e-10
