@@ -1829,14 +1829,41 @@ gdm_status gdm_extract_gpm(gdm_ctx* c, int64_t n_pw, const double* khat, const d
   return GDM_OK;
 }
 
+}  // extern "C"
+
+// A leading dimension past the tile kernels' range leaves room for at most about
+// 1000 columns in the device's memory: such a matrix is factored in a compact
+// copy, a few MB beside its own gigabytes.
+template <typename T>
+static gdm_status factor_caller_matrix(gdm_ctx* c, int64_t n, cplx<T>* A, int64_t lda, int32_t* ipiv, gdm_info* info) {
+  DevBuf none;
+  if (lda <= tiles_max_ld(sizeof(T))) return run_lu<T>(c, A, n, lda, c->ext_plan, c->ext_ws, none, ipiv, info);
+  struct Compact : DevBuf {
+    ~Compact() { release(); }
+  } compact;
+  compact.acct = &c->mem;
+  HIPCHK(c, compact.ensure(sizeof(cplx<T>) * n * n));
+  auto* F = static_cast<cplx<T>*>(compact.p);
+  auto copy = [&](const cplx<T>* a, int64_t la, cplx<T>* b, int64_t lb) {
+    if constexpr (sizeof(T) == 8) return launch_copy_d(a, la, b, lb, n, n, c->stream);
+    else return launch_copy_f(a, la, b, lb, n, n, c->stream);
+  };
+  HIPCHK(c, copy(A, lda, F, n));
+  const gdm_status s = run_lu<T>(c, F, n, n, c->ext_plan, c->ext_ws, none, ipiv, info);
+  HIPCHK(c, copy(F, n, A, lda));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  return s;
+}
+
+extern "C" {
+
 gdm_status gdm_getrf(gdm_ctx* c, int dtype, int64_t n, void* A, int64_t lda, int32_t* ipiv, gdm_info* info) {
   if (!c) return GDM_E_ARG;
   if (dtype != 0 && dtype != 1) FAIL(c, GDM_E_ARG, "dtype must be 0 or 1");
   if (n <= 0 || n > (int64_t)INT32_MAX / 4 || !A || !ipiv || lda < n) FAIL(c, GDM_E_ARG, "bad getrf arguments");
   HIPCHK(c, hipSetDevice(c->device));
-  DevBuf dummy;
-  gdm_status s = dtype == 0 ? run_lu<double>(c, A, n, lda, c->ext_plan, c->ext_ws, dummy, ipiv, info)
-                            : run_lu<float>(c, A, n, lda, c->ext_plan, c->ext_ws, dummy, ipiv, info);
+  gdm_status s = dtype == 0 ? factor_caller_matrix<double>(c, n, static_cast<double2*>(A), lda, ipiv, info)
+                            : factor_caller_matrix<float>(c, n, static_cast<float2*>(A), lda, ipiv, info);
   c->ext_dtype = (s == GDM_OK || s == GDM_E_SINGULAR) ? dtype : -1;
   return s;
 }

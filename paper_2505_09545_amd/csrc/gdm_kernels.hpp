@@ -303,6 +303,9 @@ void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu,
 // (k0, k0), width w <= nb <= 128; tinv: the block's tile inverses
 // (tinv_block_elems(nb) complex), all with an item stride for batches.
 int64_t tinv_block_elems(int nb);
+// Largest leading dimension of these kernels: a lane's offset from a uniform
+// address, up to 15 columns and 15 rows, is a 32-bit number of bytes.
+inline int64_t tiles_max_ld(int elem_bytes) { return (((int64_t)1 << 32) / (2 * elem_bytes) - 16) / 15; }
 template <typename T>
 hipError_t prepare_diag_lu();  // one-time host-side setting (before any graph capture)
 // speculative diagonal block: factors, checks (*flag |= 1), identity pivots, tile inverses

@@ -43,6 +43,7 @@ hipError_t launch_convert_d2f(const double2* a, int64_t lda, float2* b, int64_t 
 hipError_t launch_convert_f2d(const float2* a, int64_t lda, double2* b, int64_t ldb, int64_t m, int64_t n,
                               hipStream_t st);
 hipError_t launch_copy_d(const double2* a, int64_t lda, double2* b, int64_t ldb, int64_t m, int64_t n, hipStream_t st);
+hipError_t launch_copy_f(const float2* a, int64_t lda, float2* b, int64_t ldb, int64_t m, int64_t n, hipStream_t st);
 // x += c (c in float), and per-column max |c| into cmax[col]
 hipError_t launch_axpy_f2d(const float2* c, int64_t ldc, double2* x, int64_t ldx, int64_t m, int64_t n,
                            double* cmax, hipStream_t st);

@@ -349,7 +349,7 @@ __global__ void convert_f2d_kernel(const float2* a, int64_t lda, double2* b, int
     b[i + c * ldb] = make_double2(v.x, v.y);
   }
 }
-__global__ void copy_d_kernel(const double2* a, int64_t lda, double2* b, int64_t ldb, int64_t m) {
+template <typename CT> __global__ void copy_kernel(const CT* a, int64_t lda, CT* b, int64_t ldb, int64_t m) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t c = blockIdx.y;
   if (i < m) b[i + c * ldb] = a[i + c * lda];
@@ -381,14 +381,20 @@ hipError_t launch_convert_f2d(const float2* a, int64_t lda, double2* b, int64_t 
   }
   return hipSuccess;
 }
-hipError_t launch_copy_d(const double2* a, int64_t lda, double2* b, int64_t ldb, int64_t m, int64_t n,
-                         hipStream_t st) {
+template <typename CT>
+static hipError_t launch_copy(const CT* a, int64_t lda, CT* b, int64_t ldb, int64_t m, int64_t n, hipStream_t st) {
   for (int64_t c0 = 0; c0 < n; c0 += 65535) {
     const int64_t nc = n - c0 < 65535 ? n - c0 : 65535;
-    hipError_t e = launch_cols(copy_d_kernel, m, nc, st, a + c0 * lda, lda, b + c0 * ldb, ldb);
+    hipError_t e = launch_cols(copy_kernel<CT>, m, nc, st, a + c0 * lda, lda, b + c0 * ldb, ldb);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+hipError_t launch_copy_d(const double2* a, int64_t lda, double2* b, int64_t ldb, int64_t m, int64_t n, hipStream_t st) {
+  return launch_copy(a, lda, b, ldb, m, n, st);
+}
+hipError_t launch_copy_f(const float2* a, int64_t lda, float2* b, int64_t ldb, int64_t m, int64_t n, hipStream_t st) {
+  return launch_copy(a, lda, b, ldb, m, n, st);
 }
 
 // one workgroup per column: x += c, cmax[col] = max |c|

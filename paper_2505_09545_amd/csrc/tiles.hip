@@ -754,7 +754,7 @@ template <typename T>
 hipError_t launch_diag_lu(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, int32_t* ipiv, int32_t* flag,
                           cplx<T>* tinv, hipStream_t st, int nbatch, int64_t sA, int64_t sipiv, int64_t sflag,
                           int64_t stinv) {
-  if (w < 1 || w > 128 || w > nb) return hipErrorInvalidValue;
+  if (w < 1 || w > 128 || w > nb || ld > tiles_max_ld(sizeof(T))) return hipErrorInvalidValue;
   hipLaunchKernelGGL(diag_lu_kernel<T>, dim3(1, (unsigned)nbatch), dim3(512), diag_lu_lds_bytes(sizeof(T)), st, A, ld, k0,
                      w, ipiv, flag, tinv, tinv_uoff(nb), sA, sipiv, sflag, stinv);
   return hipGetLastError();
@@ -775,7 +775,7 @@ hipError_t launch_tri_panel(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, i
                             int64_t sflag, SplitOut lout, SplitOut uout, int64_t ssplit) {
   const int64_t cb = (ncols + 15) / 16, rb = (nrows + 15) / 16;
   if (cb + rb <= 0) return hipSuccess;
-  if (w < 1 || w > 128 || w > nb || cb + rb > INT32_MAX) return hipErrorInvalidValue;
+  if (w < 1 || w > 128 || w > nb || cb + rb > INT32_MAX || ld > tiles_max_ld(sizeof(T))) return hipErrorInvalidValue;
   if ((lout.planes || uout.planes) && w != 128 && w != 64) return hipErrorInvalidValue;
   hipLaunchKernelGGL(tri_panel_kernel<T>, dim3((unsigned)(cb + rb), (unsigned)nbatch), dim3(64), 0, st, A, ld, k0, w,
                      nrows, cu, ncols, (int)cb, tinv, tinv_uoff(nb), flag, lout, uout, sA, stinv, sflag, ssplit);
@@ -796,7 +796,7 @@ template <typename T>
 hipError_t launch_finish(cplx<T>* A, int64_t ld, int64_t n, int nb, const cplx<T>* tinv, hipStream_t st, int nbatch,
                          int64_t sA, int64_t stinv) {
   const int64_t nblk = (n + nb - 1) / nb;
-  if (nblk > 65535 || 2 * (int64_t)nbatch > 65535) return hipErrorInvalidValue;
+  if (nblk > 65535 || 2 * (int64_t)nbatch > 65535 || ld > tiles_max_ld(sizeof(T))) return hipErrorInvalidValue;
   if (nblk > 1) {
     // rows of a block column outside its diagonal block, in 16s (at most one more than n / 16)
     hipLaunchKernelGGL(tri_rows_kernel<T>, dim3((unsigned)((n + 15) / 16 + 1), (unsigned)nblk, (unsigned)nbatch), dim3(64),

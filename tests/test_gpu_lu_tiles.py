@@ -210,3 +210,25 @@ def test_getrf_fp32_row_scales(ctx, n, rows, cols, trans):
         got, ref = X.cpu().numpy() * C, np.linalg.solve(A, B.T).T
     err = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= 8 * n * 1.2e-7, err
+
+
+@pytest.mark.parametrize("dtype,lda", [(torch.complex128, 18_000_000), (torch.complex64, 36_000_000)])
+def test_getrf_long_columns(ctx, dtype, lda):
+    """17 columns so far apart that a 16 x 16 tile spans more than 2^32 bytes, in the
+    middle of larger ones: solution to the bound above, the rest of the storage
+    untouched."""
+    n = 17
+    rng = np.random.default_rng(5)
+    A = 2 * np.eye(n) + (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(2 * n)
+    A = A[rng.permutation(n)]
+    F = torch.full((n, lda), 7.0, dtype=dtype, device="cuda")
+    F[:, :n] = torch.as_tensor(A.T.copy()).to(device="cuda", dtype=dtype)
+    ctx.getrf(F)
+    B = rng.standard_normal((3, n)) + 1j * rng.standard_normal((3, n))
+    for trans in (0, 1):
+        X = torch.as_tensor(B).to(device="cuda", dtype=dtype).contiguous()
+        ctx.getrs(F, X, trans)
+        ref = np.linalg.solve(A.T if trans else A, B.T).T
+        err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert err.max() <= 8 * n * (2.2e-16 if dtype == torch.complex128 else 1.2e-7), (trans, err)
+    assert all(bool((F[j, n:] == 7).all()) for j in range(n))
