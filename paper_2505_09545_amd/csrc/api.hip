@@ -27,6 +27,9 @@ namespace {
 struct MemAccount {
   size_t used = 0;
   size_t limit = 0;
+  // Buffers that hold nothing between calls are kept for the next one and given
+  // back when another buffer needs the room.  Returns whether there were any.
+  std::function<bool()> give_back;
 };
 
 struct DevBuf {
@@ -37,7 +40,8 @@ struct DevBuf {
     if (bytes <= cap && p) return hipSuccess;
     if (bytes == 0) bytes = 256;
     // the limit counts what the context would hold after the call
-    if (acct && acct->limit > 0 && acct->used - cap + bytes > acct->limit) return hipErrorOutOfMemory;
+    const auto over = [&] { return acct && acct->limit > 0 && acct->used - cap + bytes > acct->limit; };
+    if (over() && !(acct->give_back && acct->give_back() && !over())) return hipErrorOutOfMemory;
     if (p) {
       hipError_t e = hipFree(p);
       if (e != hipSuccess) return e;
@@ -45,12 +49,17 @@ struct DevBuf {
       p = nullptr;
       cap = 0;
     }
-    hipError_t e = hipMalloc(&p, bytes);
+    void* got = nullptr;
+    hipError_t e = hipMalloc(&got, bytes);
     if (e != hipSuccess) {
-      p = nullptr;
       (void)hipGetLastError();
-      return e;
+      if (acct && acct->give_back && acct->give_back()) e = hipMalloc(&got, bytes);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+      }
     }
+    p = got;
     cap = bytes;
     if (acct) acct->used += cap;
     return hipSuccess;
@@ -129,6 +138,8 @@ struct gdm_ctx {
   DevBuf X, Rr, C32, small, scratch, flag;
   DevBuf Lam, adj;  // adjoint field and adjoint workspace
   DevBuf part;      // split-k partial sums of the small-RHS refinement residual
+  // of use within one call only: the last buffers that the call allocates
+  DevBuf planes;    // split operands of an FP32 factorisation or batch
   DevBuf iter;      // workspace of gdm_solve_iterative
   HostBuf iter_host;  // the scalars its kernels hand to the host
   DevBuf src;       // unit point sources of gdm_ldos / gdm_green_tensor: positions, moments, F0, q, fields
@@ -147,7 +158,7 @@ struct gdm_ctx {
   MemAccount mem;    // device bytes of the buffers below and the caller's limit
   std::vector<DevBuf*> buffers() {
     return {&pos, &eps,  &alpha_c, &alpha6, &M,     &M64,  &ipiv,  &luws, &rows,   &ext_ws, &X,   &Rr,   &C32, &small,
-            &scratch, &flag, &Lam,  &adj,   &part, &bM64, &bM32, &bipiv, &bws, &bvec, &bpart, &bsmall, &bpos, &bwl, &iter, &src,
+            &scratch, &flag, &Lam,  &adj,   &part, &bM64, &bM32, &bipiv, &bws, &bvec, &bpart, &bsmall, &bpos, &bwl, &planes, &iter, &src,
             &gpm_gid, &gpm_tab, &gpm_alpha};
   }
 };
@@ -242,14 +253,17 @@ static gdm_status run_lu(gdm_ctx* c, void* A, int64_t n, int64_t ld, LUPlan& pla
     wsb = std::max(wsb, lu_workspace_bytes(search, (int)sizeof(T), c->num_cu));
   }
   HIPCHK(c, ws.ensure(wsb));
-  LUWork w;
-  lu_workspace_carve(ws.p, plan, (int)sizeof(T), c->num_cu, w);
-  w.events = &c->lu_events;
   int32_t* piv = ipiv_out;
   if (!piv) {
     HIPCHK(c, ipiv.ensure(sizeof(int32_t) * n));
     piv = ipiv.as<int32_t>();
   }
+  const size_t planes = std::max(lu_planes_bytes(plan), lu_planes_bytes(search));
+  if (planes > 0 && c->planes.ensure(planes) != hipSuccess) plan.split = search.split = false;
+  LUWork w;
+  lu_workspace_carve(ws.p, plan, (int)sizeof(T), c->num_cu, w);
+  w.split = c->planes.as<unsigned char>();
+  w.events = &c->lu_events;
   HIPCHK(c, lu_factor<T>(A, ld, plan, w, piv, c->stream, &c->prof, c->lookahead ? c->side : nullptr));
   int32_t err[2] = {0, 0};
   HIPCHK(c, hipMemcpyAsync(err, w.err, sizeof(err), hipMemcpyDeviceToHost, c->stream));
@@ -268,6 +282,7 @@ static gdm_status run_lu(gdm_ctx* c, void* A, int64_t n, int64_t ld, LUPlan& pla
     HIPCHK(c, rebuild());
     plan = search;
     lu_workspace_carve(ws.p, plan, (int)sizeof(T), c->num_cu, w);
+    w.split = c->planes.as<unsigned char>();
     w.events = &c->lu_events;
     HIPCHK(c, lu_factor<T>(A, ld, plan, w, piv, c->stream, &c->prof, c->lookahead ? c->side : nullptr));
     HIPCHK(c, hipMemcpyAsync(err, w.err, sizeof(err), hipMemcpyDeviceToHost, c->stream));
@@ -490,12 +505,12 @@ int64_t batch_part_elems(int64_t n, int B, int64_t npw) {
 
 }  // namespace
 
-static bool batch_shape_for(gdm_ctx* c, int64_t n, int B, int nb_max, bool ir, BatchShape& sh) {
+static bool batch_shape_for(gdm_ctx* c, int64_t n, int B, int nb_max, bool ir, bool split, BatchShape& sh) {
   const int eb = ir ? 4 : 8;
   sh.n = n;
   sh.B = B;
   const int pb = panel_pb(c, true);
-  sh.plan = lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, pb, ir);
+  sh.plan = lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, pb, split);
   sh.nb = sh.plan.nb;
   // (group sizes are those whose searching panels would fit, also for speculative ones)
   const LUPlan search = pb ? sh.plan : lu_plan(n, eb, c->num_cu, c->lds_bytes, B, nb_max, 1);
@@ -516,6 +531,7 @@ static gdm_status batch_enqueue_group(gdm_ctx* c, const BatchShape& sh, const Ba
   hipStream_t st = c->stream;
   LUWork w;
   lu_workspace_carve(b.ws, sh.plan, ir ? 4 : 8, c->num_cu, w, B);
+  w.split = c->planes.as<unsigned char>();
   w.events = &c->lu_events;
   HIPCHK(c, launch_batch_assemble(b.pos, N, b.alpha, b.k0, c->n_env, step, radiative, b.M64, ir ? b.M32 : nullptr, B,
                                   st));
@@ -640,8 +656,9 @@ extern "C" gdm_status gdm_batch_spectra(gdm_ctx* c, int64_t n_struct, const int6
   HIPCHK(c, hipSetDevice(c->device));
   size_t free_b = 0, total_b = 0;
   HIPCHK(c, hipMemGetInfo(&free_b, &total_b));
-  size_t budget = std::min<size_t>(free_b / 2, (size_t)64 << 30);
-  if (c->mem.limit > 0) budget = std::min(budget, c->mem.limit > c->mem.used ? (c->mem.limit - c->mem.used) / 2 : 0);
+  const size_t spare = c->planes.cap + c->iter.cap, used = c->mem.used - spare;  // (spare: given back if needed)
+  size_t budget = std::min<size_t>((free_b + spare) / 2, (size_t)64 << 30);
+  if (c->mem.limit > 0) budget = std::min(budget, c->mem.limit > used ? (c->mem.limit - used) / 2 : 0);
 
   // largest feasible group per structure size: panels of all items co-resident,
   // matrices within the memory budget, at most 32 items and n_wl
@@ -649,12 +666,12 @@ extern "C" gdm_status gdm_batch_spectra(gdm_ctx* c, int64_t n_struct, const int6
     int best = 0;
     for (int B = 1; B <= 32 && B <= n_wl; B *= 2) {
       BatchShape sh;
-      if (batch_shape_for(c, n, B, 128, ir, sh) && (size_t)B * batch_item_bytes(n, ir) <= budget) best = B;
+      if (batch_shape_for(c, n, B, 128, ir, ir, sh) && (size_t)B * batch_item_bytes(n, ir) <= budget) best = B;
     }
     return best;
   };
   // size the workspaces for the largest group any structure may use
-  size_t m_elems = 0, ws_bytes = 0, vec_elems = 0, part_elems = 0, pos_elems = 0;
+  size_t m_elems = 0, ws_bytes = 0, planes = 0, vec_elems = 0, part_elems = 0, pos_elems = 0;
   int Bcap = 0;
   std::vector<int> bmax(n_struct);
   for (int64_t s = 0; s < n_struct; ++s) {
@@ -664,8 +681,9 @@ extern "C" gdm_status gdm_batch_spectra(gdm_ctx* c, int64_t n_struct, const int6
     for (int B = 1; B <= bmax[s]; B *= 2)
       for (int nbm : {128, 64}) {
         BatchShape sh;
-        if (!batch_shape_for(c, n, B, nbm, ir, sh)) continue;
+        if (!batch_shape_for(c, n, B, nbm, ir, ir, sh)) continue;
         ws_bytes = std::max(ws_bytes, lu_workspace_bytes(sh.plan, ir ? 4 : 8, c->num_cu, B));
+        planes = std::max(planes, lu_planes_bytes(sh.plan, B));
       }
     m_elems = std::max(m_elems, (size_t)bmax[s] * n * n);
     vec_elems = std::max(vec_elems, (size_t)bmax[s] * n_pw * n);
@@ -686,6 +704,7 @@ extern "C" gdm_status gdm_batch_spectra(gdm_ctx* c, int64_t n_struct, const int6
   HIPCHK(c, c->bsmall.ensure(sizeof(double) * nsmall));
   HIPCHK(c, c->bpos.ensure(sizeof(double) * pos_elems));
   HIPCHK(c, c->bwl.ensure(sizeof(double) * n_wl));
+  const bool split = planes > 0 && c->planes.ensure(planes) == hipSuccess;
   HIPCHK(c, hipMemcpyAsync(c->bwl.p, wavelengths, sizeof(double) * n_wl, hipMemcpyHostToDevice, c->stream));
   BatchBufs b{};
   b.M64 = c->bM64.as<double2>();
@@ -756,7 +775,7 @@ extern "C" gdm_status gdm_batch_spectra(gdm_ctx* c, int64_t n_struct, const int6
     auto it = c->batch_tune.find(key);
     auto add_cand = [&](int B, int nbm) {
       BatchShape sh;
-      if (!batch_shape_for(c, n, B, nbm, ir, sh)) return;
+      if (!batch_shape_for(c, n, B, nbm, ir, split, sh)) return;
       for (auto& x : cand)
         if (x.first == B && x.second == sh.nb) return;
       cand.push_back({B, sh.nb});
@@ -773,7 +792,7 @@ extern "C" gdm_status gdm_batch_spectra(gdm_ctx* c, int64_t n_struct, const int6
       const bool tuning = cand.size() > 1 && ci < cand.size();
       const std::pair<int, int> cfg = tuning ? cand[ci] : best;
       BatchShape sh;
-      if (!batch_shape_for(c, n, cfg.first, cfg.second, ir, sh)) {
+      if (!batch_shape_for(c, n, cfg.first, cfg.second, ir, split, sh)) {
         status = GDM_E_STATE;
         break;
       }
@@ -915,6 +934,12 @@ gdm_status gdm_create(int device, void* hip_stream, gdm_ctx** out) {
   gdm_ctx* c = new gdm_ctx();
   c->device = device;
   for (DevBuf* b : c->buffers()) b->acct = &c->mem;
+  c->mem.give_back = [c] {
+    const bool any = c->planes.p || c->iter.p;
+    c->planes.release();
+    c->iter.release();
+    return any;
+  };
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) {
     c->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
@@ -1179,11 +1204,18 @@ gdm_status gdm_solve_iterative(gdm_ctx* c, double wl, int64_t nrhs, const double
   const int64_t n = c->n;
   const Wave w = wave_of(c, wl);
   const DipoleView d = view_of(c, self_term(c, w));
-  HIPCHK(c, c->iter.ensure(iter_workspace_bytes(c->N, n, nrhs, restart, c->num_cu)));
   HIPCHK(c, c->X.ensure(sizeof(double2) * n * nrhs));
   HIPCHK(c, c->iter_host.ensure(gmres_host_bytes(nrhs, restart)));
+  // where the workspace does not fit, with fewer parts per scalar product
+  bool tight = false;
+  hipError_t fit = c->iter.ensure(iter_workspace_bytes(c->N, n, nrhs, restart, c->num_cu, tight));
+  if (fit != hipSuccess) {
+    tight = true;
+    fit = c->iter.ensure(iter_workspace_bytes(c->N, n, nrhs, restart, c->num_cu, tight));
+  }
+  HIPCHK(c, fit);
   IterWork iw;
-  iter_workspace_carve(c->iter.p, c->N, n, nrhs, restart, c->num_cu, iw);
+  iter_workspace_carve(c->iter.p, c->N, n, nrhs, restart, c->num_cu, tight, iw);
   double2* X = c->X.as<double2>();
   HIPCHK(c, hipEventRecord(c->ev[0], c->stream));
   GmresStats gs;
@@ -1498,9 +1530,13 @@ gdm_status gdm_cross_sections(gdm_ctx* c, int64_t nrhs, const double* f0, const 
   HIPCHK(c, hipSetDevice(c->device));
   const Wave w = wave_of(c, c->wavelength);
   const DipoleView d = view_of(c, make_double2(0, 0));
-  const int64_t nblk = sca_ff_blocks(c->N);
+  int64_t nblk = sca_ff_blocks(c->N);
   const int64_t ng = c->n_gpm;
-  HIPCHK(c, c->small.ensure(sizeof(double) * std::max<int64_t>(5 * nrhs + nrhs * (nblk + ng), 4 * nrhs)));
+  auto sums_bytes = [&] { return sizeof(double) * std::max<int64_t>(5 * nrhs + nrhs * (nblk + ng), 4 * nrhs); };
+  if (c->small.ensure(sums_bytes()) != hipSuccess) {
+    nblk = sca_ff_blocks(c->N, 1);  // the sources of a target in one part
+    HIPCHK(c, c->small.ensure(sums_bytes()));
+  }
   double* sums = c->small.as<double>();
   double* mutual = sums + 5 * nrhs;  // [nrhs][ng], GPM groups only
   double* part = mutual + nrhs * ng;

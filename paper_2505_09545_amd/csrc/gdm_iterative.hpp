@@ -32,8 +32,9 @@ struct GmresStats {
 };
 
 int coupling_num_splits(int64_t N, int num_cu);
-size_t iter_workspace_bytes(int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu);
-void iter_workspace_carve(void* base, int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu, IterWork& w);
+size_t iter_workspace_bytes(int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu, bool tight);
+void iter_workspace_carve(void* base, int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu, bool tight,
+                          IterWork& w);
 hipError_t launch_precond_build(const DipoleView& d, const Wave& w, const IterWork& iw, hipStream_t st);
 hipError_t launch_precond_apply(const DipoleView& d, const IterWork& iw, int64_t n, int64_t nrhs, const double2* v,
                                 double2* z, hipStream_t st);

@@ -251,6 +251,7 @@ struct LUPlan {
   int64_t lds_bytes = 0;  // LDS of a CU
   bool spec = false;  // speculative panels (diagonal pivots checked against partial pivoting; pb = 1 plan)
   bool split = false;  // FP32: trailing updates from operands split in two f16 (update_split.hip)
+  int tmp_cols = 0;    // columns of the solves' scratch
   std::vector<LUBlock> blocks;
 };
 
@@ -269,9 +270,11 @@ struct LUWork {
   int32_t* pairs;            // [nblocks][2][2 nb]: destination rows then source rows
   int32_t* npairs;           // [nblocks]
   int32_t* spec;             // [nblocks] speculative panel failed its check (after npairs, same item stride)
-  void* tmp;                 // [tmp_elems] complex scratch (operand copies, split-k partials, solve sweeps)
-  void* tinv;                // [nblocks][tinv_block_elems(nb)] complex inverses of the 16 x 16 diagonal triangles
-  unsigned char* split;      // FP32: split L21 of even blocks, of odd blocks, then U12 (s_split bytes each)
+  void* tmp;                 // [tmp_elems] complex scratch of the solves (sweeps, split-k partials)
+  void* tinv;                // [nblocks][tinv_block_elems(nb)] complex inverses of the 16 x 16 diagonal triangles,
+                             // in the place of tmp (a factorisation's, of no use after it)
+  unsigned char* split = nullptr;  // the caller's buffer of lu_planes_bytes (plan.split): split L21 of even blocks,
+                                   // of odd blocks, then U12 (s_split bytes each)
   std::vector<hipEvent_t>* events;  // host-side pool of reusable events (look-ahead)
   int64_t tmp_elems;         // capacity of tmp per item in complex elements
   int nbatch = 1;
@@ -297,6 +300,9 @@ template <typename T>
 hipError_t lu_prepare(const LUPlan& plan);
 bool lu_plan_fits(const LUPlan& p);
 size_t lu_workspace_bytes(const LUPlan& p, int elem_bytes, int num_cu, int nbatch = 1);
+// split operands of a factorisation, apart from the workspace: a plan whose
+// `split` is taken back does without them
+size_t lu_planes_bytes(const LUPlan& p, int nbatch = 1);
 void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu, LUWork& w, int nbatch = 1);
 
 // Triangular block operations on 16 x 16 matrix-core tiles (tiles.hip).  Block at

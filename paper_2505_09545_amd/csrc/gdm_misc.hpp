@@ -35,7 +35,7 @@ hipError_t launch_cs_sums(const DipoleView& d, const double2* f0, const double2*
 // sum_{i != j} q_i^H G6_ij q_j per RHS (partial sums per workgroup, [nrhs][nblk]).
 hipError_t launch_sca_ff(const DipoleView& d, const Wave& w, const double2* q, int64_t ldq, int64_t nrhs,
                          double* partial, int64_t nblk, hipStream_t st);
-int64_t sca_ff_blocks(int64_t N);
+int64_t sca_ff_blocks(int64_t N, int splits = 0);  // splits 0: as many as fill the device
 
 // conversions and refinement helpers
 hipError_t launch_convert_d2f(const double2* a, int64_t lda, float2* b, int64_t ldb, int64_t m, int64_t n,

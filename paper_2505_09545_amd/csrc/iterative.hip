@@ -337,7 +337,6 @@ static int arnoldi_entries(int64_t n) {
   const int64_t e = (n + 128 * 128 - 1) / (128 * 128) * 128;
   return (int)(e < AR_EMAX ? e : AR_EMAX);
 }
-static int arnoldi_parts(int64_t n) { return (int)((n + arnoldi_entries(n) - 1) / arnoldi_entries(n)); }
 
 __device__ inline double2 wave_sum(double2 s) {
 #pragma unroll
@@ -582,13 +581,14 @@ int coupling_num_splits(int64_t N, int num_cu) {
   return (int)((N + len - 1) / len);
 }
 
-size_t iter_workspace_bytes(int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu) {
+size_t iter_workspace_bytes(int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu, bool tight) {
   IterWork w;
-  iter_workspace_carve(nullptr, N, n, nrhs, restart, num_cu, w);
+  iter_workspace_carve(nullptr, N, n, nrhs, restart, num_cu, tight, w);
   return w.bytes;
 }
 
-void iter_workspace_carve(void* base, int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu, IterWork& w) {
+void iter_workspace_carve(void* base, int64_t N, int64_t n, int64_t nrhs, int restart, int num_cu, bool tight,
+                          IterWork& w) {
   char* p = static_cast<char*>(base);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -605,7 +605,14 @@ void iter_workspace_carve(void* base, int64_t N, int64_t n, int64_t nrhs, int re
   // the parts of the scalar products (two passes) share the scratch vector, which
   // is used between cycles only
   w.E = arnoldi_entries(n);
-  w.C = arnoldi_parts(n);
+  if (tight) {
+    // so few parts that they fit the scratch vector, and the norm's parts 32 bytes per
+    // basis vector (as far as a part of W fits the LDS of arnoldi_kernel)
+    const int64_t c = std::max<int64_t>(1, std::min<int64_t>(n / (2 * (restart + 1)), 4 * (restart + 1)));
+    const int64_t e = ((n + c - 1) / c + 127) / 128 * 128, emax = (4096 - AR_G * 128 - (restart + 1)) / 128 * 128;
+    w.E = (int)std::max<int64_t>(w.E, std::min(e, emax));
+  }
+  w.C = (int)((n + w.E - 1) / w.E);
   const size_t hp = (size_t)nrhs * (restart + 1) * w.C * sizeof(double2);
   w.t = reinterpret_cast<double2*>(take(std::max(vec, 2 * hp)));
   w.hp = w.t;

@@ -1539,18 +1539,19 @@ LUPlan lu_plan(int64_t n, int elem_bytes, int num_cu, int lds_bytes, int nbatch,
   // per 32 of them must be resident too (G + ceil(G / 32) <= max_wg)
   const int avail = pb > 1 ? std::max(1, 32 * p.max_wg / 33) : p.max_wg;
   const int cbytes = 2 * elem_bytes;
-  int nb = nb_max >= 16 && nb_max <= 128 ? nb_max : 128;
-  // the panel must fit: ceil(n / avail) rows x nb columns in LDS (not a speculative
-  // one, which keeps no rows there; a failed factorisation is repeated with a
-  // plan of its own.  128 instead of 64 columns halve the traffic of the updates:
-  // spectra of four structures up to n = 4500, 16 systems at a time, 64.9 -> 53.0 ms;
-  // one FP32 factorisation of n = 69 000 7.5 -> 4.1 s)
-  while (nb > 16 && !p.spec) {
-    const int64_t R = (n + avail - 1) / avail;
-    if (R <= panel_rows_max(nb, lds_bytes, cbytes, pb)) break;
-    nb /= 2;
-  }
+  const int nb_want = nb_max >= 16 && nb_max <= 128 ? nb_max : 128;
+  // a searching panel must fit: ceil(n / avail) rows x nb columns in LDS
+  int nb_fit = nb_want;
+  while (nb_fit > 16 && (n + avail - 1) / avail > panel_rows_max(nb_fit, lds_bytes, cbytes, pb)) nb_fit /= 2;
+  // (not a speculative one, which keeps no rows there; a failed factorisation is
+  // repeated with a plan of its own.  128 instead of 64 columns halve the traffic of
+  // the updates: spectra of four structures up to n = 4500, 16 systems at a time,
+  // 64.9 -> 53.0 ms; one FP32 factorisation of n = 69 000 7.5 -> 4.1 s)
+  const int nb = p.spec ? nb_want : nb_fit;
   p.nb = nb;
+  // wide blocks need no more workspace than blocks of nb_fit columns with an
+  // inverse, a copied panel and a solve's scratch of that width did
+  p.tmp_cols = p.spec ? std::min(nb, 3 * nb_fit) : nb;
   // (whole blocks of 128 or 64 columns; the planes hold no others)
   p.split = refined && elem_bytes == 4 && (nb == 128 || nb == 64) && nb < n;
   // Workgroups of one panel.  Measured on n = 12 000: an FP32 panel over at most
@@ -1588,11 +1589,16 @@ bool lu_plan_fits(const LUPlan& p) {
   return true;
 }
 
-// rows of the complex scratch `tmp` (x nb columns): operand copies need n; the
-// split-k partial sums of the transposed solve need more than n for small n
+// rows of the complex scratch `tmp` (x plan.tmp_cols): the sweeps of a solve need
+// n; the split-k partial sums of the transposed solve more than n for small n
 static int64_t tmp_rows(const LUPlan& p) { return p.n > 512 ? p.n : 512; }
 
 static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
+
+// bytes of one split operand (the updates read whole 128-wide tiles from any
+// multiple of 64 columns on)
+static int64_t lu_plane_stride(const LUPlan& p) { return p.split ? split_bytes(p.n - p.nb + 128, p.nb) : 0; }
+size_t lu_planes_bytes(const LUPlan& p, int nbatch) { return (size_t)nbatch * 3 * lu_plane_stride(p); }
 
 size_t lu_workspace_bytes(const LUPlan& p, int elem_bytes, int num_cu, int nbatch) {
   LUWork w;
@@ -1622,11 +1628,12 @@ void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu,
   const size_t nwc = 2 * (size_t)elem_bytes / 4;  // 32-bit words per complex
   // tournament: records [2][gitem][pb][1 + pb nwc], then the roots' winners
   // [2][ceil(gitem / 32)][pb][2 + pb nwc]; partial pivoting: keys [2][gitem][KEY_STRIDE]
-  const size_t cand_words = p.pb > 1 ? 2 * (size_t)w.gitem * pbz * (1 + pbz * nwc) +
+  // (speculative panels exchange nothing)
+  const size_t cand_words = p.spec ? 0 : p.pb > 1 ? 2 * (size_t)w.gitem * pbz * (1 + pbz * nwc) +
                                            2 * (size_t)tp_roots(w.gitem) * pbz * (2 + pbz * nwc)
                                      : 2 * (size_t)w.gitem * KEY_STRIDE;
   w.s_cand = (int64_t)(al256(cand_words * 8) / 8);
-  w.s_rows = (int64_t)(al256(2 * (size_t)w.gitem * pbz * ww * 8) / 8);
+  w.s_rows = p.spec ? 0 : (int64_t)(al256(2 * (size_t)w.gitem * pbz * ww * 8) / 8);
   w.cand = reinterpret_cast<unsigned long long*>(take((size_t)nbatch * w.s_cand * 8));
   w.rows = reinterpret_cast<unsigned long long*>(take((size_t)nbatch * w.s_rows * 8));
   w.err = reinterpret_cast<int32_t*>(take(64));
@@ -1635,14 +1642,11 @@ void lu_workspace_carve(void* base, const LUPlan& p, int elem_bytes, int num_cu,
   w.pairs = reinterpret_cast<int32_t*>(take((size_t)nbatch * w.s_pairs * 4));
   w.npairs = reinterpret_cast<int32_t*>(take((size_t)nbatch * w.s_npairs * 4));
   w.spec = w.npairs ? w.npairs + nblk : nullptr;
-  w.tmp_elems = tmp_rows(p) * (int64_t)nb;
+  w.tmp_elems = tmp_rows(p) * (int64_t)p.tmp_cols;
   w.s_tmp = (int64_t)(al256((size_t)w.tmp_elems * cb) / cb);
-  w.tmp = take((size_t)nbatch * w.s_tmp * cb);
   w.s_tinv = (int64_t)(al256(nblk * (size_t)tinv_block_elems(p.nb) * cb) / cb);
-  w.tinv = take((size_t)nbatch * w.s_tinv * cb);
-  // split operands (the updates read whole 128-wide tiles from any multiple of 64 columns on)
-  w.s_split = p.split ? split_bytes(p.n - (int64_t)nb + 128, p.nb) : 0;
-  w.split = reinterpret_cast<unsigned char*>(w.s_split ? take((size_t)nbatch * 3 * w.s_split) : nullptr);
+  w.tmp = w.tinv = take((size_t)nbatch * std::max(w.s_tmp, w.s_tinv) * cb);
+  w.s_split = lu_plane_stride(p);
   w.events = nullptr;
   w.bytes = off + 256;
 }
@@ -1751,7 +1755,7 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
   const double fb = (double)NB;
   hipError_t e;
   if (NB < 1 || NB > 65535 || !lu_plan_fits(plan) || plan.max_wg * NB > ws.gmax || plan.max_wg > ws.gitem ||
-      plan.pb > ws.pb)
+      plan.pb > ws.pb || (plan.split && !ws.split))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(init_err_kernel, dim3(1), dim3(64), 0, st, ws.err);
   // exchange buffers start from zero (epoch 0 is never used), so epochs 1, 2, ...

@@ -316,12 +316,12 @@ static int sca_ff_splits(int64_t N) {
   const int64_t tb = (N + 255) / 256;
   return (int)std::max<int64_t>(1, std::min<int64_t>((N + FFT - 1) / FFT, 256 / tb));
 }
-int64_t sca_ff_blocks(int64_t N) { return (N + 255) / 256 * sca_ff_splits(N); }
+int64_t sca_ff_blocks(int64_t N, int splits) { return (N + 255) / 256 * (splits > 0 ? splits : sca_ff_splits(N)); }
 
 hipError_t launch_sca_ff(const DipoleView& d, const Wave& w, const double2* q, int64_t ldq, int64_t nrhs,
                          double* partial, int64_t nblk, hipStream_t st) {
   if (nrhs <= 0 || d.N <= 0) return hipSuccess;
-  const int ns = sca_ff_splits(d.N);
+  const int ns = (int)(nblk / ((d.N + 255) / 256));
   const int64_t jps = ((d.N + ns - 1) / ns + FFT - 1) / FFT * FFT;  // trailing splits may be empty (partial sum 0)
   if (nrhs == 1)
     hipLaunchKernelGGL(sca_ff_kernel<1>, dim3((unsigned)nblk, 1), dim3(256), 0, st, d, w, q, ldq, nrhs, ns, jps, partial,

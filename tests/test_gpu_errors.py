@@ -186,3 +186,75 @@ def test_batch_noconv_when_corrections_fall_short(gdm):
         assert ei.value.status == gdm.GDM_E_ARG
     finally:
         ctx.close()
+
+
+def test_buffers_of_one_call_yield_to_a_limit(gdm):
+    """The split operands of an FP32 factorisation, the wide form of the iterative
+    solver's workspace and the far-field sum's parts are given back, or done
+    without, where a limit leaves no room: one byte less than an unlimited context
+    holds after each call still serves it, refined results to the same tolerance
+    (backward error 1e-14; condition numbers below 100: 1e-11)."""
+    w = small_structure()
+    n = 3 * len(w["r_cell"])
+
+    def stages(ctx, limit):
+        out = []
+        ctx.set_environment(w["n_env"])
+        ctx.set_structure(torch.as_tensor(w["r_cell"]), w["step"], torch.as_tensor(w["eps_cell"]))
+        say("limit: factorize", limit[0])
+        ctx.set_memory_limit(limit[0])
+        ctx.factorize(w["wavelength"], gdm.PREC_FP32_IR)
+        used = [ctx.memory_used()]
+        khat, e0, e2 = gdm.plane_wave_inputs(w, ctx)
+        f0 = ctx.incident_planewave(khat, e0)
+        say("limit: solve", limit[1])
+        ctx.set_memory_limit(limit[1])
+        q, f = ctx.solve(f0)
+        used.append(ctx.memory_used())
+        out += [q, f]
+        say("limit: far field", limit[2])
+        ctx.set_memory_limit(limit[2])
+        out.append(ctx.cross_sections(f0, q, f, e2, want_ff=True))
+        used.append(ctx.memory_used())
+        say("limit: iterative", limit[3])
+        ctx.set_memory_limit(limit[3])
+        out.append(ctx.solve_iterative(w["wavelength"], f0, restart=200)[0])
+        used.append(ctx.memory_used())
+        torch.cuda.synchronize()
+        return used, [o.cpu().numpy() for o in out]
+
+    ref, lim = gdm.Context(0), gdm.Context(0)
+    try:
+        used, a = stages(ref, [0] * 4)
+        tight, b = stages(lim, [u - 1 for u in used])
+    finally:
+        ref.close()
+        lim.close()
+    assert all(t < u for t, u in zip(tight, used)), (tight, used)
+    # the matrices, and no more than three buffers of n x 128 beside them
+    assert tight[0] < 24 * n * n + 3 * max(n, 512) * 128 * 8 + (2 << 20)
+    for x, y in zip(a, b):
+        assert relcol(y, x) <= 1e-11
+
+
+def test_batch_without_room_for_split_operands(gdm):
+    """The same for batched spectra: 16 systems of n = 150, whose split operands
+    take more than their matrices."""
+    structs = [gi.cuboid_cells(5, 5, 2, 10.0)]
+    wl = np.linspace(450.0, 800.0, 16)
+    eps = (2.2 + 0.05j * np.arange(16))[None, :]
+    khat, e0 = gi.normal_incidence_xy()
+    ref, lim = gdm.Context(0), gdm.Context(0)
+    try:
+        for c in (ref, lim):
+            c.set_environment(1.0)
+        a, _ = ref.batch_spectra(structs, 10.0, wl, eps, khat, e0, prec=1)
+        say("batch: limit one byte below", ref.memory_used())
+        lim.set_memory_limit(ref.memory_used() - 1)
+        b, be = lim.batch_spectra(structs, 10.0, wl, eps, khat, e0, prec=1)
+        assert bool((be <= 1e-14).all())
+        a, b = a.cpu().numpy(), b.cpu().numpy()
+        assert np.max(np.abs(a - b) / a[..., :1]) <= 1e-11
+    finally:
+        ref.close()
+        lim.close()
