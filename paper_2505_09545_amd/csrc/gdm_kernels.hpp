@@ -118,7 +118,7 @@ hipError_t launch_assemble_dual(const DipoleView& d, const struct Wave& w, doubl
 
 // A block step of the solves: rows [ar0, ar0 + adw) of A are a square block (row
 // r - ar0, column k) of which only one triangle is read (the rest counts as zero).
-enum { GEMM_MASK_NONE = 0, GEMM_MASK_STRICT_LOWER = 1, GEMM_MASK_UPPER = 2, GEMM_MASK_STRICT_UPPER = 3 };
+enum { GEMM_MASK_NONE = 0, GEMM_MASK_STRICT_LOWER = 1, GEMM_MASK_UPPER = 2, GEMM_MASK_STRICT_UPPER = 3, GEMM_MASK_LOWER = 4 };
 struct GemmMask {
   int akind = 0;
   int64_t ar0 = 0, adw = 0;

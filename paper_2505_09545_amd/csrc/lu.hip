@@ -1921,6 +1921,22 @@ hipError_t lu_factor(void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws,
 #undef LUCHK
 }
 
+// Whether a transposed sweep pushes a block's part into the later columns
+// (skinny_push_kernel) or gathers each block's sum (skinny_t_kernel).  Pushing
+// saves a launch and the partial sums per block (n = 3000 speculative, time of a
+// push over a gather: 0.40 for one column in FP32, 0.46 in FP64), but starts with
+// the diagonal blocks, one workgroup each, whose time only several blocks make up
+// for: n = 120 1.1 to 1.9 in FP32 and 1.4 to 3.0 in FP64, n = 420 0.61 to 0.88 and
+// 0.79 (1 column), 1.00 (2), 1.30 (3, 4), 0.93 (5 and more), n = 1029 0.48 to 0.89
+// and 0.57 to 0.99.  And its reductions over 128 rows, where a gather's run over
+// 256, bound it once the launches are full: FP64 n = 6000 0.78 at 16 columns, 0.99
+// at 32, 1.16 at 66, n = 2100 0.98 at 66, 1.05 at 130; FP32 n = 6000 0.98 at 66, 1.07
+// at 130.
+static bool lu_solve_pushes(int elem_bytes, int64_t n, int nblk, int64_t nr, int nbatch) {
+  if (elem_bytes == 4) return nblk >= (nr == 1 ? 2 : 3) && n * nr * nbatch <= 450000;
+  return nblk >= (nr == 1 ? 3 : nr == 2 ? 5 : nr <= 4 ? 8 : 4) && n * nr * nbatch <= 190000;
+}
+
 template <typename T>
 hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, const LUWork& ws, void* Bv,
                     int64_t ldb, int64_t nrhs, hipStream_t st, int64_t sA, int64_t sB) {
@@ -1993,10 +2009,19 @@ hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, c
         if (e != hipSuccess) return e;
       }
     } else {
+      const bool push = lu_solve_pushes((int)sizeof(T), n, nblk, nr, NB);
       // M^T = U^T L_k^T P_k ... L_1^T P_1.  U^T forward, with V = U01 U11^-1 stored above the diagonal:
       //   z_b = U11^-T g_b - V_b^T z_above, the first term of all blocks at once
-      if ((e = launch_skinny_diag_t<T>(false, n, nb, A, ld, B, ldb, nr, st, NB, sA, sB)) != hipSuccess) return e;
-      for (int bi = 0; bi + 1 < nblk; ++bi) {
+      if (push && (e = launch_skinny_diag_t<T>(false, n, nb, A, ld, B, ldb, nr, st, NB, sA, sB)) != hipSuccess) return e;
+      // (or gathered, z_b = g_b - V_b^T z_above - (I - U11^-1)^T g_b: both products read g_b)
+      for (int bi = 0; !push && bi < nblk; ++bi) {
+        const LUBlock& b = plan.blocks[bi];
+        const int64_t k0 = b.k0;
+        if ((e = launch_skinny_t<T>(b.w, nr, A + k0 * ld, ld, B, ldb, k0, A + k0 + k0 * ld, ld, B + k0, ldb, b.w,
+                                    GEMM_MASK_LOWER, X, part_elems, B + k0, ldb, st, NB, sA, sB, sB)) != hipSuccess)
+          return e;
+      }
+      for (int bi = 0; push && bi + 1 < nblk; ++bi) {
         const LUBlock& b = plan.blocks[bi];
         const int64_t k0 = b.k0, c1 = k0 + b.w;
         if ((e = launch_skinny_push<T>(b.w, n - c1, A + k0 + c1 * ld, ld, B + k0, B + c1, ldb, nr, st, NB, sA, sB)) !=
@@ -2004,7 +2029,7 @@ hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, c
           return e;
       }
       // then for b = k..1: z_b = L11^-T z_b - (L21 L11^-1)^T z_below, and z = P_b^T z
-      if (!perm) {
+      if (push && !perm) {
         if ((e = launch_skinny_diag_t<T>(true, n, nb, A, ld, B, ldb, nr, st, NB, sA, sB)) != hipSuccess) return e;
         for (int bi = nblk - 1; bi > 0; --bi) {
           const LUBlock& b = plan.blocks[bi];
@@ -2021,6 +2046,7 @@ hipError_t lu_solve(int trans, const void* Av, int64_t ld, const LUPlan& plan, c
                                     ldb, b.w, GEMM_MASK_STRICT_UPPER, X, part_elems, B + k0, ldb, st, NB, sA, sB, sB)) !=
             hipSuccess)
           return e;
+        if (!perm) continue;
         const int32_t* dst = ws.pairs + bi * 4 * (size_t)nb;
         const int32_t* src = dst + 2 * nb;
         hipLaunchKernelGGL(row_permute_inv_kernel<T>, dim3((unsigned)nr, NB), dim3(256), 0, st, B, ldb, (int64_t)0, dst,

@@ -11,10 +11,10 @@
 // eight columns, m = 1500 9.9 us (14.6).
 //
 // A transposed solve subtracts a block's part from the later columns as soon as it
-// is known (skinny_push_kernel).  Where interchanges come between the blocks (L^T
-// of a pivoting panel's factors), a step instead gathers its 128-row block from a
-// long product (k up to n): C[w x nr] -= op(A)^T B, and the transposed refinement
-// residual is the same shape with w = n.  Each output is the dot product of a
+// is known (skinny_push_kernel).  For few blocks or many columns, and where
+// interchanges come between the blocks (L^T of a pivoting panel's factors), a step
+// instead gathers its 128-row block from a long product (k up to n): C[w x nr] -=
+// op(A)^T B, and the transposed refinement residual is the same shape with w = n.  Each output is the dot product of a
 // stored column of A with B: one wave per column, lanes along k (coalesced
 // column reads), the k range split into chunks of KC rows, one partial sum per
 // (chunk, column) reduced across the wave; the masked diagonal block is one
@@ -34,6 +34,7 @@ __device__ inline bool sk_keep(int kind, int64_t r, int64_t c) {
   switch (kind) {
     case GEMM_MASK_STRICT_LOWER: return r > c;
     case GEMM_MASK_UPPER: return r <= c;
+    case GEMM_MASK_LOWER: return r >= c;
     case GEMM_MASK_STRICT_UPPER: return r < c;
     default: return true;
   }

@@ -232,3 +232,50 @@ def test_getrf_long_columns(ctx, dtype, lda):
         err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
         assert err.max() <= 8 * n * (2.2e-16 if dtype == torch.complex128 else 1.2e-7), (trans, err)
     assert all(bool((F[j, n:] == 7).all()) for j in range(n))
+
+
+@pytest.mark.parametrize("dtype,n,nrhs", [(torch.complex64, 120, 3), (torch.complex64, 200, 1), (torch.complex64, 2000, 230),
+                                          (torch.complex128, 250, 1), (torch.complex128, 400, 4), (torch.complex128, 500, 6),
+                                          (torch.complex128, 1000, 3), (torch.complex128, 1500, 140)])
+def test_transposed_sweeps(ctx, dtype, n, nrhs):
+    """Both sides of the choice between pushing and gathering transposed sweeps (few
+    blocks, many columns): the bound above."""
+    rng = np.random.default_rng(n + nrhs)
+    A = 2 * np.eye(n) + (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(2 * n)
+    A = A[rng.permutation(n)]
+    B = rng.standard_normal((nrhs, n)) + 1j * rng.standard_normal((nrhs, n))
+    F = torch.as_tensor(A.T.copy()).to(device="cuda", dtype=dtype).contiguous()
+    X = torch.as_tensor(B).to(device="cuda", dtype=dtype).contiguous()
+    ctx.getrf(F)
+    ctx.getrs(F, X, 1)
+    ref = np.linalg.solve(A.T, B.T).T
+    err = np.linalg.norm(X.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 8 * n * (2.2e-16 if dtype == torch.complex128 else 1.2e-7), err
+
+
+@pytest.mark.parametrize("dims,parts", [((7, 10, 10), 2), ((5, 4, 3), 3), ((5, 4, 7), 3)])
+def test_transposed_sweeps_without_interchanges(ctx, dims, parts):
+    """The adjoint's solves on speculative FP64 factors: gradients of 102 plane waves
+    in one call (n = 2100: gathered) against the sum of parts of 51 (pushed), of 9 in
+    one (n = 420: pushed) against threes (gathered), and n = 180, gathered either way.
+    Condition numbers below 100 leave 1e-11 a factor of 400 over eps times that."""
+    import gdm_inputs as gi
+    rng = np.random.default_rng(11)
+    r = gi.cuboid_cells(*dims, 7.0)
+    ctx.set_environment(1.1)
+    ctx.set_structure(r, 7.0, rng.uniform(2.0, 6.0, len(r)) + 0.2j)
+    before = ctx.pivot_fallbacks()
+    ctx.factorize(640.0, 0)
+    assert ctx.pivot_fallbacks() == before
+    nr = 102 if len(r) > 500 else 9
+    k, e0 = gi.random_planewaves(rng, nr)
+    gs = torch.as_tensor(rng.uniform(0.5, 1.5, (nr, 3)))
+    f0 = ctx.incident_planewave(k, e0)
+    q, f = ctx.solve(f0)
+    whole = [t.cpu().numpy() for t in ctx.adjoint(k, e0, f0, q, f, gs)]
+    sums = [0.0] * 3
+    for p in np.array_split(np.arange(nr), parts):
+        got = ctx.adjoint(k[p], e0[p], f0[p], q[p], f[p], gs[p])
+        sums = [a + t.cpu().numpy() for a, t in zip(sums, got)]
+    for a, b in zip(whole, sums):
+        assert np.linalg.norm(a - b) <= 1e-11 * np.linalg.norm(b)
