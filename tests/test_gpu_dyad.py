@@ -66,3 +66,34 @@ def test_far_field_sum_edges(ctx, cells, eff, nrhs):
     scale = np.abs(O.cross_sections(D, q.T, q.T, q.T, np.ones(nrhs))["rad"]) + np.abs(ref)
     # near-field terms cancel in the imaginary part: their size relative to the radiated power is below 1e4 here
     assert np.max(np.abs(cs[:, 4] - ref) / scale) <= 1e-9, (cs[:, 4], ref)
+
+
+@pytest.mark.parametrize("cells,eff,nrhs", [(63, 2, 5), (65, 1, 1), (257, 0, 3), (260, 70, 9)])
+def test_far_field_sum_against_its_terms(ctx, cells, eff, nrhs):
+    """The same sum against the size of its own terms.  Both sides round a dyad to
+    eps (10 + kR) of its norm (kR below 100 here) and add N terms per target one
+    after another: 2.2e-16 (110 + 330) < 1e-13 of sum_ij |q_i| |G_ij| |q_j| on each
+    side; 1e-12 leaves a factor of five over both."""
+    import gdm_inputs as gi
+    from oracle import gdm_oracle as O
+    rng = np.random.default_rng(cells + eff)
+    r = gi.cuboid_cells(7, 7, (cells + 48) // 49, 6.0)[:cells]
+    re = np.stack([150.0 + 90.0 * np.arange(eff), np.zeros(eff), 30.0 * (np.arange(eff) % 3)], 1)
+    k, e0 = gi.random_planewaves(rng, nrhs)
+    w = dict(r_cell=r, step=6.0, eps_cell=np.full(cells, 5.0 + 0.2j), n_env=1.2, wavelength=600.0, r_eff=re,
+             alpha_eff=gi.mie_like_alpha6(rng, eff, 600.0, 1.2), khat=k, e0=e0, r_probe=np.zeros((0, 3)))
+    ctx.set_environment(1.2)
+    ctx.set_structure(r, 6.0, w["eps_cell"], re if eff else None, w["alpha_eff"] if eff else None)
+    ctx.set_wavelength(600.0)
+    q = rng.standard_normal((nrhs, ctx.n)) + 1j * rng.standard_normal((nrhs, ctx.n))
+    t = torch.as_tensor(q)
+    cs = ctx.cross_sections(t, t, t, torch.ones(nrhs, dtype=torch.float64), want_ff=True).cpu().numpy()
+    D = O.Dipoles(w)
+    ref = O.sca_farfield_doublesum(D, q.T, np.ones(nrhs))
+    R = D.pos[:, None, :] - D.pos[None, :, :]
+    same = np.all(R == 0.0, axis=-1)
+    g = np.linalg.norm(O.green6(np.where(same[..., None], 1.0, R), D.k0, D.n_env), axis=(2, 3))
+    g[same] = 0.0
+    size = np.linalg.norm(D.to6(q.T), axis=1)  # [N, rhs]
+    terms = 4 * np.pi * D.k0 / D.n_env * np.einsum("ir,ij,jr->r", size, g, size)
+    assert np.max(np.abs(cs[:, 4] - ref) / terms) <= 1e-12, (cs[:, 4], ref, terms)
