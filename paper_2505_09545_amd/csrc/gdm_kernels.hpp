@@ -341,7 +341,7 @@ hipError_t launch_tri_panel(cplx<T>* A, int64_t ld, int nb, int64_t k0, int w, i
                             int64_t sflag, SplitOut lout, SplitOut uout, int64_t ssplit);
 hipError_t launch_split_rows(const float2* X, int64_t ld, int64_t nrows, int w, SplitOut out, hipStream_t st, int nbatch,
                              int64_t sX, int64_t ssplit);
-// C (m x n) -= L U from split operands (update_split.hip), k a multiple of 16; sl,
+// C (m x n) -= L U from split operands (update_split.hip), k 128 or 64; sl,
 // su: the scales of L's rows and U's columns; sL bytes, sC entries per item
 hipError_t launch_update_split(int64_t m, int64_t n, int k, const void* L, const void* U, const float* sl, const float* su,
                                float2* C, int64_t ldc, hipStream_t st, int num_cu, int nbatch, int64_t sL, int64_t sC);

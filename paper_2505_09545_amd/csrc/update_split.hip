@@ -95,17 +95,16 @@ __device__ inline void grouped_tile(int t, int tiles_m, int tiles, int& tm, int&
 // workgroup's fragments go through one of two LDS buffers (loaded into registers
 // a step ahead), one barrier per step; C is loaded during the k loop, an equal
 // part per step.  Three or four workgroups fit a CU, which overlaps one's
-// epilogue with another's products.  NKT: k / 16 (8 or 4; 0: any).
+// epilogue with another's products.  NKT: k / 16 (8 or 4).
 // m = n = 3000, k = 128: 47 us, 195 TFLOP/s by 8 m n k (128 x 128 tiles of 8
 // waves 52-58 us); the 3M form in FP32 instructions took 94 us.
 template <int NKT>
 __global__ void __launch_bounds__(256)
-update_split_kernel(int64_t m, int64_t n, int nkt_any, const u32x4* __restrict__ L, const u32x4* __restrict__ U,
+update_split_kernel(int64_t m, int64_t n, const u32x4* __restrict__ L, const u32x4* __restrict__ U,
                     const float* __restrict__ sl, const float* __restrict__ su, float2* __restrict__ C, int64_t ldc,
                     int tiles_m, int tiles, int64_t sL, int64_t sC) {
   constexpr int NF = 16, FW = 4;             // fragments per step (8 of the rows, 8 of the columns), per wave
-  constexpr int CE = NKT > 0 ? 16 / NKT : 0;  // entries of C loaded per step
-  const int nkt = NKT > 0 ? NKT : nkt_any;
+  constexpr int CE = 16 / NKT;               // entries of C loaded per step
   L += (int64_t)blockIdx.y * (sL / 16);
   U += (int64_t)blockIdx.y * (sL / 16);
   sl += (int64_t)blockIdx.y * (sL / 4);
@@ -124,7 +123,7 @@ update_split_kernel(int64_t m, int64_t n, int nkt_any, const u32x4* __restrict__
   const u32x4* src[FW];
 #pragma unroll
   for (int i = 0; i < FW; ++i)
-    src[i] = (i < 2 ? L + (int64_t)(2 * tm + i) * nkt * 256 : U + (int64_t)(2 * tn + i - 2) * nkt * 256) + wave * 64;
+    src[i] = (i < 2 ? L + (int64_t)(2 * tm + i) * NKT * 256 : U + (int64_t)(2 * tn + i - 2) * NKT * 256) + wave * 64;
   u32x4 st[FW];
   auto gload = [&](int kt) {
 #pragma unroll
@@ -159,21 +158,15 @@ update_split_kernel(int64_t m, int64_t n, int nkt_any, const u32x4* __restrict__
   sstore(0);
   __syncthreads();
   auto step = [&](int kt) {
-    if (kt + 1 < nkt) gload(kt + 1);
+    if (kt + 1 < NKT) gload(kt + 1);
 #pragma unroll
     for (int e = 0; e < CE; ++e) cload(CE * kt + e);
     __builtin_amdgcn_sched_barrier(0);
     mma(kt & 1);
-    if (kt + 1 < nkt) sstore((kt + 1) & 1);
+    if (kt + 1 < NKT) sstore((kt + 1) & 1);
     __syncthreads();
   };
-  if constexpr (NKT > 0) {
-    static_for<NKT>([&](auto kt) { step(kt); });
-  } else {
-    for (int kt = 0; kt < nkt; ++kt) step(kt);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) cload(q);
-  }
+  static_for<NKT>([&](auto kt) { step(kt); });
   // C -= (acc 2^a) 2^b
   const float fr = sl[row];
 #pragma unroll
@@ -334,7 +327,7 @@ int64_t split_planes_bytes(int64_t rows, int k) { return ((rows + 127) / 128) * 
 hipError_t launch_update_split(int64_t m, int64_t n, int k, const void* L, const void* U, const float* sl, const float* su,
                                float2* C, int64_t ldc, hipStream_t st, int num_cu, int nbatch, int64_t sL, int64_t sC) {
   if (m <= 0 || n <= 0 || k <= 0 || nbatch <= 0) return hipSuccess;
-  if (nbatch > 65535 || k % 16 || sL % 16) return hipErrorInvalidValue;
+  if (nbatch > 65535 || (k != 128 && k != 64) || sL % 16) return hipErrorInvalidValue;
   const auto* l = static_cast<const u32x4*>(L);
   const auto* u = static_cast<const u32x4*>(U);
   const int64_t entries = m * n;
@@ -355,11 +348,10 @@ hipError_t launch_update_split(int64_t m, int64_t n, int k, const void* L, const
   if (tm * tn > INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(tm * tn), (unsigned)nbatch);
 #define GDM_SPLIT(NKT)                                                                                                 \
-  hipLaunchKernelGGL(update_split_kernel<NKT>, grid, dim3(256), 0, st, m, n, k / 16, l, u, sl, su, C, ldc, (int)tm,      \
+  hipLaunchKernelGGL(update_split_kernel<NKT>, grid, dim3(256), 0, st, m, n, l, u, sl, su, C, ldc, (int)tm,      \
                      (int)(tm * tn), sL, sC)
   if (k == 128) GDM_SPLIT(8);
-  else if (k == 64) GDM_SPLIT(4);
-  else GDM_SPLIT(0);
+  else GDM_SPLIT(4);
 #undef GDM_SPLIT
   return hipGetLastError();
 }
