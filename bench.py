@@ -481,8 +481,10 @@ def main() -> int:
         "backward_err": be,
         **res,
         # the update's products run on the f16 matrix cores (three per real
-        # product, 833 TFLOP/s by the 8 m n k count); what bounds it is the
-        # traffic of the trailing matrix, 16 bytes per entry and 128 k
+        # product, 833 TFLOP/s by the 8 m n k count).  Counted against HBM: the
+        # trailing matrix's traffic, 16 bytes per entry and 128 k, is the larger
+        # of two limits (465 of 723 us alone at n = 11 872, LDS reads with the
+        # products 450) that overlap badly, so neither is reached
         "roofline": {"bound": "hbm", "achieved": achieved * 1e3 * UPDATE_BYTES_PER_FLOP, "peak": PEAK_HBM, "unit": "GB/s",
                      "frac": achieved * 1e3 * UPDATE_BYTES_PER_FLOP / PEAK_HBM, "traffic": update_gemm_traffic(),
                      "tflops_8mnk": achieved,

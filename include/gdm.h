@@ -81,7 +81,9 @@ const char* gdm_last_error(const gdm_ctx* ctx);
 /* Limit on the device memory this context's buffers may hold (bytes; 0: no
  * limit, the default).  A call that would need more fails with GDM_E_OOM before
  * it allocates, as it would when the device itself is full; the batched
- * spectra size their groups within the limit.  GDM_E_ARG for bytes < 0. */
+ * spectra size their groups within the limit.  Buffers that only speed a call up
+ * are done without, or given back, where they would not fit.  GDM_E_ARG for
+ * bytes < 0. */
 gdm_status gdm_set_memory_limit(gdm_ctx* ctx, int64_t bytes);
 /* Device bytes the context's buffers hold now. */
 int64_t gdm_memory_used(const gdm_ctx* ctx);

@@ -59,7 +59,8 @@ struct Dyad {
 template <bool WANT_V> __device__ inline Dyad dyad_at(double R2, double k) {
   // 1/R: the hardware's approximation (about 2^-23) with one third-order step.
   // The phase k R goes on in two parts: rounded to one it would be off by half an
-  // ulp of itself, the largest error of a distant pair.
+  // ulp of itself, the largest error of a distant pair (E of 4784 dipoles against
+  // 80-bit sums: 2.1e-15; by a kernel that rounded it once 4.7e-15).
   double y = __builtin_amdgcn_rsq(R2);
   const double e = fma(-R2 * y, y, 1.0);
   y = fma(y * e, fma(e, 0.375, 0.5), y);

@@ -1,8 +1,8 @@
 // Complex GEMM on the CDNA matrix cores, used for the trailing update of the
 // blocked right-looking LU (arXiv:2505.09545, Sec. "Numerical solution": the
-// coupled system is solved by LU decomposition; FP32 updates of blocks of 64 or
-// 128 columns have kernels of their own) and for the FP64 residual of iterative
-// refinement.
+// coupled system is solved by LU decomposition; FP32 updates of factors that are
+// refined take update_split.hip, small ones solve_step.hip) and for the FP64
+// residual of iterative refinement.
 //
 // Storage: column-major, interleaved complex.  Viewed as real matrices, an
 // m x k complex A is a 2m x k real matrix whose rows alternate (re, im).  The

@@ -16,7 +16,8 @@
 //          M = P1^T L1 P2^T L2 ... Pk^T Lk U
 //      and the solve applies P_b before using L_b, which is equivalent.
 //   3. U12 = L11^-1 A12 (tiles.hip), 4. A22 -= L21 U12 (complex GEMM on MFMA,
-//      gemm.hip).  With look-ahead, step 3 and step 4 for the next panel's
+//      gemm.hip; FP32 factors that are refined: update_split.hip; small updates:
+//      solve_step.hip).  With look-ahead, step 3 and step 4 for the next panel's
 //      columns run on the main stream and the rest of step 4 on a side stream,
 //      overlapping the next panel.
 //   5. after the last block, the solve-ready form of all blocks (tiles.hip).

@@ -1,5 +1,5 @@
 // Block steps of the triangular solves with more than a few right-hand sides
-// (and the look-ahead columns of the FP64 factorisation): C[m x nr] -= A[m x k]
+// (and the small trailing updates of FP64 and caller's FP32 factorisations): C[m x nr] -= A[m x k]
 // X[k x nr] with k <= 128, rows [ar0, ar0 + adw) of A a triangle.  A solve is a
 // chain of these products, each a few microseconds of matrix-core work, so what
 // bounds it is the latency inside a launch: loads, products, one reduction,

@@ -180,10 +180,10 @@ update_split_kernel(int64_t m, int64_t n, const u32x4* __restrict__ L, const u32
 // second one out) walks its share of the 128 x 128 tiles as one stream of k
 // steps.  The fragments of a step are loaded into registers two steps ahead,
 // across tile ends; a tile's entries of C are loaded during its first steps and
-// its results stored while the next tile's products start.  What bounds it is
-// the traffic of C (16 bytes per entry at 128 k: 465 us alone at m = n = 11 872)
-// beside the LDS reads and products (450 us alone).  m = n = 11 872: 723 us, 200
-// TFLOP/s by 8 m n k (one workgroup per tile 850 us; without the non-temporal
+// its results stored while the next tile's products start.  Two limits that
+// overlap badly: the traffic of C (16 bytes per entry at 128 k: 465 us alone at m =
+// n = 11 872) and the LDS reads with the products (450 us alone); neither is
+// reached.  m = n = 11 872: 723 us, 200 TFLOP/s by 8 m n k (one workgroup per tile 850 us; without the non-temporal
 // accesses 750-780; the 3M form in FP32 instructions 1365); m = n = 6000: 172 us
 // (64 x 64 tiles 200-250).
 template <bool NT>
